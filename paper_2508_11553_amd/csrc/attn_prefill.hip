@@ -37,18 +37,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void prefill_kernel(PrefillArgs a)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Workgroup i runs on XCD i % 8, and each XCD has its own L2.  All query blocks of one
-    // (sequence, kv head) read the same K/V, so they get consecutive slots of ONE XCD (query
-    // block fastest, late positions = long ranges first): they run side by side, walk the
-    // range at about the same pace, and all but the first find the tiles in that L2.
-    const unsigned per_xcd = gridDim.x / kXcds;  // the grid is padded to a multiple of kXcds
-    const unsigned item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int Hv = a.Hkv * a.HB;
-    if (item >= (unsigned)a.q_blocks * (unsigned)a.B * (unsigned)Hv) return;
-    const int jb = a.q_blocks - 1 - (int)(item % a.q_blocks);
-    const HeadBlock hb = head_block((item / a.q_blocks) % Hv, a.G, a.HB);
+    const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
+    if (item.block >= a.q_blocks) return;
+    const int jb = a.q_blocks - 1 - item.block;
+    const HeadBlock hb = head_block(item.pair % Hv, a.G, a.HB);
     const int g = hb.g;
-    const int b = item / ((unsigned)a.q_blocks * Hv);
+    const int b = item.pair / Hv;
     const int tpb = units_per_block(a.G);  // query tokens per column block
     const int tpw = kPrefillBlocks * tpb;                        // and per wave
 
@@ -185,14 +180,13 @@ __global__ __launch_bounds__(kW * 64) void prefill_wide_kernel(PrefillArgs a)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned per_xcd = gridDim.x / kXcds;  // the grid is padded to a multiple of kXcds
-    const unsigned item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     const int Hv = a.Hkv * a.HB;
-    if (item >= (unsigned)a.q_blocks * (unsigned)a.B * (unsigned)Hv) return;
-    const int jb = a.q_blocks - 1 - (int)(item % a.q_blocks);
-    const HeadBlock hb = head_block((item / a.q_blocks) % Hv, a.G, a.HB);
+    const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
+    if (item.block >= a.q_blocks) return;
+    const int jb = a.q_blocks - 1 - item.block;
+    const HeadBlock hb = head_block(item.pair % Hv, a.G, a.HB);
     const int g = hb.g;
-    const int b = item / ((unsigned)a.q_blocks * Hv);
+    const int b = item.pair / Hv;
     const int tpb = units_per_block(a.G);  // query tokens per column block
     const int tpw = NB * tpb;              // and per wave
 
@@ -322,9 +316,8 @@ __global__ __launch_bounds__(kW * 64) void prefill_wide_kernel(PrefillArgs a)
 hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipStream_t stream, hipEvent_t start,
                           hipEvent_t stop)
 {
-    const unsigned items = (unsigned)a.q_blocks * (unsigned)a.B * (unsigned)(a.Hkv * a.HB);
-    if (items == 0) return hipSuccess;
-    const unsigned grid = (items + kXcds - 1) / kXcds * kXcds;
+    const unsigned grid = prefill_grid(a.q_blocks, a.B * a.Hkv * a.HB);
+    if (grid == 0) return hipSuccess;
     const dim3 g(grid), b(prefill_waves(kv_dtype, head_dim) * 64);
     auto go = [&](auto kernel) {
         if (start || stop)
