@@ -225,10 +225,14 @@ SD_DEV void online_softmax_folded(const float (&s)[8], float c, float (&p)[8], S
 // ---------------------------------------------------------------------------
 template <int D>
 struct Bf16Path {
+    typedef Bf16Path<D> B;                                // whose parked form a tile has
     static constexpr int kDim = D;
     static constexpr int kTileBytes = kPage * D * 2;      // one (page, head) tile
     static constexpr int kScratchBytes = 2 * kTileBytes;  // K of one 32-token tile in LDS
     static constexpr int kOpsBytes = (D / 16) * 1024;     // the V^T operands of one tile in LDS
+    static constexpr int kImageBytes = kScratchBytes;     // K image of a parked tile
+    static constexpr int kParkedBytes = kImageBytes + kOpsBytes;   // and the whole of it
+    static constexpr bool kScaled = false;                // a parked tile comes without scales
     static constexpr int kPieces = D / 8;                 // 16-byte pieces per K row
     static constexpr int kRowsPerLoad = 64 / kPieces;     // K rows one 1024-byte load covers
     typedef WaveState<D> State;
@@ -472,6 +476,11 @@ struct Bf16Path {
     // exponent.  The weight sum is one more accumulator fed an all-ones operand,
     // i.e. the sum of the rounded weights exactly.
     //
+    // SCALED (fp8 pools, whose codes were parked as bf16): `scales` points at the tile's PageScales.  A score's exponent is
+    // s * (c * k_scale) + log2(v_scale), so that the weight carries the page's V scale and multiplies the raw
+    // codes; what the sum accumulator is fed is then 1 / v_scale instead of ones, in three bf16
+    // parts (rows 0, 1, 2 of every four), which sums the very weights the product uses to fp32 precision.
+    //
     // Order of issue.  A wave issues in program order, and a matrix instruction
     // holds the matrix pipe for 16 cycles of which its issue takes 4.  With several
     // blocks and no mask (the tiles below the diagonal: nearly all) the vector
@@ -480,15 +489,22 @@ struct Bf16Path {
     // second product of block 0 after the last block), a few vector instructions per
     // matrix instruction, so that both pipes work at once within one wave.  Tiles
     // with a mask take the plain order (products, softmax, products).
-    template <int NB, bool MASK>
+    template <int NB, bool MASK, bool SCALED = false>
     SD_DEV static void attend_parked(const u32x4 (&ka)[D / 32], const u32x4 (&kb)[D / 32], const char *vslot,
                                      const u32x4 (&qop)[NB][D / 32], ParkedState (&st)[NB], float c, int tok0,
-                                     int lane, const int (&row_end)[NB], bool tile_has_end = true)
+                                     int lane, const int (&row_end)[NB], bool tile_has_end = true, const char *scales = nullptr)
     {
         constexpr int S = D / 32, K = D / 16;
         constexpr bool kBeside = NB > 1 && !MASK;
         const int qd = lane >> 4;
-        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // bf16 1.0 pairs
+        u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // bf16 1.0 pairs
+        float ca = c, cb = c, oa = 0.f, ob = 0.f;   // per page: exponent = s * c + o
+        if (SCALED) {
+            const f32x4 sc = *reinterpret_cast<const f32x4 *>(scales);
+            const u32x2 part = *reinterpret_cast<const u32x2 *>(scales + 16 + (lane & 3) * 8);
+            ca = c * sc[0], cb = c * sc[1], oa = sc[2], ob = sc[3];
+            ones = u32x4{part[0], part[0], part[1], part[1]};
+        }
         f32x4 sa[NB], sb[NB];
         u32x4 va[K], pop[NB];
 #pragma unroll
@@ -535,10 +551,20 @@ struct Bf16Path {
                 x[e] = sa[b][e];
                 x[4 + e] = sb[b][e];
             }
+            constexpr bool kScaledFirst = SCALED && !kBeside;   // ahead of the mask: a page's scale may be 0
+            if (kScaledFirst) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] = __builtin_fmaf(x[e], ca, oa);
+                    x[4 + e] = __builtin_fmaf(x[4 + e], cb, ob);
+                }
+            }
             if (MASK && tile_has_end) mask_scores(x, tok0, row_end[b], qd);
             auto weights = [&]() {
+                const float na = oa - st[b].m, nb = ob - st[b].m;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[e], c, -st[b].m));
+                for (int e = 0; e < 8; ++e)
+                    p[e] = __builtin_amdgcn_exp2f(kScaledFirst ? x[e] - st[b].m : __builtin_fmaf(x[e], e < 4 ? ca : cb, SCALED ? (e < 4 ? na : nb) : -st[b].m));
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) pop[b][e >> 1] = cvt_pk_bf16(p[e], p[e + 1]);
             };
@@ -560,7 +586,14 @@ struct Bf16Path {
                     // kLead above the row's maximum: its weights are then at most 2^-kLead (nothing is lost:
                     // bf16 has fp32's exponent range), and the row's scores can grow by kLead + 1 octaves
                     // before the reference has to move again
-                    advance_max(st[b], max_of(st[b].m, head_max(max8(x)) * c + kLead));
+                    if (SCALED) {
+                        float y[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf(x[e], e < 4 ? ca : cb, e < 4 ? oa : ob);
+                        advance_max(st[b], max_of(st[b].m, head_max(max8(y)) + kLead));
+                    } else {
+                        advance_max(st[b], max_of(st[b].m, head_max(max8(x)) * c + kLead));
+                    }
                     weights();
                 }
                 if (b == NB - 2) {
@@ -569,7 +602,7 @@ struct Bf16Path {
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
-                advance_max(st[b], max_of(st[b].m, head_max(max8(x)) * c));
+                advance_max(st[b], max_of(st[b].m, SCALED ? head_max(max8(x)) : head_max(max8(x)) * c));
                 weights();
             }
         }
@@ -589,6 +622,8 @@ struct Bf16Path {
         }
     }
     SD_DEV static float weight_sum(const ParkedState &st) { return st.acc[D / 16][0]; }
+    // fed the three parts of 1 / v_scale
+    SD_DEV static float scaled_weight_sum(const ParkedState &st) { return st.acc[D / 16][0] + st.acc[D / 16][1] + st.acc[D / 16][2]; }
 
     // this lane's accumulators -> row `dst` ([D] floats)
     template <class S>
@@ -615,6 +650,29 @@ struct Bf16Path {
             }
     }
 };
+
+// Scales of a tile of an fp8 pool that is parked as bf16: {k_scale, k_scale} and {log2 |v_scale|, log2 |v_scale|} of its two pages,
+// then 1 / |v_scale| as three bf16 parts (hi, mid, lo, and a zero), each twice in a word: [part][page].
+constexpr int kPageScalesBytes = 48;
+// A negative V scale turns the signs of its page's codes (the weights are positive); a V scale of 0 zeroes them and counts as 1.
+SD_DEV unsigned sign_codes(float v_scale) { return v_scale < 0.f ? 0x80808080u : 0u; }
+SD_DEV void park_scales(char *dst, int half, float ks, float vs, int lane)
+{
+    const float v = vs != 0.f ? __builtin_fabsf(vs) : 1.0f;
+    const float inv = 1.0f / v;
+    const float hi = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, inv) & 0xffff0000u);
+    const float mid = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, inv - hi) & 0xffff0000u);
+    const float lo = inv - hi - mid;   // at most 8 significant bits are left
+    const float part = lane == 0 ? hi : lane == 1 ? mid : lane == 2 ? lo : 0.f;
+    if (lane < 4) {
+        const unsigned u = __builtin_bit_cast(unsigned, part);
+        *reinterpret_cast<unsigned *>(dst + 16 + lane * 8 + half * 4) = pack_hi(u, u);
+    }
+    if (lane == 0) {
+        *reinterpret_cast<float *>(dst + half * 4) = ks;
+        *reinterpret_cast<float *>(dst + 8 + half * 4) = __builtin_log2f(v);
+    }
+}
 
 // ---------------------------------------------------------------------------
 // fp8 e4m3fn pools, head_dim 128: rows of 128 bytes, tiles of 2 KB.  The codes
@@ -651,6 +709,62 @@ struct Fp8Path {
         for (int j = 0; j < 4; ++j) r.v[pg][j] = kv_load<STREAM>(reinterpret_cast<const u32x2 *>(vl + j * D));
         r.ks[pg] = ((ConstScales)ks)[si];
         r.vs[pg] = ((ConstScales)vs)[si];
+    }
+
+    // One page brought on its own and parked as bf16: the codes are converted once, by the wave that loads them, into the
+    // K image and the V^T operands that the bf16 path of head_dim 128 works with; its tile step does the rest.
+    typedef Bf16Path<128> B;
+    static constexpr int kImageBytes = B::kImageBytes;
+    static constexpr int kParkedBytes = B::kParkedBytes + kPageScalesBytes;
+    static constexpr bool kScaled = true;
+    struct Page {
+        u32x4 k[2];   // as Tile, one page
+        u32x2 v[4];
+        float ks, vs;
+    };
+    template <bool STREAM>
+    SD_DEV static void load_one(Page &r, const char *kp, const char *vp, const float *ks, const float *vs, int64_t si, int lane)
+    {
+        r.k[0] = kv_load<STREAM>(reinterpret_cast<const u32x4 *>(kp + lane * 16));
+        r.k[1] = kv_load<STREAM>(reinterpret_cast<const u32x4 *>(kp + 1024 + lane * 16));
+        const char *vl = vp + (lane >> 4) * 4 * D + (lane & 15) * 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r.v[j] = kv_load<STREAM>(reinterpret_cast<const u32x2 *>(vl + j * D));
+        r.ks = ((ConstScales)ks)[si];
+        r.vs = ((ConstScales)vs)[si];
+    }
+    SD_DEV static void park_one(Page &r, char *slot, int half, int lane, int tok0, int t_end)
+    {
+        char *kdst = slot + half * B::kTileBytes;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int row = 8 * j + (lane >> 3);   // the lane's 16 codes: d = 16 * (lane & 7) .. +16
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const unsigned lo = r.k[j][2 * hh], hi = r.k[j][2 * hh + 1];
+                const int piece = (2 * (lane & 7) + hh) ^ row;
+                *reinterpret_cast<u32x4 *>(kdst + row * (D * 2) + piece * 16) =
+                    u32x4{cvt_pk_bf16_fp8<false>(lo), cvt_pk_bf16_fp8<true>(lo), cvt_pk_bf16_fp8<false>(hi), cvt_pk_bf16_fp8<true>(hi)};
+            }
+        }
+        const unsigned flip = sign_codes(r.vs), keep = r.vs != 0.f ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            r.v[j] = (r.v[j] & u32x2{keep, keep}) ^ u32x2{flip, flip};
+            if (tok0 + 4 * (lane >> 4) + j >= t_end) r.v[j] = u32x2{0, 0};   // tokens that do not exist
+        }
+        char *vdst = slot + kImageBytes + lane * 16 + half * 8;
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                unsigned f[4];   // codes 4w + 2hi and the next one of four tokens
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] = hi ? cvt_pk_bf16_fp8<true>(r.v[j][w]) : cvt_pk_bf16_fp8<false>(r.v[j][w]);
+                *reinterpret_cast<u32x2 *>(vdst + (4 * w + 2 * hi) * 1024) = u32x2{pack_lo(f[0], f[1]), pack_lo(f[2], f[3])};
+                *reinterpret_cast<u32x2 *>(vdst + (4 * w + 2 * hi + 1) * 1024) = u32x2{pack_hi(f[0], f[1]), pack_hi(f[2], f[3])};
+            }
+        park_scales(slot + B::kParkedBytes, half, r.ks, r.vs, lane);
     }
 
     // fp8 pools take new tokens through kv_append_fp8 (a page's scale may have to change)
@@ -922,6 +1036,47 @@ struct Fp8Path64 {
 
     // four codes -> four bf16
     SD_DEV static u32x2 cvt4(unsigned w) { return u32x2{cvt_pk_bf16_fp8<false>(w), cvt_pk_bf16_fp8<true>(w)}; }
+
+    // One page on its own, as in the 128-wide fp8 path.
+    static constexpr int kImageBytes = B::kImageBytes;
+    static constexpr int kParkedBytes = B::kParkedBytes + kPageScalesBytes;
+    static constexpr bool kScaled = true;
+    struct Page {
+        u32x4 k;
+        unsigned v[4];
+        float ks, vs;
+    };
+    template <bool STREAM>
+    SD_DEV static void load_one(Page &r, const char *kp, const char *vp, const float *ks, const float *vs, int64_t si, int lane)
+    {
+        r.k = kv_load<STREAM>(reinterpret_cast<const u32x4 *>(kp + lane * 16));
+        const char *vl = vp + (lane >> 4) * 4 * D + (lane & 15) * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r.v[j] = kv_load<STREAM>(reinterpret_cast<const unsigned *>(vl + j * D));
+        r.ks = ((ConstScales)ks)[si];
+        r.vs = ((ConstScales)vs)[si];
+    }
+    SD_DEV static void park_one(Page &r, char *slot, int half, int lane, int tok0, int t_end)
+    {
+        const int row = lane >> 2;
+        char *kdst = slot + half * B::kTileBytes + row * (D * 2);
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const u32x2 lo = cvt4(r.k[2 * hh]), hi = cvt4(r.k[2 * hh + 1]);
+            *reinterpret_cast<u32x4 *>(kdst + ((2 * (lane & 3) + hh) ^ (row % B::kPieces)) * 16) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+        const unsigned flip = sign_codes(r.vs), keep = r.vs != 0.f ? 0xffffffffu : 0u;
+        u32x2 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = cvt4(tok0 + 4 * (lane >> 4) + j >= t_end ? 0u : (r.v[j] & keep) ^ flip);
+        char *vdst = slot + kImageBytes + lane * 16 + half * 8;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            *reinterpret_cast<u32x2 *>(vdst + 2 * w * 1024) = u32x2{pack_lo(v[0][w], v[1][w]), pack_lo(v[2][w], v[3][w])};
+            *reinterpret_cast<u32x2 *>(vdst + (2 * w + 1) * 1024) = u32x2{pack_hi(v[0][w], v[1][w]), pack_hi(v[2][w], v[3][w])};
+        }
+        park_scales(slot + B::kParkedBytes, half, r.ks, r.vs, lane);
+    }
 
     // The lane's 16 codes are two 16-byte pieces of the bf16 row; they go where the bf16 path's k_store
     // would have put them, so that its k_fetch reads them back.

@@ -74,11 +74,29 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
     const int rest = pairs % kXcds, classes = prefill_classes(rest);
     return (unsigned)(pairs / kXcds * kXcds) * (unsigned)q_blocks + (rest ? (unsigned)(rest * classes) * (unsigned)((q_blocks + classes - 1) / classes) : 0u);
 }
-constexpr int kPrefillBlocks = 2;   // 16-row column blocks one wave of the causal pass carries
-constexpr int kPrefillWideWaves = 8; // waves of a workgroup of the causal pass over bf16 pools with head_dim 128 (else kWaves)
-// Waves per workgroup of the causal pass for a pool type (0 = bf16, 1 = fp8) and head size: the host sizes the grid with it.
-// (At head_dim 64 three workgroups of 4 waves fit a compute unit and beat one of 8.)
-__host__ __device__ inline int prefill_waves(int kv_dtype, int head_dim) { return kv_dtype == 0 && head_dim == 128 ? kPrefillWideWaves : kWaves; }
+// Column blocks of 16 query rows that one workgroup of the causal pass owns: 16, 8, 4 or 2.  Large blocks share a
+// tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several waves
+// share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip:
+// head_dim 128 runs one workgroup per compute unit, head_dim 64 two or three, and blocks of 16 beat blocks of 8 there
+// only from four rounds of the chip on.  A wave keeps at least four tiles of the longest range to itself.
+// Measured, us with 16 / 8 / 4 / 2 blocks:
+//   head_dim 128, 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads      150 /  98 /  91 / 100
+//                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      296 / 278 / 360 / 419
+//                 8 sequences of 2 k - 8 k, 512 - 1400 queries, 32/8 heads     579 / 634 / 834 / -
+//                 1 sequence of 3000, 64 queries, 16/2 heads                    88 /  58 /  42 /  30
+//                 10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads        36 /  27 /  21 /  26
+//   head_dim 64   16 sequences of 8192, 2048 queries, 32/8 heads              1885 / 2029 / 2373 / 3678
+//                 16 whole prompts of 200 - 1000, 32/8 heads                    72 /  61 / 109 / 225
+//                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      203 / 161 / 157 / 222
+//                 3 sequences of 1 k - 6 k, 50 - 400 queries, 32/8 heads       137 /  92 /  49 /  40
+__host__ inline int prefill_blocks(int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
+{
+    const auto workgroups = [&](int blocks) { return (total_q / (blocks * units) + batch) * heads; };   // about
+    if (head_dim == 64) return workgroups(16) >= 2048 ? 16 : workgroups(8) >= 512 ? 8 : workgroups(4) >= 512 || max_context_len < 1024 ? 4 : 2;
+    if (workgroups(16) >= 256 || max_context_len < 256) return 16;
+    if (workgroups(8) >= 256 || max_context_len < 512) return 8;
+    return workgroups(4) >= 256 || max_context_len < 1024 ? 4 : 2;
+}
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens
 // [c*chunk, (c+1)*chunk).  With a shared prefix of `sh` tokens (a multiple of
@@ -203,7 +221,8 @@ struct PrefillArgs {
     uint32_t q_keep;             // 0 when scale == 0 (all scores are zero: zero queries, scale 1), else all ones
     int32_t B, Hq, Hkv, G, HB, max_blocks, max_context_len;  // HB: head blocks per KV head, ceil(G / 16)
     int32_t total_q, max_q_len;  // rows of q; host-known bound on the rows of one sequence
-    int32_t q_blocks;            // workgroups (prefill_waves x kPrefillBlocks x 16/G query tokens each) that cover max_q_len
+    int32_t blocks;              // column blocks of 16 rows that a workgroup owns (see prefill_blocks)
+    int32_t q_blocks;            // workgroups (blocks x 16/G query tokens each) that cover max_q_len
 };
 
 struct AppendArgs {

@@ -175,3 +175,18 @@ def test_scores_that_outgrow_the_running_reference(sd, shape, d, kv_dtype):
             first = np.arange(0, L, 16)
             wl.k_scales[wl.block_table[b, first // 16], :] *= factor(first + 15)[:, None].astype(np.float32)
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
+
+
+@pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("bf16", 64), ("fp8", 128), ("fp8", 64)])
+@pytest.mark.parametrize("blocks", [16, 8, 4, 2])
+def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
+    """Each size of a workgroup's row block (the small ones split the range over the waves) at its edges; one sequence's fp8
+    scales include a V scale of 0 and a negative one, which are turned into codes when a page is parked."""
+    from tests.test_prefill_geometry import block_case
+    lens, nq, Hq, Hkv = block_case(blocks, d)
+    wl, q, q_start = make(lens, nq, Hq, Hkv, d, kv_dtype, seed=300 + blocks + d)
+    if kv_dtype == "fp8":
+        pages = wl.block_table[len(lens) - 1]
+        wl.v_scales[pages[0]] = 0.0
+        wl.v_scales[pages[1]] *= -1.0
+    check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)

@@ -14,6 +14,10 @@ PROGRAM = r"""
 #include "kernels.h"
 int main(int argc, char **argv)
 {
+    if (argc > 3) {
+        printf("%d\n", sd::prefill_blocks(atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])));
+        return 0;
+    }
     const int q_blocks = atoi(argv[1]), pairs = atoi(argv[2]);
     const unsigned grid = sd::prefill_grid(q_blocks, pairs);
     std::vector<int> seen((size_t)pairs * q_blocks, 0), per_die(sd::kXcds, 0);
@@ -51,3 +55,28 @@ def test_every_item_is_dealt_once_and_to_every_die_alike(program, q_blocks, pair
     assert missing == 0
     assert grid % 8 == 0 and grid < pairs * q_blocks + 7 * 8   # what is padded: a class's last block of a left-over pair
     assert hi - lo <= 7   # at most one block per left-over pair
+
+
+def block_case(blocks, d):
+    """(lens, queries, Hq, Hkv): a small batch that the rule gives workgroups of `blocks` column blocks, with sequences on both
+    sides of a page, a tile, a round and a workgroup's rows."""
+    edge = [1, 15, 16, 17, 31, 33, 129, 255, 256, 257]
+    if d == 128:
+        lens, q, Hq, Hkv = {16: (edge * 4, [1, 3, 17, 33] * 10, 16, 8),
+                            8: (edge + [700, 512], [300] * 12, 16, 8),
+                            4: (edge[4:] + [700], [120] * 7, 8, 4),
+                            2: (edge[4:] + [1030, 1500], [70] * 8, 8, 4)}[blocks]
+    else:
+        lens, q, Hq, Hkv = {16: (edge * 7, [1, 3, 17, 33, 2] * 14, 32, 32),
+                            8: (edge + edge[2:], [1, 40, 130] * 6, 32, 32),
+                            4: (edge[4:] + [700], [120] * 7, 8, 4),
+                            2: (edge[4:] + [1030, 1500], [70] * 8, 8, 4)}[blocks]
+    return lens, [min(n, L) for n, L in zip(q, lens)], Hq, Hkv
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("blocks", [16, 8, 4, 2])
+def test_the_block_cases_are_what_they_say(program, blocks, d):
+    lens, q, Hq, Hkv = block_case(blocks, d)
+    got = subprocess.run([program] + [str(x) for x in (d, sum(q), len(lens), Hkv, 16 // (Hq // Hkv), max(lens))], capture_output=True, text=True, check=True)
+    assert int(got.stdout) == blocks
