@@ -413,6 +413,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
         rm.tile_off = ra.tile_off;
         rm.merge_rec = ra.merge_rec;
         rm.by_sequence = ra.B <= ra.ranges;
+        rm.groups = sd::merge_groups(rl.rblocks, ra.B);
         rm.ws_m = ra.ws_m;
         rm.ws_l = ra.ws_l;
         rm.ws_acc = ra.ws_acc;

@@ -30,6 +30,8 @@
 // The same kernel with PROBE = true issues exactly the same loads and does no
 // arithmetic on them beyond an XOR fold: its duration is what the memory system
 // delivers for this walk.
+#include <type_traits>
+
 #include "attn_tile.h"
 
 namespace sd {
@@ -51,59 +53,67 @@ SD_DEV int64_t partial_slot(int r, int gv, int Hv, int o0, int per)
     return ((int64_t)r * Hv + gv) * 2 + (o0 > r * per ? 1 : 0);
 }
 
-// Combines the partials that the ranges of `parts` hold for the `rows` query heads of one
-// (sequence, head block) and writes columns [col0, col0 + DW) of the rows of `out` starting at
-// row0.  One wave: the 64 lanes share the rows out (a row goes to 64 / R2 neighbouring lanes, R2 the
-// power of two >= rows, each lane a run of DW * R2 / 64 >= 4 floats) and PB partials are fetched at
-// a time, all loads in flight together, so up to PB partials cost one trip to memory.  Partials
-// are folded in range order with a running maximum.
-template <int PB, int NL_MAX>
+// Combines the partials that the ranges of `parts` hold for up to kMergeRows query heads of one
+// (sequence, head block), heads r0 .. r0 + rows - 1 of the block, and writes columns [col0, col0 + 64) of their rows of
+// `out` starting at row0.  16 lanes take a row, 16 bytes each, and PB partials are fetched at
+// a time, all loads in flight together, so up to PB partials cost one trip to memory.  a.groups
+// waves take turns over the batches of PB partials (this one is number `group`) and group 0
+// adds their sums up through `lds`.  Partials are folded in a fixed order with a running maximum.
+template <int D>
 SD_DEV void combine_parts(const RangeMergeArgs &a, const LiveParts &parts, int gv, int Hv, int o0, int per,
-                          int rows, int64_t row0, int D, int col0, int DW, int lane)
+                          int r0, int rows, int64_t row0, int col0, int lane, int group, float *lds)
 {
-    const int R2 = rows > 8 ? 16 : rows > 4 ? 8 : rows > 2 ? 4 : rows > 1 ? 2 : 1;
-    const int lpr = min(64 / R2, DW / 4);   // lanes per row
-    const int F = DW / lpr;                 // floats per lane
-    const int NL = F / 4;                   // 16-byte loads per lane and partial (<= NL_MAX)
-    const int mr = lane / lpr, c = lane - mr * lpr;
-    if (mr >= rows) return;
+    constexpr int PB = kMergeParts;
+    const int mr = lane >> 4, col = col0 + (lane & 15) * 4;
+    const bool mine = mr < rows;
     float M = -INFINITY, den = 0.f;
-    f32x4 num[NL_MAX];
-#pragma unroll
-    for (int j = 0; j < NL_MAX; ++j) num[j] = f32x4{0, 0, 0, 0};
-    for (int base = 0; base < parts.count; base += PB) {
-        float m[PB], l[PB];
-        f32x4 v[PB][NL_MAX];
-#pragma unroll
-        for (int p = 0; p < PB; ++p) {
-            const bool valid = base + p < parts.count;   // wave-uniform
-            const int64_t ps = partial_slot(parts.range(valid ? base + p : 0), gv, Hv, o0, per);
-            m[p] = valid ? a.ws_m[ps * kMaxGroup + mr] : -INFINITY;
-            l[p] = valid ? a.ws_l[ps * kMaxGroup + mr] : 0.f;
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(a.ws_acc + (ps * a.rows_stride + mr) * D + col0 + c * F);
-#pragma unroll
-            for (int j = 0; j < NL_MAX; ++j) v[p][j] = valid && j < NL ? src[j] : f32x4{0, 0, 0, 0};
-        }
+    f32x4 num = {0, 0, 0, 0};
+    auto fold = [&](const auto &m, const auto &l, const auto &v, auto count) {
         float Mn = M;
 #pragma unroll
-        for (int p = 0; p < PB; ++p) Mn = fmaxf(Mn, m[p]);
+        for (int p = 0; p < count; ++p) Mn = fmaxf(Mn, m[p]);
         const float shrink = __builtin_amdgcn_exp2f(M - Mn);  // first batch: exp2(-inf) = 0 on zeros
         M = Mn;
         den *= shrink;
+        num *= shrink;
 #pragma unroll
-        for (int j = 0; j < NL_MAX; ++j) num[j] *= shrink;
-#pragma unroll
-        for (int p = 0; p < PB; ++p) {
+        for (int p = 0; p < count; ++p) {
             const float w = __builtin_amdgcn_exp2f(m[p] - M);
             den += w * l[p];
+            num += w * v[p];
+        }
+    };
+    if (mine)
+        for (int base = group * PB; base < parts.count; base += a.groups * PB) {
+            float m[PB], l[PB];
+            f32x4 v[PB];
 #pragma unroll
-            for (int j = 0; j < NL_MAX; ++j) num[j] += w * v[p][j];
+            for (int p = 0; p < PB; ++p) {
+                const bool valid = base + p < parts.count;   // wave-uniform
+                const int64_t ps = partial_slot(parts.range(valid ? base + p : 0), gv, Hv, o0, per);
+                m[p] = valid ? a.ws_m[ps * kMaxGroup + r0 + mr] : -INFINITY;
+                l[p] = valid ? a.ws_l[ps * kMaxGroup + r0 + mr] : 0.f;
+                v[p] = valid ? *reinterpret_cast<const f32x4 *>(a.ws_acc + (ps * a.rows_stride + r0 + mr) * D + col) : f32x4{0, 0, 0, 0};
+            }
+            fold(m, l, v, std::integral_constant<int, PB>{});
+        }
+    if (a.groups > 1) {   // [group][lane]: sums, then maximum and weight sum
+        const int used = min(a.groups, (parts.count + PB - 1) / PB);   // later groups had nothing to do
+        float *at = lds + (group * 64 + lane) * 4, *head = lds + a.groups * 64 * 4 + (group * 64 + lane) * 2;
+        if (group > 0 && group < used) {
+            *reinterpret_cast<f32x4 *>(at) = num;
+            *reinterpret_cast<f32x2 *>(head) = f32x2{M, den};
+        }
+        __syncthreads();
+        if (group > 0) return;
+        for (int w = 1; w < used; ++w) {
+            const f32x2 h = *reinterpret_cast<const f32x2 *>(head + w * 64 * 2);
+            const float m[1] = {h[0]}, l[1] = {h[1]};
+            const f32x4 v[1] = {*reinterpret_cast<const f32x4 *>(at + w * 64 * 4)};
+            fold(m, l, v, std::integral_constant<int, 1>{});
         }
     }
-    float *dst = a.out + (row0 + mr) * D + col0 + c * F;
-#pragma unroll
-    for (int j = 0; j < NL_MAX; ++j)
-        if (j < NL) *reinterpret_cast<f32x4 *>(dst + 4 * j) = num[j] / den;
+    if (mine) *reinterpret_cast<f32x4 *>(a.out + (row0 + mr) * D + col) = num / den;
 }
 
 // Two waves per SIMD, also for the probe, whose few registers would otherwise let the dispatcher
@@ -369,15 +379,25 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // Merge pass of the range design.  A sequence that one range held whole was written by the wave
-// that walked it; a sequence that was cut is combined here.  One workgroup of two waves (each takes
-// half of the columns) per item; an item is a (sequence, head block) when the batch has fewer
-// sequences than the grid has ranges, else a (range, head block): the range pass leaves, per range,
+// that walked it; a sequence that was cut is combined here.  One workgroup per item and slice of kMergeRows
+// query heads: a.groups sets of waves (a wave of a set takes 64 columns); an item is a (sequence, head block) when
+// the batch has fewer sequences than the grid has ranges, else a (range, head block): the range pass leaves, per range,
 // a record of the cut sequence whose first part lies there (at most one).
+//
+// Latency-bound: tile offsets -> parts -> out.  A set of waves fetches 16 parts per trip to memory; the few long
+// sequences at the end of a rollout leave up to a part per workgroup of the range pass, so the
+// host gives small batches more sets (merge_groups), and heads are spread over workgroups because one compute unit
+// would take 16 us for the 2 MB of parts that 16 heads leave.  Against one workgroup of two waves per item, us per decode step:
+// 3 sequences of 9 k - 33 k, 32/8 heads 33.7 -> 31.1; one of 20 k, 32/8 heads 30.0 -> 23.2, fp8, 32/4 heads 29.9 -> 20.6;
+// two of 9 k - 39 k, 32/2 heads 43 -> 22; batches of 8 and more unchanged.
 template <int D>
-__global__ __launch_bounds__(128) void range_merge_kernel(RangeMergeArgs a)
+__global__ __launch_bounds__(D * kMaxMergeGroups) void range_merge_kernel(RangeMergeArgs a)
 {
+    extern __shared__ __attribute__((aligned(16))) float merge_lds[];
     const int Hv = a.Hkv * a.HB;
-    const int lane = threadIdx.x & 63, half = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % (D / 64), group = wave / (D / 64);
+    const int r0 = blockIdx.y * kMergeRows;
     const int gv = blockIdx.x % Hv;
     int b, o0, o1, T;
     if (a.by_sequence) {
@@ -393,24 +413,23 @@ __global__ __launch_bounds__(128) void range_merge_kernel(RangeMergeArgs a)
     // parts that were handed over inside a workgroup are in their neighbour's; a sequence with a single part
     // left was written by the wave that held it
     const LiveParts parts = live_parts(o0, o1, T, per);
-    if (parts.count == 1) return;
     const HeadBlock hb = head_block(gv, a.G, a.HB);
-    const int64_t row0 = (int64_t)b * a.Hq + hb.head0;
-    if (hb.rows > kMaxGroup / 2)
-        combine_parts<8, D / 32>(a, parts, gv, Hv, o0, per, hb.rows, row0, D, half * (D / 2), D / 2, lane);
-    else
-        combine_parts<16, (D / 64 > 0 ? D / 64 : 1)>(a, parts, gv, Hv, o0, per, hb.rows, row0, D, half * (D / 2), D / 2, lane);
+    if (parts.count == 1 || r0 >= hb.rows) return;   // everything so far was workgroup-uniform
+    combine_parts<D>(a, parts, gv, Hv, o0, per, r0, min(kMergeRows, hb.rows - r0), (int64_t)b * a.Hq + hb.head0 + r0, part * 64, lane, group,
+                     merge_lds + part * a.groups * (kMergeLdsBytes / 4));
 }
 
 hipError_t launch_range_merge(const RangeMergeArgs &a, int head_dim, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
 {
-    const unsigned grid = (unsigned)(a.by_sequence ? a.B : a.ranges) * (unsigned)(a.Hkv * a.HB);
-    if (grid == 0 || a.B == 0) return hipSuccess;
+    const unsigned items = (unsigned)(a.by_sequence ? a.B : a.ranges) * (unsigned)(a.Hkv * a.HB);
+    if (items == 0 || a.B == 0) return hipSuccess;
+    const dim3 grid(items, (unsigned)(a.rows_stride + kMergeRows - 1) / kMergeRows);
+    const size_t lds = a.groups > 1 ? (size_t)(head_dim / 64 * a.groups) * kMergeLdsBytes : 0;
     auto go = [&](auto kernel) {
         if (start || stop)
-            hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(128), 0, stream, start, stop, 0, a);
+            hipExtLaunchKernelGGL(kernel, grid, dim3(head_dim * a.groups), lds, stream, start, stop, 0, a);
         else
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(128), 0, stream, a);
+            hipLaunchKernelGGL(kernel, grid, dim3(head_dim * a.groups), lds, stream, a);
     };
     if (head_dim == 128)
         go(range_merge_kernel<128>);

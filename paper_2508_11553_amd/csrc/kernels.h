@@ -197,7 +197,22 @@ struct RangeMergeArgs {
     float *out;
     int32_t B, Hq, Hkv, G, HB, ranges, min_tiles, rows_stride;
     int32_t by_sequence;         // items are (sequence, head block) instead of (range, head block)
+    int32_t groups;              // waves that share the parts of an item (see merge_groups)
 };
+constexpr int kMergeRows = 4;         // query heads of an item that one workgroup of the merge pass combines
+constexpr int kMergeParts = 16;       // parts a wave of it fetches per trip to memory
+constexpr int kMaxMergeGroups = 8;    // and the most waves that share the parts of an item
+constexpr int kMergeLdsBytes = 64 * (16 + 8);   // LDS of one wave when several do: a lane's sums, a row's maximum and weight sum
+// Waves that share the parts of an item.  A sequence leaves at most about one part per workgroup of its head (`rblocks`); one that is
+// twice as long as the average 2 * rblocks / batch.  (With room for four times the average 8 sequences of 1 k to 9 k were 2 % slower: a
+// barrier for nothing.)
+__host__ inline int merge_groups(int rblocks, int batch)
+{
+    const int64_t parts = (int64_t)2 * rblocks / batch < rblocks ? (int64_t)2 * rblocks / batch : rblocks;
+    int groups = 1;
+    while (groups < kMaxMergeGroups && groups * kMergeParts < parts) groups *= 2;
+    return groups;
+}
 
 struct MergeArgs {
     const float *ws_m, *ws_l, *ws_acc;

@@ -138,6 +138,15 @@ def test_parts_handed_over_inside_a_workgroup(sd, Hq, Hkv, d, kv_dtype, min_rang
     assert torch.equal(dw.attend(), got)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (4, 1), (5, 1), (16, 1), (17, 1), (20, 2)])
+@pytest.mark.parametrize("lens", [[21000], [17, 9000, 5000], [3000] * 9])
+def test_few_long_sequences_leave_many_parts(sd, lens, Hq, Hkv, d):
+    # up to 512 parts of one sequence: several waves share them in the merge pass, each over several trips; fewer: some waves have none
+    wl = workloads.make_custom(lens, Hq, Hkv, d, seed=900 + Hq + d + len(lens))
+    check(gpu_attend(wl), oracle_full(wl))
+
+
 def test_more_sequences_than_ranges(sd):
     """1300 short sequences: more than the grid has ranges per head, so the merge pass works from the records the
     range pass leaves per range; ranges of twelve tiles cut many of the sequences, inside workgroups and between them."""
