@@ -226,9 +226,10 @@ int paged_decode_attention(const sd_shape *shape, const void *q,
  * is the K/V of sequence b's newest token, whose position is
  * context_lens[b] - 1 (the lengths passed already count it).  The result is
  * that of kv_append(rows at those positions) followed by
- * paged_decode_attention, bit for bit in the pool; where the range pass runs,
- * the wave that walks a sequence's last tile takes the token from the rows and
- * writes it into its slot, so no separate append kernel is launched.
+ * paged_decode_attention, bit for bit in the pool; the wave that walks a
+ * sequence's last tile takes the token from the rows and writes it into its
+ * slot, so no separate append kernel is launched (except for batches above
+ * 4096 sequences that need the chunked passes).
  * Sequences with context_lens <= 0 are left alone (zero rows in `out`).
  * SD_BF16 pools only (SD_EUNSUPPORTED otherwise: fp8 pools take new tokens
  * through kv_append_fp8).  Other arguments as for paged_decode_attention;

@@ -431,7 +431,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
         return SD_OK;
     }
 
-    if (k_new) {   // these passes read the newest token from the pool: put it there first
+    if (k_new && !direct) {   // the chunked passes read the newest token from the pool: put it there first
         sd::AppendArgs ap;
         ap.k_new = static_cast<const uint4 *>(k_new);
         ap.v_new = static_cast<const uint4 *>(v_new);
@@ -492,6 +492,11 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     sa.group_items = (uint32_t)group_items;
     sa.max_shared_len = max_shared_len;
     sa.out_direct = direct ? out : nullptr;
+    const bool in_place = direct && k_new;
+    sa.k_new = in_place ? static_cast<const uint16_t *>(k_new) : nullptr;
+    sa.v_new = in_place ? static_cast<const uint16_t *>(v_new) : nullptr;
+    sa.k_pages_out = in_place ? static_cast<uint16_t *>(const_cast<void *>(k_pages)) : nullptr;
+    sa.v_pages_out = in_place ? static_cast<uint16_t *>(const_cast<void *>(v_pages)) : nullptr;
 
     sd::MergeArgs ma;
     ma.ws_m = sa.ws_m;

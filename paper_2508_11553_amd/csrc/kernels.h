@@ -118,6 +118,9 @@ struct SplitArgs {
     float *ws_l;                 // [B][Hq][S]   sum of weights
     float *ws_acc;               // [B][Hq][S][D] weighted V sum
     float *out_direct;           // [B][Hq][D] or null: every sequence is one chunk, write the output instead of partials
+    // append and attend in one go (single-chunk mode, bf16 pools; all null otherwise), as in RangeArgs
+    const uint16_t *k_new, *v_new;
+    uint16_t *k_pages_out, *v_pages_out;
     float scale_log2e;           // scale * log2(e)
     // the shared-prefix items fold a non-negative scale into their exponent: |scale| * log2(e), the sign as a
     // bit flip of the queries (0x80008000 when scale < 0), and zeroed queries with scale 1 when scale == 0

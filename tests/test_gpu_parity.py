@@ -299,7 +299,7 @@ def test_append_and_attend_in_one_call(sd, Hq, Hkv, d, min_range):
     """paged_decode_attention_append = kv_append of every sequence's newest token + attention over it: pool bytes equal
     the oracle's append bit for bit, the output matches the oracle run over the appended pool.  Lengths put the
     newest token first in its page, last in its page, alone in the sequence, first of a new tile; one sequence is
-    empty.  Ranges of 4096 tokens cover every sequence, which takes the path that launches the append separately."""
+    empty.  Ranges of 4096 tokens cover every sequence, which takes the single-pass path."""
     import torch
     lens = [1, 2, 16, 17, 32, 33, 34, 0, 64, 65, 513, 700, 1025, 1]
     wl = workloads.make_custom(lens, Hq, Hkv, d, seed=500 + Hq + d, append=True)
