@@ -14,8 +14,7 @@
 // parked, once per workgroup, and then take the bf16 pools' tile step (12 sequences of 2.5 k to 8 k tokens, 700 to
 // 2048 queries, 32/8 heads: 1.50 -> 1.28 ms against converting K in every consuming wave).
 //
-// Bound by the matrix pipe and by the latency between dependent stages with two waves per SIMD: 16 x 8192 / 2048 queries,
-// 32/8 heads, d = 128, bf16 runs at 1.1 PFLOP/s.
+// Large calls over bf16 pools, whose rows need no conversion, have kernels of their own further down.
 //
 // The causal limit is a per-lane token bound in the score mask; a wave stops
 // once a tile starts at or past the last position any of its rows may see.
@@ -32,6 +31,76 @@
 #include "attn_tile.h"
 
 namespace sd {
+
+// Which query rows a wave owns (everything but `n`-dependent values is wave-uniform).
+struct PrefillRows {
+    HeadBlock hb;
+    int b, qs, nq, L;
+    int base;           // position of query 0 (may be negative)
+    int kv_end;         // tokens the workgroup's last row sees
+    int tpb, iw0;       // query tokens per column block; the wave's first query token
+    int max_end;        // its last row's limit
+    int min_end;        // its first visible row's limit
+    int first_end;      // limit of the last row of its first column block; those of the others lie tpb apart
+    bool active;        // some row of the wave sees a token
+
+    // The rows of wave group `group` of `groups` with `blocks` column blocks each; false: the workgroup has nothing to do.
+    SD_DEV bool find(const PrefillArgs &a, int groups, int group, int blocks)
+    {
+        const int Hv = a.Hkv * a.HB;
+        const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
+        if (item.block >= a.q_blocks) return false;
+        const int jb = a.q_blocks - 1 - item.block;
+        hb = head_block(item.pair % Hv, a.G, a.HB);
+        b = item.pair / Hv;
+        tpb = units_per_block(a.G);
+        const int tpw = blocks * tpb;   // query tokens per wave
+        qs = a.q_start[b];
+        nq = min(a.q_start[b + 1] - qs, a.max_q_len);
+        const int i0 = jb * groups * tpw;
+        if (i0 >= nq) return false;
+        if (qs < 0 || (int64_t)qs + nq > a.total_q) return false;  // rows outside q: nothing is read or written
+        L = max(0, min(a.context_lens[b], a.max_context_len));
+        base = L - nq;
+        kv_end = max(0, base + min(nq, i0 + groups * tpw));
+        iw0 = i0 + group * tpw;
+        const int iw1 = min(iw0 + tpw, nq);
+        active = iw0 < nq && base + iw1 > 0;
+        max_end = base + iw1;
+        min_end = max(0, base + iw0) + 1;
+        first_end = base + iw0 + tpb;
+        return true;
+    }
+    // row of column block c in this lane (n = lane & 15): query token, whether it exists, whether it sees a token
+    // (recomputed where needed rather than kept in registers across the loop)
+    SD_DEV int locate(const PrefillArgs &a, int c, int n, bool &in_range, bool &row_ok, int64_t &row) const
+    {
+        const int i = iw0 + c * tpb + n / hb.rows;
+        in_range = n / hb.rows < tpb && i < nq;
+        row_ok = in_range && base + i >= 0;
+        row = ((int64_t)qs + i) * a.Hq + hb.head0 + n % hb.rows;
+        return i;
+    }
+    // Q^T operands, limits and empty sums of the wave's column blocks.  Rows that see nothing ride along with zero queries, masked
+    // only past the sequence's end.  The exponent's reference starts finite: a wave may meet only tokens that a row does not see.
+    template <class B, int NB, class State>
+    SD_DEV void load(const PrefillArgs &a, int lane, u32x4 (&qop)[NB][B::kDim / 32], int (&row_end)[NB], State (&st)[NB]) const
+    {
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            bool in_range, row_ok;
+            int64_t row;
+            const int i = locate(a, c, lane & 15, in_range, row_ok, row);
+            row_end[c] = row_ok ? base + i + 1 : L;
+#pragma unroll
+            for (int s = 0; s < B::kDim / 32; ++s)
+                qop[c][s] = row_ok ? (*reinterpret_cast<const u32x4 *>(a.q + row * B::kDim + B::q_offset(s, lane)) & a.q_keep) ^ a.q_flip
+                                   : u32x4{0, 0, 0, 0};
+            reset(st[c]);
+            st[c].m = -FLT_MAX;
+        }
+    }
+};
 
 template <class P, int kW, int NB>
 struct PrefillLds {
@@ -62,62 +131,17 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int Hv = a.Hkv * a.HB;
-    const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
-    if (item.block >= a.q_blocks) return;
-    const int jb = a.q_blocks - 1 - item.block;
-    const HeadBlock hb = head_block(item.pair % Hv, a.G, a.HB);
-    const int g = hb.g;
-    const int b = item.pair / Hv;
-    const int tpb = units_per_block(a.G);  // query tokens per column block
-    const int tpw = NB * tpb;              // and per wave
     const int group = wave / kSplit, part = wave % kSplit;
-
-    // everything below up to the loop is workgroup-uniform
-    const int qs = a.q_start[b];
-    const int nq = min(a.q_start[b + 1] - qs, a.max_q_len);
-    const int i0 = jb * kGroups * tpw;
-    if (i0 >= nq) return;
-    if (qs < 0 || (int64_t)qs + nq > a.total_q) return;  // rows outside q: nothing is read or written
-    const int L = max(0, min(a.context_lens[b], a.max_context_len));
-    const int base = L - nq;                                        // position of query 0 (may be negative)
-    const int kv_end = max(0, base + min(nq, i0 + kGroups * tpw));  // tokens the block's last row sees
-
-    // this wave's rows
-    const int iw0 = i0 + group * tpw;
-    const int iw1 = min(iw0 + tpw, nq);
-    const bool active = iw0 < nq && base + iw1 > 0;  // some row of the wave sees a token
-    const int wave_max_end = base + iw1;              // its last row's limit
-    const int wave_min_end = max(0, base + iw0) + 1;  // its first visible row's limit
+    PrefillRows rows;
+    if (!rows.find(a, kGroups, group, NB)) return;
+    const int g = rows.hb.g, L = rows.L;
     const int n = lane & 15;
-    // row of column block c in this lane: query token, whether it exists, whether it sees a token
-    // (recomputed where needed rather than kept in registers across the loop)
-    auto locate = [&](int c, int n, bool &in_range, bool &row_ok, int64_t &row) {
-        const int i = iw0 + c * tpb + n / hb.rows;
-        in_range = n / hb.rows < tpb && i < nq;
-        row_ok = in_range && base + i >= 0;
-        row = ((int64_t)qs + i) * a.Hq + hb.head0 + n % hb.rows;
-        return i;
-    };
     int row_end[NB];
     u32x4 qop[NB][D / 32];
     typename P::B::ParkedState st[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-        bool in_range, row_ok;
-        int64_t row;
-        const int i = locate(c, n, in_range, row_ok, row);
-        // rows that see nothing ride along with zero queries, masked only past the sequence's end
-        row_end[c] = row_ok ? base + i + 1 : L;
-#pragma unroll
-        for (int s = 0; s < D / 32; ++s)
-            qop[c][s] = row_ok ? (*reinterpret_cast<const u32x4 *>(a.q + row * D + P::B::q_offset(s, lane)) & a.q_keep) ^ a.q_flip
-                               : u32x4{0, 0, 0, 0};
-        reset(st[c]);
-        st[c].m = -FLT_MAX;   // finite: a split may meet only tokens that a row does not see
-    }
+    rows.load<typename P::B>(a, lane, qop, row_end, st);
 
-    const int32_t *bt = a.block_table + (int64_t)b * a.max_blocks;
+    const int32_t *bt = a.block_table + (int64_t)rows.b * a.max_blocks;
     const int64_t page_bytes = (int64_t)P::kTileBytes * a.Hkv;
     const char *kbase = static_cast<const char *>(a.k_pages) + g * P::kTileBytes;
     const char *vbase = static_cast<const char *>(a.v_pages) + g * P::kTileBytes;
@@ -132,15 +156,15 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
         P::B::k_fetch(slot, lane, ka, kb);
         P::B::template attend_parked<NB, decltype(masked)::value, P::kScaled>(ka, kb, slot + P::kImageBytes, qop, st, a.scale_log2e,
                                                                              tile * kTileTokens, lane, row_end, true,
-                                                                             slot + P::B::kParkedBytes);
+                                                                             slot + P::B::kParkedBytes, rows.first_end, rows.tpb);
     };
-    const int ntiles = (kv_end + kTileTokens - 1) / kTileTokens;
-    const int last_page = (kv_end + kPage - 1) / kPage - 1;
+    const int ntiles = (rows.kv_end + kTileTokens - 1) / kTileTokens;
+    const int last_page = (rows.kv_end + kPage - 1) / kPage - 1;
 
     if constexpr (kOwn) {
         // tiles wave, wave + kW, ...: those below `plain` end at or before the first visible row's limit
         const int count = ntiles > wave ? (ntiles - wave + kW - 1) / kW : 0;
-        const int plain = wave_min_end / kTileTokens;
+        const int plain = rows.min_end / kTileTokens;
         char *mine = lds + wave * kSlot;
         if (count > 0) {
             Page r[2];
@@ -211,11 +235,11 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
                         if (rd + 2 < rounds) issue(r[i], next_page[i]);
                     }
                 }
-                if (active) {
+                if (rows.active) {
                     // the round's tiles below the diagonal of every row of the wave, then those on it
                     const int t0 = kTiles * rd * kTileTokens;
-                    const int j_end = min(kTiles, (wave_max_end - t0 + kTileTokens - 1) / kTileTokens);
-                    const int j_plain = max(0, min(j_end, (wave_min_end - t0) / kTileTokens));
+                    const int j_end = min(kTiles, (rows.max_end - t0 + kTileTokens - 1) / kTileTokens);
+                    const int j_plain = max(0, min(j_end, (rows.min_end - t0) / kTileTokens));
                     int j = part;
 #pragma unroll 1
                     for (; j < j_plain; j += kSplit) step(cur + j * kSlot, kTiles * rd + j, std::false_type{});
@@ -234,7 +258,7 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
             const float l = weight_sum(c);
             bool in_range, row_ok;
             int64_t row;
-            locate(c, n, in_range, row_ok, row);
+            rows.locate(a, c, n, in_range, row_ok, row);
             if (!in_range) continue;
             const float inv = row_ok ? 1.0f / l : 0.0f;  // rows before the sequence's first token get zeros
 #pragma unroll
@@ -263,7 +287,7 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
             const int c = rr >> 4, rn = rr & 15;
             bool in_range, row_ok;
             int64_t row;
-            locate(c, rn, in_range, row_ok, row);
+            rows.locate(a, c, rn, in_range, row_ok, row);
             if (!in_range) continue;
             float M = -FLT_MAX, den = 0.f;
             f32x4 num = {0, 0, 0, 0};
@@ -278,6 +302,384 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
             }
             *reinterpret_cast<f32x4 *>(a.out + row * D + col) = row_ok ? num / den : f32x4{0, 0, 0, 0};
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// bf16 pools, large calls.  K and V rows go from memory straight into LDS, without passing through registers: a tile's
+// slot holds K of its two pages and V of its two pages as rows, and the V^T operands are formed by
+// transposing LDS reads.  That leaves the registers and the vector instructions of parking (a fifth of the tile step's) to
+// the tile step.  A row's 16-byte pieces are permuted as they are loaded, so that the reads spread over all banks:
+// K piece c of row r sits at c ^ r (as in k_store), V's 32-byte units at unit ^ row.
+//
+// The slots are separate arrays, and the loops are written out over them: reads of one array do not wait for loads
+// into another only where the compiler can tell the two apart.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 *LdsVector;
+typedef __attribute__((address_space(3))) s16x4 *LdsTransposed;
+
+// 16 bytes per lane from global memory straight into LDS: lane l's, at byte `offset` of the `bytes` at `src` (wave-uniform), land
+// at dst + 16 * l.
+SD_DEV void load_to_lds(const char *src, int bytes, int offset, char *dst)
+{
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(src), 0, bytes, 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)dst, 16, offset, 0, 0, 0);
+}
+// Waits for all but the newest N loads into LDS of this wave; for its LDS reads and writes.  (s_waitcnt: vmcnt in bits 0-3 and 14-15, expcnt
+// in 4-6, lgkmcnt in 8-11.)
+template <int N>
+SD_DEV void wait_loads()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0f70);
+    asm volatile("" ::: "memory");
+}
+SD_DEV void wait_lds()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("" ::: "memory");
+}
+// A bare barrier: what must have arrived is waited for by name, loads under way stay under way.
+SD_DEV void phase_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// What one wave brings of every slot, and where the operands of a slot lie for a lane.
+template <int D>
+struct RowSlot {
+    static constexpr int kPageBytes = Bf16Path<D>::kTileBytes;   // K or V of one page and head
+    static constexpr int kBytes = 4 * kPageBytes;                // K of pages 0 and 1, V of pages 0 and 1
+    static constexpr int kRowBytes = D * 2, kPieces = D / 8;
+    SD_DEV static int v_unit(int row) { return D == 128 ? row & 7 : row >> 1 & 3; }
+    // byte of a K (kind 0) or V (kind 1) page that belongs at byte `at` of its image
+    SD_DEV static int source(int kind, int at)
+    {
+        const int row = at / kRowBytes, piece = at % kRowBytes / 16;
+        return row * kRowBytes + (piece ^ (kind ? v_unit(row) << 1 : row % kPieces)) * 16;
+    }
+    // K row lane & 15, d = 32 s + 8 (lane >> 4) .. +8, of the slot's first page (the second kPageBytes on)
+    SD_DEV static int k_at(int s, int lane) { return (lane & 15) * kRowBytes + ((4 * s + (lane >> 4)) ^ (lane % 16 % kPieces)) * 16; }
+    // V^T operand k, first page: the transposing read gives this lane column 16 k + (lane & 15) of rows 4 (lane >> 4) .. +3
+    SD_DEV static int v_at(int k, int lane)
+    {
+        const int row = 4 * (lane >> 4) + ((lane >> 2) & 3);
+        return 2 * kPageBytes + row * kRowBytes + 8 * (lane & 3) + ((k ^ v_unit(row)) << 5);
+    }
+    // `at` is one offset from an array: with more address arithmetic the compiler loses track of which array it is
+    SD_DEV static void fetch_k(const char *buf, int offset, int lane, u32x4 (&ka)[D / 32], u32x4 (&kb)[D / 32])
+    {
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) {
+            const int at = offset + k_at(s, lane);
+            ka[s] = *(LdsVector)(buf + at);
+            kb[s] = *(LdsVector)(buf + (at + kPageBytes));
+        }
+    }
+    SD_DEV static u32x4 v_operand(const char *buf, int offset, int k, int lane)
+    {
+        const int at = offset + v_at(k, lane);
+        const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTransposed)(buf + at)));
+        const u32x2 y = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsTransposed)(buf + (at + kPageBytes))));
+        return u32x4{x[0], x[1], y[0], y[1]};
+    }
+    // acc[k][r] = O[row lane & 15][d = 16 k + 4 (lane >> 4) + r]
+    template <class State>
+    SD_DEV static void store(const State &st, float *dst, int lane, bool row_ok, float l)
+    {
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int k = 0; k < D / 16; ++k)   // rows before the sequence's first token get zeros
+            *reinterpret_cast<f32x4 *>(dst + 16 * k + 4 * (lane >> 4)) = row_ok ? st.acc[k] * inv : f32x4{0, 0, 0, 0};
+    }
+};
+
+// head_dim 64: workgroups of 4 waves with four column blocks each, two to a compute unit; a round is two tiles in one of four
+// arrays, asked for three rounds ahead.  (8 prompts of 1.5 k to 4 k, 32/8 heads 429 -> 405 us, 16 x 8192 / 2048 1909 -> 1828 us,
+// against parking through registers.)
+template <int NB>
+__global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
+{
+    constexpr int D = 64, kW = 4, kTiles = 2;
+    typedef Bf16Path<D> P;
+    typedef RowSlot<D> Slot;
+    constexpr int kLoads = Slot::kPageBytes / 1024;   // of a K or V page
+    static_assert(2 * kTiles == kW, "a wave brings K and V of one page per round");
+    __shared__ __attribute__((aligned(16))) char buf0[kTiles * Slot::kBytes], buf1[kTiles * Slot::kBytes], buf2[kTiles * Slot::kBytes], buf3[kTiles * Slot::kBytes];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    PrefillRows rows;
+    if (!rows.find(a, kW, wave, NB)) return;
+    int row_end[NB];
+    u32x4 qop[NB][D / 32];
+    typename P::ParkedState st[NB];
+    rows.load<P>(a, lane, qop, row_end, st);
+
+    const ConstTable bt = (ConstTable)(a.block_table + (int64_t)rows.b * a.max_blocks);
+    const int64_t page_bytes = (int64_t)Slot::kPageBytes * a.Hkv;
+    const char *kbase = static_cast<const char *>(a.k_pages) + rows.hb.g * Slot::kPageBytes;
+    const char *vbase = static_cast<const char *>(a.v_pages) + rows.hb.g * Slot::kPageBytes;
+    const int ntiles = (rows.kv_end + kTileTokens - 1) / kTileTokens;
+    const int last_page = (rows.kv_end + kPage - 1) / kPage - 1;
+    const int rounds = (ntiles + kTiles - 1) / kTiles;
+    // past the end the last page once more; nobody attends it
+    auto page_of = [&](int rd) { return bt[min(2 * kTiles * min(rd, rounds - 1) + wave, last_page)]; };
+    const int my_k = (wave >> 1) * Slot::kBytes + (wave & 1) * Slot::kPageBytes, my_v = my_k + 2 * Slot::kPageBytes;
+    auto bring = [&](char *buf, int page) {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) load_to_lds(kbase + page * page_bytes, Slot::kPageBytes, Slot::source(0, j * 1024 + lane * 16), buf + (my_k + j * 1024));
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) load_to_lds(vbase + page * page_bytes, Slot::kPageBytes, Slot::source(1, j * 1024 + lane * 16), buf + (my_v + j * 1024));
+    };
+    // V rows of tokens that do not exist may hold anything: zeros
+    auto clean = [&](char *buf, int rd) {
+        const int tok0 = (2 * kTiles * rd + wave) * kPage;
+        if (tok0 + kPage <= rows.L) return;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j)
+            if (tok0 + (j * 1024 + lane * 16) / Slot::kRowBytes >= rows.L) *reinterpret_cast<u32x4 *>(buf + (my_v + j * 1024 + lane * 16)) = u32x4{0, 0, 0, 0};
+    };
+    auto step = [&](const char *buf, int j, int tile, auto masked) {
+        u32x4 ka[D / 32], kb[D / 32];
+        Slot::fetch_k(buf, j * Slot::kBytes, lane, ka, kb);
+        P::template attend_fetched<NB, decltype(masked)::value, false>(
+            ka, kb, [&](int k) { return Slot::v_operand(buf, j * Slot::kBytes, k, lane); }, qop, st, a.scale_log2e, tile * kTileTokens,
+            lane, row_end, true, nullptr, rows.first_end, rows.tpb);
+    };
+    constexpr int kPer = 2 * kLoads;   // loads a wave issues per round
+    auto turn = [&](int rd, char *cur, char *next, char *fill, int page) {
+        bring(fill, page);   // round rd + 3
+        if (rows.active) {
+            const int t0 = kTiles * rd * kTileTokens;
+            const int j_end = min(kTiles, (rows.max_end - t0 + kTileTokens - 1) / kTileTokens);
+            const int j_plain = max(0, min(j_end, (rows.min_end - t0) / kTileTokens));
+            int j = 0;
+#pragma unroll 1
+            for (; j < j_plain; ++j) step(cur, j, kTiles * rd + j, std::false_type{});
+#pragma unroll 1
+            for (; j < j_end; ++j) step(cur, j, kTiles * rd + j, std::true_type{});
+        }
+        wait_loads<2 * kPer>();   // round rd + 1 has arrived
+        clean(next, rd + 1);
+        wait_lds();
+        phase_barrier();
+    };
+    if (rounds > 0) {
+        bring(buf0, page_of(0));
+        bring(buf1, page_of(1));
+        bring(buf2, page_of(2));
+        int page = page_of(3);
+        wait_loads<2 * kPer>();
+        clean(buf0, 0);
+        wait_lds();
+        phase_barrier();
+        for (int rd = 0;;) {
+            { const int after = page_of(rd + 4); turn(rd, buf0, buf1, buf3, page); page = after; }
+            if (++rd == rounds) break;
+            { const int after = page_of(rd + 4); turn(rd, buf1, buf2, buf0, page); page = after; }
+            if (++rd == rounds) break;
+            { const int after = page_of(rd + 4); turn(rd, buf2, buf3, buf1, page); page = after; }
+            if (++rd == rounds) break;
+            { const int after = page_of(rd + 4); turn(rd, buf3, buf0, buf2, page); page = after; }
+            if (++rd == rounds) break;
+        }
+        wait_loads<0>();   // no load may outlive the workgroup
+    }
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+        bool in_range, row_ok;
+        int64_t row;
+        rows.locate(a, c, lane & 15, in_range, row_ok, row);
+        const float l = P::weight_sum(st[c]);
+        if (in_range) Slot::store(st[c], a.out + row * D, lane, row_ok, l);
+    }
+}
+
+// head_dim 128: one workgroup of 8 waves per compute unit, two waves per SIMD that take turns at the matrix pipe.  A tile is two
+// phases: the matrix phase (scores of tile t + 1, weighted sum of tile t: 34 matrix instructions) and the vector phase (softmax
+// of tile t).  Waves 4 to 7 run one phase behind waves 0 to 3, and a barrier ends every phase, so that while
+// one wave of a SIMD issues matrix instructions the other does its exponentials.  Tiles are asked for four ahead, into one of
+// six slots: a slot is read last (V, by the late waves) two tiles after it was due, and filled again from then on.
+//
+// What bounds it (16 x 8192 / 2048 queries, 32/8 heads: 3.45 -> 3.22 ms on one machine, 1.2 PFLOP/s): the matrix pipe is busy 57 % of the
+// time; without the loads into LDS the kernel takes 0.88 of its time, without any operand reads 0.9, without the exponentials 0.99, with
+// matrix instructions and barriers alone 0.70.  Operand reads and loads moved between the two phases, and more of
+// them beside the matrix instructions, gave 3.25 - 3.35 ms.
+__global__ __launch_bounds__(512, 2) void prefill_pingpong_kernel(PrefillArgs a)
+{
+    constexpr int D = 128, NB = 2, kW = 8, S = D / 32, K = D / 16;
+    typedef Bf16Path<D> P;
+    typedef RowSlot<D> Slot;
+    constexpr int kLoads = Slot::kBytes / 1024 / kW;   // of a wave per tile
+    __shared__ __attribute__((aligned(16))) char buf0[Slot::kBytes], buf1[Slot::kBytes], buf2[Slot::kBytes], buf3[Slot::kBytes], buf4[Slot::kBytes], buf5[Slot::kBytes];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    PrefillRows rows;
+    if (!rows.find(a, kW, wave, NB)) return;
+    int row_end[NB];
+    u32x4 qop[NB][S];
+    typename P::ParkedState st[NB];
+    rows.load<P>(a, lane, qop, row_end, st);
+
+    const ConstTable bt = (ConstTable)(a.block_table + (int64_t)rows.b * a.max_blocks);
+    const int64_t page_bytes = (int64_t)Slot::kPageBytes * a.Hkv;
+    const int ntiles = (rows.kv_end + kTileTokens - 1) / kTileTokens;
+    const int last_page = (rows.kv_end + kPage - 1) / kPage - 1;
+    const int mine = rows.active ? (rows.max_end + kTileTokens - 1) / kTileTokens : 0;   // tiles this wave attends
+    const float c = a.scale_log2e;
+
+    // this wave brings bytes [kLoads * 1024 * wave, ..) of every slot, which lie in one page's K or V
+    const int my_at = kLoads * 1024 * wave, my_kind = my_at / (2 * Slot::kPageBytes), my_page = my_at / Slot::kPageBytes & 1;
+    const int my_off = my_at % Slot::kPageBytes;
+    const char *pool = static_cast<const char *>(my_kind ? a.v_pages : a.k_pages) + rows.hb.g * Slot::kPageBytes;
+    int from[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) from[j] = Slot::source(my_kind, my_off + j * 1024 + lane * 16);
+    // past the end the last page once more; nobody attends it
+    auto page_of = [&](int t) { return bt[min(2 * min(t, ntiles - 1) + my_page, last_page)]; };
+    auto bring = [&](char *buf, int page) {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) load_to_lds(pool + page * page_bytes, Slot::kPageBytes, from[j], buf + (my_at + j * 1024));
+    };
+    // V rows of tokens that do not exist may hold anything: zeros
+    auto clean = [&](char *buf, int t) {
+        const int tok0 = t * kTileTokens + my_page * kPage;
+        if (my_kind == 0 || tok0 + kPage <= rows.L) return;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j)
+            if (tok0 + (my_off + j * 1024 + lane * 16) / Slot::kRowBytes >= rows.L) *reinterpret_cast<u32x4 *>(buf + (my_at + j * 1024 + lane * 16)) = u32x4{0, 0, 0, 0};
+    };
+
+    u32x4 ka[S], kb[S], va[K], pop[NB];
+    f32x4 sa[NB], sb[NB];
+    const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // bf16 1.0 pairs: the weight sum
+    auto fetch_k = [&](const char *buf) { Slot::fetch_k(buf, 0, lane, ka, kb); };
+    auto fetch_v = [&](const char *buf) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) va[k] = Slot::v_operand(buf, 0, k, lane);
+    };
+    auto first_products = [&]() {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) sa[i] = sb[i] = f32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                sa[i] = mfma_bf16_k32(ka[s], qop[i][s], sa[i]);
+                sb[i] = mfma_bf16_k32(kb[s], qop[i][s], sb[i]);
+            }
+    };
+    auto second_products = [&]() {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) st[i].acc[K] = mfma_bf16_k32(ones, pop[i], st[i].acc[K]);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) st[i].acc[k] = mfma_bf16_k32(va[k], pop[i], st[i].acc[k]);
+    };
+    // as in Bf16Path::attend_parked: weights against the reference as it stands, which moves only when one of them reaches 2
+    auto softmax = [&](int t) {
+        float x[NB][8];
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[i][e] = sa[i][e];
+                x[i][4 + e] = sb[i][e];
+            }
+        if ((t + 1) * kTileTokens > rows.min_end) {   // wave-uniform
+#pragma unroll
+            for (int i = 0; i < NB; ++i) mask_scores(x[i], t * kTileTokens, row_end[i], lane >> 4);
+        }
+        auto weights = [&](int i) {
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[i][e], c, -st[i].m));
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) pop[i][e >> 1] = cvt_pk_bf16(p[e], p[e + 1]);
+        };
+        unsigned big = 0;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            weights(i);
+            big |= pop[i][0] | pop[i][1] | pop[i][2] | pop[i][3];
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64((big & 0x40004000u) != 0) != 0, 0)) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const unsigned own = (pop[i][0] | pop[i][1] | pop[i][2] | pop[i][3]) & 0x40004000u;
+                if (__builtin_amdgcn_ballot_w64(own != 0) != 0) {
+                    advance_max(st[i], max_of(st[i].m, head_max(max8(x[i])) * c + kLead));
+                    weights(i);
+                }
+            }
+        }
+    };
+    auto turn = [&](int t, const char *cur, const char *next, char *arrive, char *fill, int page) {
+        // vector phase: tile t + 4 is asked for, the K operands of tile t + 1 arrive beside the softmax
+        bring(fill, page);
+        fetch_k(next);
+        softmax(t);
+        wait_loads<2 * kLoads>();   // tile t + 2 has arrived
+        clean(arrive, t + 2);
+        wait_lds();
+        phase_barrier();
+        // matrix phase: the V^T operands arrive beside the scores
+        fetch_v(cur);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+        first_products();
+        if (t < mine) second_products();   // wave-uniform: not past the wave's last row, where V may be anything
+        __builtin_amdgcn_s_setprio(0);
+        phase_barrier();
+    };
+    if (ntiles > 0) {
+        bring(buf0, page_of(0));
+        bring(buf1, page_of(1));
+        bring(buf2, page_of(2));
+        bring(buf3, page_of(3));
+        wait_loads<2 * kLoads>();
+        clean(buf0, 0);
+        clean(buf1, 1);
+        wait_lds();
+        int page = page_of(4);
+        phase_barrier();
+        fetch_k(buf0);
+        if (wave >= kW / 2) phase_barrier();   // one phase behind from here on
+        first_products();
+        phase_barrier();
+        for (int t = 0;;) {
+            { const int after = page_of(t + 5); turn(t, buf0, buf1, buf2, buf4, page); page = after; }
+            if (++t == ntiles) break;
+            { const int after = page_of(t + 5); turn(t, buf1, buf2, buf3, buf5, page); page = after; }
+            if (++t == ntiles) break;
+            { const int after = page_of(t + 5); turn(t, buf2, buf3, buf4, buf0, page); page = after; }
+            if (++t == ntiles) break;
+            { const int after = page_of(t + 5); turn(t, buf3, buf4, buf5, buf1, page); page = after; }
+            if (++t == ntiles) break;
+            { const int after = page_of(t + 5); turn(t, buf4, buf5, buf0, buf2, page); page = after; }
+            if (++t == ntiles) break;
+            { const int after = page_of(t + 5); turn(t, buf5, buf0, buf1, buf3, page); page = after; }
+            if (++t == ntiles) break;
+        }
+        if (wave < kW / 2) phase_barrier();   // every wave has met the same number
+        wait_loads<0>();                      // no load may outlive the workgroup
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        bool in_range, row_ok;
+        int64_t row;
+        rows.locate(a, i, lane & 15, in_range, row_ok, row);
+        const float l = P::weight_sum(st[i]);
+        if (in_range) Slot::store(st[i], a.out + row * D, lane, row_ok, l);
     }
 }
 
@@ -297,7 +699,11 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
         switch (a.blocks) {
-        case 16: return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
+        case 16:
+            if constexpr (std::is_same<P, Bf16Path<128>>::value)
+                return go(prefill_pingpong_kernel, 8);
+            else
+                return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
         case 8: return go(prefill_wide_kernel<P, 8, 4, 2, 2, 2>, 8);
         case 4: return go(prefill_wide_kernel<P, 8, 4, 4, 2, 2>, 8);
         default: return go(prefill_wide_kernel<P, 8, 8, 8, 2, 2>, 8);
@@ -306,7 +712,11 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto narrow = [&](auto path) {   // head_dim 64: half the operands per tile, so a wave has room for four blocks, or a compute unit for three workgroups
         typedef decltype(path) P;
         switch (a.blocks) {
-        case 16: return go(prefill_wide_kernel<P, 4, 4, 1, 4, 2>, 4);
+        case 16:
+            if constexpr (std::is_same<P, Bf16Path<64>>::value)
+                return go(prefill_direct_kernel<4>, 4);
+            else
+                return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);   // (four blocks per wave do not fit beside the codes)
         case 8: return go(prefill_wide_kernel<P, 4, 2, 1, 2, 3>, 4);
         case 4: return go(prefill_wide_kernel<P, 4, 4, 4, 4, 2>, 4);
         default: return go(prefill_wide_kernel<P, 8, 8, 8, 2, 2>, 8);

@@ -18,6 +18,8 @@
 //                  ready-made V^T operands (v_park); NB column blocks of 16 rows
 //                  share every operand read
 #pragma once
+#include <climits>
+
 #include "kernels.h"
 
 namespace sd {
@@ -492,7 +494,18 @@ struct Bf16Path {
     template <int NB, bool MASK, bool SCALED = false>
     SD_DEV static void attend_parked(const u32x4 (&ka)[D / 32], const u32x4 (&kb)[D / 32], const char *vslot,
                                      const u32x4 (&qop)[NB][D / 32], ParkedState (&st)[NB], float c, int tok0,
-                                     int lane, const int (&row_end)[NB], bool tile_has_end = true, const char *scales = nullptr)
+                                     int lane, const int (&row_end)[NB], bool tile_has_end = true, const char *scales = nullptr,
+                                     int first_end = INT_MAX, int per_block = 0)
+    {
+        attend_fetched<NB, MASK, SCALED>(ka, kb, [&](int k) { return *reinterpret_cast<const u32x4 *>(vslot + k * 1024 + lane * 16); },
+                                         qop, st, c, tok0, lane, row_end, tile_has_end, scales, first_end, per_block);
+    }
+    // The same with the V^T operands coming from `v_of(k)`.  Masked tiles: the rows of block b end at first_end + b * per_block at the
+    // latest; a block that ends before the tile takes no part in the second product (its weights are 0, but V may be anything).
+    template <int NB, bool MASK, bool SCALED, class V>
+    SD_DEV static void attend_fetched(const u32x4 (&ka)[D / 32], const u32x4 (&kb)[D / 32], V v_of,
+                                      const u32x4 (&qop)[NB][D / 32], ParkedState (&st)[NB], float c, int tok0,
+                                      int lane, const int (&row_end)[NB], bool tile_has_end, const char *scales, int first_end, int per_block)
     {
         constexpr int S = D / 32, K = D / 16;
         constexpr bool kBeside = NB > 1 && !MASK;
@@ -532,7 +545,7 @@ struct Bf16Path {
         constexpr int kBesideAll = K + 1;  // covers either kind of group
         auto fetch_v = [&]() {
 #pragma unroll
-            for (int k = 0; k < K; ++k) va[k] = *reinterpret_cast<const u32x4 *>(vslot + k * 1024 + lane * 16);
+            for (int k = 0; k < K; ++k) va[k] = v_of(k);
         };
 #pragma unroll
         for (int b = 0; b < (kBeside ? 1 : NB); ++b)
@@ -612,13 +625,18 @@ struct Bf16Path {
             for (int b = 1; b < NB; ++b)
 #pragma unroll
                 for (int k = 0; k <= K; ++k) second_product(b, k == 0 ? K : k - 1);
+        } else if (MASK && NB > 1) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if (tok0 < first_end + b * per_block) {   // wave-uniform
+#pragma unroll
+                    for (int k = 0; k <= K; ++k) second_product(b, k == 0 ? K : k - 1);
+                }
         } else {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) second_product(b, K);
+            for (int k = 0; k <= K; ++k)
 #pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) second_product(b, k);
+                for (int b = 0; b < NB; ++b) second_product(b, k == 0 ? K : k - 1);
         }
     }
     SD_DEV static float weight_sum(const ParkedState &st) { return st.acc[D / 16][0]; }

@@ -190,3 +190,23 @@ def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
         wl.v_scales[pages[0]] = 0.0
         wl.v_scales[pages[1]] *= -1.0
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("blocks", [16, 2])
+def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, blocks, d):
+    """K and V rows of the last 20 tokens are NaN and infinite: rows that end 64 tokens (a tile and a wave's rows) before them
+    do not change.  Many sequences of one length, so that waves past their own rows still ride along with their workgroup."""
+    B, Hq, Hkv = (40, 16, 8) if blocks == 16 else (1, 8, 4)
+    if d == 64 and blocks == 16:
+        B, Hq, Hkv = 64, 32, 32
+    L = 300 if blocks == 16 else 1100
+    lens, nq = [L] * B, [150] * B
+    wl, q, q_start = make(lens, nq, Hq, Hkv, d, seed=77)
+    want = gpu(wl, q, q_start)
+    for b in range(B):
+        for t in range(L - 20, L):
+            wl.v_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 2 else 0x7f80
+            wl.k_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 3 else 0xff80
+    got = gpu(wl, q, q_start).reshape(B, 150, Hq, d)
+    assert np.array_equal(got[:, :150 - 84], want.reshape(B, 150, Hq, d)[:, :150 - 84])
