@@ -87,7 +87,8 @@ int sd_last_hip_error(void);
 
 /* The split-K chunk (tokens) the library uses for this shape; <= 0 is an SD_E* code.
    With shape->chunk_tokens == 0 it is chosen from the shape alone, taking sequences
-   to average 55 % of max_context_len. */
+   to average 55 % of max_context_len; a call with shared prefixes then cuts its chunks
+   shorter where its groups hold fewer distinct tokens than that. */
 int sd_chunk_tokens(const sd_shape *shape);
 
 /* The chunk that balances the split pass for a batch whose sequences hold

@@ -617,6 +617,18 @@ def test_prefix_entry_point_matches_oracle(sd, Hq, Hkv, d, chunk):
     assert np.abs(got - plain).max() <= ALARM_ABS + ALARM_REL * np.abs(plain).max()
 
 
+@pytest.mark.parametrize("Hq,Hkv,sizes,prefix,most", [
+    (8, 2, [1, 2, 9, 16], [300, 700, 33, 1029], 400),      # short chunks: the groups hold few tokens
+    (28, 4, [16, 5], [2500, 256], 130),                    # two workgroups of branches per group
+    (64, 1, [150, 150], [500, 260], 1200),                 # the shortest chunk's slots do not fit the workspace
+])
+def test_prefix_entry_point_with_the_library_s_chunk(sd, Hq, Hkv, sizes, prefix, most):
+    session_of, prefix_len = np.repeat(np.arange(len(sizes)), sizes), np.repeat(prefix, sizes)
+    lens = prefix_len + np.random.default_rng(Hq).integers(0, most, size=len(session_of), endpoint=True)
+    wl = workloads.make_custom(lens, Hq, Hkv, 128, seed=430 + Hq, session_of=session_of, prefix_len=prefix_len)
+    check(gpu_attend_prefix(wl), oracle_full(wl))
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_prefix_entry_point_fp8(sd, d):
     sizes = [4, 16, 1]
