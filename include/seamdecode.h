@@ -203,7 +203,8 @@ int kv_copy_pages(const sd_shape *shape, const int32_t *src_pages, const int32_t
  * across ranges each wave leaves (max, sum, weighted sum) in `workspace`.  Merge
  * pass: combines the parts of every cut sequence in range order (results are
  * reproducible bit for bit).  shape->chunk_tokens, when non-zero, is the least
- * number of tokens a range holds.  Larger batches take the chunked passes of
+ * number of tokens a range holds.  Batches of short sequences run one kernel, a
+ * workgroup per (sequence, KV head).  Larger batches take the chunked passes of
  * paged_decode_attention_prefix.  Results do not depend on the physical
  * placement of pages.
  *

@@ -138,6 +138,23 @@ int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_
     return std::min(best, from_shape);
 }
 
+// Whether a batch goes one workgroup per (sequence, KV head) although the chunk rule would cut its sequences.  Against the range
+// pass that saves the second launch, the search for the pieces and the borders between sequences inside them, and loses
+// when few workgroups walk long sequences or the longest ends last.  By the K/V bytes of the longest sequence and the
+// workgroups; measured, us per step, single pass : range pass, over bf16 pools with head_dim 128 (512 bytes per token):
+//   up to 1100 tokens   8 workgroups 9.8 : 13.2, 64 14.1 : 15.5, 200 16.6 : 25, 512 35 : 43
+//   1500                8 workgroups 17 : 13, 64 18.1 : 18.2, 128 19 : 22, 320 36 : 37, 600 53 : 55, 900 69 : 78
+//   2200 - 3000         128 workgroups 30 : 28, 200 34 : 39, 256 44 : 50, 400 76 : 70 (one per compute unit and no more)
+bool short_enough(const sd_shape *s)
+{
+    if (s->chunk_tokens) return false;
+    const int64_t bytes = (int64_t)s->max_context_len * s->head_dim * 2 * (s->kv_dtype == SD_BF16 ? 2 : 1);
+    const int64_t workgroups = (int64_t)s->batch * s->num_kv_heads * sd::head_blocks(s->num_q_heads / s->num_kv_heads);
+    if (bytes <= 576 << 10) return true;
+    if (bytes <= 768 << 10) return workgroups >= 64;
+    return bytes <= 1536 << 10 && workgroups >= 160 && workgroups <= 256;
+}
+
 // The device address of `scratch` is asked for once per device, with that device current, and kept.
 constexpr size_t kStaticScratchBytes = SD_STATIC_SCRATCH_BYTES;
 constexpr int kMaxDevices = 64;
@@ -377,7 +394,8 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     if (shape->kv_dtype == SD_FP8_E4M3 && (bad_ptr(k_scales) || bad_ptr(v_scales))) return SD_EINVAL;
     if (num_groups > 0 && (bad_ptr(group_start) || bad_ptr(shared_len) || max_group_size < 1)) return SD_EINVAL;
     if (!(scale == scale)) return SD_EINVAL;
-    const int chunk = prefix_chunk(shape, num_groups, max_group_size, max_shared_len, own_scratch ? 0 : workspace_bytes);
+    int chunk = prefix_chunk(shape, num_groups, max_group_size, max_shared_len, own_scratch ? 0 : workspace_bytes);
+    if ((num_groups == 0 || max_shared_len == 0) && short_enough(shape)) chunk = std::max(chunk, (shape->max_context_len + 127) / 128 * 128);
     const int S = num_chunks(shape, chunk);
     const WsLayout w = ws_layout(shape, S);
     const int shared_chunks = num_groups > 0 ? (max_shared_len + chunk - 1) / chunk : 0;
