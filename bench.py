@@ -215,7 +215,7 @@ def prefill_main(args):
                      "unit": "TFLOP/s", "frac": flops / (kernel_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
                      "traffic": stored_traffic([os.path.join(ROOT, "paper_2508_11553_amd", "csrc", f)
                                                 for f in ("attn_prefill.hip", "attn_tile.h", "kernels.h")], f"prefill_resume_{wl.kv_dtype}"),
-                     "kernel": "causal pass (sd::prefill_wide_kernel)" if wl.kv_dtype == "bf16" else "causal pass (sd::prefill_kernel)",
+                     "kernel": "causal pass (sd::prefill_pingpong_kernel)" if wl.kv_dtype == "bf16" else "causal pass (sd::prefill_wide_kernel)",
                      "flops_per_launch": flops},
     }
     if not args.no_cpu_baseline:

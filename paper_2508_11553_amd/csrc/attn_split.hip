@@ -56,7 +56,8 @@ template <class P>
 SD_DEV void shared_item(const SplitArgs &a, char *lds, int lane, int wave)
 {
     constexpr int D = P::kDim;
-    constexpr int kSlot = Lds<P>::kSlotBytes;
+    constexpr int kSlot = P::kParkedBytes;
+    typedef typename P::B B;   // whose parked form the tiles take
     const unsigned item = blockIdx.x;  // (chunk, group, block of 4 column blocks, head block), head block fastest
     const int Hv = a.Hkv * a.HB;
     const HeadBlock hb = head_block(item % Hv, a.G, a.HB);
@@ -81,9 +82,9 @@ SD_DEV void shared_item(const SplitArgs &a, char *lds, int lane, int wave)
     u32x4 qop[D / 32];
 #pragma unroll
     for (int s = 0; s < D / 32; ++s)
-        qop[s] = row_ok ? (*reinterpret_cast<const u32x4 *>(a.q + row * D + P::q_offset(s, lane)) & a.q_keep) ^ a.q_flip
+        qop[s] = row_ok ? (*reinterpret_cast<const u32x4 *>(a.q + row * D + B::q_offset(s, lane)) & a.q_keep) ^ a.q_flip
                         : u32x4{0, 0, 0, 0};
-    typename P::ParkedState st;
+    typename B::ParkedState st;
     reset(st);
 
     const int32_t *bt = a.block_table + (int64_t)gs * a.max_blocks + t0 / kPage;
@@ -105,8 +106,7 @@ SD_DEV void shared_item(const SplitArgs &a, char *lds, int lane, int wave)
     for (int rd = 0; rd < rounds; ++rd) {
         const int tn = kWaves * min(rd + 1, rounds - 1) + wave;
         const int na = bt[min(2 * tn, last_page)], nb = bt[min(2 * tn + 1, last_page)];
-        P::k_store(r, mine, lane);
-        P::v_park(r, mine + P::kScratchBytes, lane, t0 + (kWaves * rd + wave) * kTileTokens, t1);
+        P::park(r, mine, lane, t0 + (kWaves * rd + wave) * kTileTokens, t1);
         if (rd + 1 < rounds) issue(r, na, nb);
         __syncthreads();
         if (active) {
@@ -117,17 +117,18 @@ SD_DEV void shared_item(const SplitArgs &a, char *lds, int lane, int wave)
                 if (tok0 >= t1) break;  // wave-uniform
                 const char *slot = lds + j * kSlot;
                 u32x4 ka[D / 32], kb[D / 32];
-                P::k_fetch(slot, lane, ka, kb);
+                B::k_fetch(slot, lane, ka, kb);
                 auto &q1 = reinterpret_cast<const u32x4 (&)[1][D / 32]>(qop);
-                auto &st1 = reinterpret_cast<typename P::ParkedState (&)[1]>(st);
-                P::template attend_parked<1, true>(ka, kb, slot + P::kScratchBytes, q1, st1, a.abs_scale_log2e, tok0, lane, ends,
-                                                   tok0 + kTileTokens > t1);  // the shared stretch ends inside the tile
+                auto &st1 = reinterpret_cast<typename B::ParkedState (&)[1]>(st);
+                B::template attend_parked<1, true, P::kScaled>(ka, kb, slot + P::kImageBytes, q1, st1, a.abs_scale_log2e, tok0, lane, ends,
+                                                               tok0 + kTileTokens > t1,  // the shared stretch ends inside the tile
+                                                               slot + B::kParkedBytes);
             }
         }
         __syncthreads();
     }
     if (!active) return;
-    const float l = P::weight_sum(st);
+    const float l = P::kScaled ? B::scaled_weight_sum(st) : B::weight_sum(st);
     if (row_ok) {
         const int64_t slot = row * a.S + c;
         P::store_acc(st, a.ws_acc + slot * D, lane >> 4);

@@ -15,7 +15,7 @@
 //                  operands formed in registers from the V rows it loaded
 //   attend_parked  the tile sits in an LDS slot that several waves consume: the
 //                  loading wave has parked the K image (k_store) and the
-//                  ready-made V^T operands (v_park); NB column blocks of 16 rows
+//                  ready-made V^T operands (park); NB column blocks of 16 rows
 //                  share every operand read
 #pragma once
 #include <climits>
@@ -166,14 +166,11 @@ SD_DEV float max8(const float (&x)[8])
 // In the causal pass the reference m of a row's exponents may lag the row's largest score so far:
 // weights above 1 lose nothing in fp32 or as bf16 (same relative rounding), and weight sum and
 // weighted sum are relative to m whatever it is.  The row-wide maximum, a chain of a dozen
-// dependent instructions with two lane exchanges, is taken there only when some lane's score has
-// outgrown the reference: by kSlack over fp8 pools (checked before the weights are formed); over
-// bf16 pools when a weight reaches 2 (seen from the weights themselves, see
-// Bf16Path::attend_parked), the reference then moving to kLead above the row's maximum.  The
-// decode kernels, which wait for memory, keep the exact maximum: a lagging reference made no
+// dependent instructions with two lane exchanges, is taken there only when a weight reaches 2
+// (seen from the weights themselves, see Bf16Path::attend_fetched), the reference then moving to kLead above
+// the row's maximum.  The decode kernels, which wait for memory, keep the exact maximum: a lagging reference made no
 // difference to them.
-constexpr float kSlack = 8.0f;  // log2 domain
-constexpr float kLead = 7.0f;   // log2 domain: where a moved reference is put relative to the row's maximum (bf16 pools)
+constexpr float kLead = 7.0f;   // log2 domain: where a moved reference is put relative to the row's maximum
 
 // The running max goes m_old -> m_new: everything accumulated so far shrinks by
 // alpha = exp2(m_old - m_new).  When no row of the wave moved (the usual case once
@@ -199,27 +196,6 @@ SD_DEV void online_softmax(const float (&x)[8], float (&p)[8], State &st)
     advance_max(st, max_of(st.m, head_max(max8(x))));
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(x[e] - st.m);
-}
-
-// The same with a reference that may lag the row's maximum by up to kSlack.
-template <class State>
-SD_DEV void online_softmax_lagging(const float (&x)[8], float (&p)[8], State &st)
-{
-    const float hi = max8(x);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(hi > st.m + kSlack) != 0, 0)) advance_max(st, max_of(st.m, head_max(hi)));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(x[e] - st.m);
-}
-
-// The same for raw scores and a positive scale c (log2 domain) folded into the
-// exponent: p = exp2(s * c - m), one fused multiply-add per score; the max runs
-// over the raw scores.
-template <class State>
-SD_DEV void online_softmax_folded(const float (&s)[8], float c, float (&p)[8], State &st)
-{
-    advance_max(st, max_of(st.m, head_max(max8(s)) * c));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -st.m));
 }
 
 // ---------------------------------------------------------------------------
@@ -262,7 +238,7 @@ struct Bf16Path {
                 r.v[pg][h][j] = kv_load<STREAM>(reinterpret_cast<const u32x2 *>(vl + j * (D * 2) + h * 128));
     }
 
-    // One page of a tile on its own: the causal pass with 8 waves brings its tiles page by page.
+    // One page of a tile on its own: the causal pass brings its tiles page by page.
     struct Page {
         u32x4 k[D / 32];     // as Tile, one page
         u32x2 v[D / 64][4];
@@ -280,7 +256,7 @@ struct Bf16Path {
             for (int j = 0; j < 4; ++j) r.v[h][j] = kv_load<STREAM>(reinterpret_cast<const u32x2 *>(vl + j * (D * 2) + h * 128));
     }
     // Page `half` (tokens tok0 .. tok0 + 15, those < t_end exist) of the tile parked in `slot`: its half
-    // of the K image (as k_store) and of every V^T operand (as v_park: words 2 * half and 2 * half + 1).
+    // of the K image (as k_store) and of every V^T operand (as park: words 2 * half and 2 * half + 1).
     SD_DEV static void park_one(Page &r, char *slot, int half, int lane, int tok0, int t_end)
     {
         char *kdst = slot + half * kTileBytes;
@@ -460,10 +436,12 @@ struct Bf16Path {
             for (int i = 0; i < 4; ++i) st.acc[4 * h + i] = mfma_bf16_k32(v_operand(r, h, i), pop, st.acc[4 * h + i]);
     }
 
-    // The loading wave's half of a shared tile: the V^T operands, one 16-byte
+    // The loading wave's half of a shared tile: the K image and the V^T operands, one 16-byte
     // piece per lane and operand, ready for attend_parked.
-    SD_DEV static void v_park(Tile &r, char *vslot, int lane, int tok0, int t_end)
+    SD_DEV static void park(Tile &r, char *slot, int lane, int tok0, int t_end)
     {
+        k_store(r, slot, lane);
+        char *vslot = slot + kImageBytes;
         v_sanitise(r, tok0, t_end, lane >> 4);
 #pragma unroll
         for (int h = 0; h < D / 64; ++h)
@@ -702,9 +680,7 @@ struct Fp8Path {
     static constexpr int kDim = D;
     static constexpr int kTileBytes = kPage * D;
     static constexpr int kScratchBytes = 2 * kTileBytes;
-    static constexpr int kOpsBytes = 8 * 1024 + 16;  // eight bf16 V^T operands and the four page scales
     typedef WaveState<D> State;
-    typedef WaveState<D> ParkedState;
 
     struct Tile {
         u32x4 k[2][2];  // [page][j]: 16 bytes at byte offset 1024*j + 16*lane of the K tile
@@ -919,57 +895,19 @@ struct Fp8Path {
         v_operands(r, [&](int k, u32x4 a) { st.acc[k] = mfma_bf16_k32(a, pop, st.acc[k]); });
     }
 
-    SD_DEV static void v_park(Tile &r, char *vslot, int lane, int tok0, int t_end)
+    // a whole tile parked as bf16, as its two pages
+    SD_DEV static void park(const Tile &r, char *slot, int lane, int tok0, int t_end)
     {
-        v_sanitise(r, tok0, t_end, lane >> 4);
-        v_operands(r, [&](int k, u32x4 a) { *reinterpret_cast<u32x4 *>(vslot + k * 1024 + lane * 16) = a; });
-        if (lane == 0) *reinterpret_cast<f32x4 *>(vslot + 8 * 1024) = f32x4{r.ks[0], r.ks[1], r.vs[0], r.vs[1]};
-    }
-
-    // as Bf16Path::attend_parked; the scores are scaled per page before the mask
-    // (a page of zeros has scale 0), so nothing is folded here
-    template <int NB, bool MASK>
-    SD_DEV static void attend_parked(const u32x4 (&ka)[4], const u32x4 (&kb)[4], const char *vslot,
-                                     const u32x4 (&qop)[NB][4], ParkedState (&st)[NB], float c, int tok0, int lane,
-                                     const int (&row_end)[NB], bool tile_has_end = true)
-    {
-        const int qd = lane >> 4;
-        const f32x4 sc = *reinterpret_cast<const f32x4 *>(vslot + 8 * 1024);  // k scales, v scales of the two pages
-        f32x4 sa[NB], sb[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) sa[b] = sb[b] = f32x4{0, 0, 0, 0};
+        for (int h = 0; h < 2; ++h) {
+            Page p;
+            p.k[0] = r.k[h][0], p.k[1] = r.k[h][1];
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                sa[b] = mfma_bf16_k32(ka[s], qop[b][s], sa[b]);
-                sb[b] = mfma_bf16_k32(kb[s], qop[b][s], sb[b]);
-            }
-        const float ca = c * sc[0], cb = c * sc[1];
-        u32x4 pop[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float x[8], p[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x[e] = sa[b][e] * ca;
-                x[4 + e] = sb[b][e] * cb;
-            }
-            if (MASK && tile_has_end) mask_scores(x, tok0, row_end[b], qd);
-            if (MASK)
-                online_softmax(x, p, st[b]);
-            else
-                online_softmax_lagging(x, p, st[b]);
-            pop[b] = weight_operand(p, sc[2], sc[3], st[b].l);
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(vslot + k * 1024 + lane * 16);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) st[b].acc[k] = mfma_bf16_k32(a, pop[b], st[b].acc[k]);
+            for (int j = 0; j < 4; ++j) p.v[j] = r.v[h][j];
+            p.ks = r.ks[h], p.vs = r.vs[h];
+            park_one(p, slot, h, lane, tok0 + h * kPage, t_end);
         }
     }
-    SD_DEV static float weight_sum(const ParkedState &st) { return head_sum(st.l); }
 
     template <class S>
     SD_DEV static void store_acc(const S &st, float *dst, int qd)
@@ -1010,9 +948,7 @@ struct Fp8Path64 {
     static constexpr int kDim = D;
     static constexpr int kTileBytes = kPage * D;             // one (page, head) tile of codes
     static constexpr int kScratchBytes = B::kScratchBytes;   // K of one 32-token tile in LDS, as bf16
-    static constexpr int kOpsBytes = B::kOpsBytes + 16;      // four bf16 V^T operands and the four page scales
     typedef WaveState<D> State;
-    typedef WaveState<D> ParkedState;
 
     struct Tile {
         u32x4 k[2];        // [page]: 16 codes at byte offset 16*lane of the K tile: row lane>>2, d = 16*(lane&3) .. +16
@@ -1148,57 +1084,19 @@ struct Fp8Path64 {
         for (int i = 0; i < 4; ++i) st.acc[i] = mfma_bf16_k32(B::v_operand(t, 0, i), pop, st.acc[i]);
     }
 
-    SD_DEV static void v_park(Tile &r, char *vslot, int lane, int tok0, int t_end)
+    // a whole tile parked as bf16, as its two pages
+    SD_DEV static void park(const Tile &r, char *slot, int lane, int tok0, int t_end)
     {
-        typename B::Tile t;
-        v_to_bf16(r, t);
-        B::v_park(t, vslot, lane, tok0, t_end);
-        if (lane == 0) *reinterpret_cast<f32x4 *>(vslot + B::kOpsBytes) = f32x4{r.ks[0], r.ks[1], r.vs[0], r.vs[1]};
-    }
-
-    // as Fp8Path::attend_parked, with the four operands of head_dim 64
-    template <int NB, bool MASK>
-    SD_DEV static void attend_parked(const u32x4 (&ka)[2], const u32x4 (&kb)[2], const char *vslot,
-                                     const u32x4 (&qop)[NB][2], ParkedState (&st)[NB], float c, int tok0, int lane,
-                                     const int (&row_end)[NB], bool tile_has_end = true)
-    {
-        const int qd = lane >> 4;
-        const f32x4 sc = *reinterpret_cast<const f32x4 *>(vslot + B::kOpsBytes);  // k scales, v scales of the two pages
-        f32x4 sa[NB], sb[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) sa[b] = sb[b] = f32x4{0, 0, 0, 0};
+        for (int h = 0; h < 2; ++h) {
+            Page p;
+            p.k = r.k[h];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                sa[b] = mfma_bf16_k32(ka[s], qop[b][s], sa[b]);
-                sb[b] = mfma_bf16_k32(kb[s], qop[b][s], sb[b]);
-            }
-        const float ca = c * sc[0], cb = c * sc[1];
-        u32x4 pop[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            float x[8], p[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x[e] = sa[b][e] * ca;
-                x[4 + e] = sb[b][e] * cb;
-            }
-            if (MASK && tile_has_end) mask_scores(x, tok0, row_end[b], qd);
-            if (MASK)
-                online_softmax(x, p, st[b]);
-            else
-                online_softmax_lagging(x, p, st[b]);
-            pop[b] = Fp8Path::weight_operand(p, sc[2], sc[3], st[b].l);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(vslot + k * 1024 + lane * 16);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) st[b].acc[k] = mfma_bf16_k32(a, pop[b], st[b].acc[k]);
+            for (int j = 0; j < 4; ++j) p.v[j] = r.v[h][j];
+            p.ks = r.ks[h], p.vs = r.vs[h];
+            park_one(p, slot, h, lane, tok0 + h * kPage, t_end);
         }
     }
-    SD_DEV static float weight_sum(const ParkedState &st) { return head_sum(st.l); }
 
     template <class S>
     SD_DEV static void store_acc(const S &st, float *dst, int qd) { B::store_acc(st, dst, qd); }
@@ -1206,14 +1104,13 @@ struct Fp8Path64 {
 };
 
 // LDS of one workgroup of the split pass.  Plain items: per-wave K scratch plus
-// the merge buffers.  Shared items (and the causal pass): four tile slots (K
-// image + V^T operands), one filled by each wave and read by all.
+// the merge buffers.  Shared items: four tile slots (K image + V^T operands), one
+// filled by each wave and read by all.
 template <class P>
 struct Lds {
     static constexpr int kRow = P::kDim + 4;  // padded: 16 rows x float4 stores hit 64 distinct banks
-    static constexpr int kSlotBytes = P::kScratchBytes + ((P::kOpsBytes + 15) / 16) * 16;
     static constexpr int kPlainBytes = kWaves * P::kScratchBytes + kWaves * kMaxGroup * kRow * 4 + 2 * kWaves * kMaxGroup * 4;
-    static constexpr int kSharedBytes = kWaves * kSlotBytes;
+    static constexpr int kSharedBytes = kWaves * P::kParkedBytes;
     static constexpr int kBytes = kPlainBytes > kSharedBytes ? kPlainBytes : kSharedBytes;
 };
 

@@ -89,6 +89,8 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
 //                 16 whole prompts of 200 - 1000, 32/8 heads                    72 /  61 / 109 / 225
 //                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      203 / 161 / 157 / 222
 //                 3 sequences of 1 k - 6 k, 50 - 400 queries, 32/8 heads       137 /  92 /  49 /  40
+// (Taken with 16 blocks on the general kernel; the kernels that bf16 pools have for 16 blocks take 4 - 7 % less: 259, 540 and 1828 us where 296, 579
+// and 1885 stand, the other machine's share taken out: 272, 560, 1909.)
 __host__ inline int prefill_blocks(int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
 {
     const auto workgroups = [&](int blocks) { return (total_q / (blocks * units) + batch) * heads; };   // about
