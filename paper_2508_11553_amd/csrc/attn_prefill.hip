@@ -699,12 +699,14 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
         switch (a.blocks) {
-        case 16:
+        case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us, 89 - 547, 40/8 heads 15.0 against 18.5)
             if constexpr (std::is_same<P, Bf16Path<128>>::value)
-                return go(prefill_pingpong_kernel, 8);
-            else
-                return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
-        case 8: return go(prefill_wide_kernel<P, 8, 4, 2, 2, 2>, 8);
+                if (a.max_context_len >= kPrefillShort) return go(prefill_pingpong_kernel, 8);
+            return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
+        case 8:
+            if constexpr (P::kScaled)
+                if (a.max_context_len < kPrefillShort) return go(prefill_wide_kernel<P, 4, 2, 1, 2, 2>, 4);
+            return go(prefill_wide_kernel<P, 8, 4, 2, 2, 2>, 8);
         case 4: return go(prefill_wide_kernel<P, 8, 4, 4, 2, 2>, 8);
         default: return go(prefill_wide_kernel<P, 8, 8, 8, 2, 2>, 8);
         }

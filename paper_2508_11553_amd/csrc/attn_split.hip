@@ -144,20 +144,24 @@ SD_DEV void shared_item(const SplitArgs &a, char *lds, int lane, int wave)
 // the chunk may be ragged at the sequence's end; nobody else reads these K/V
 // bytes, so they stream.  The four waves take every fourth 32-token tile,
 // merge through LDS and write one partial per head.
-template <class P>
+//
+// GROUPS: the grid begins with shared-prefix items.  NEWEST: append and attend in one go.  Instances of their own, so that a plain
+// launch holds neither their code nor the tile slots of the shared items (15 KB of LDS over fp8 pools); its time is the same either way.
+template <class P, bool GROUPS, bool NEWEST>
 __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
 {
     constexpr int D = P::kDim;
     constexpr int kRow = Lds<P>::kRow;
-    __shared__ __attribute__((aligned(16))) char lds[Lds<P>::kBytes];
+    __shared__ __attribute__((aligned(16))) char lds[GROUPS ? Lds<P>::kBytes : Lds<P>::kPlainBytes];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (blockIdx.x < a.group_items) {  // shared-prefix items come first in the grid
-        shared_item<P>(a, lds, lane, wave);
-        return;
-    }
+    if constexpr (GROUPS)
+        if (blockIdx.x < a.group_items) {  // shared-prefix items come first in the grid
+            shared_item<P>(a, lds, lane, wave);
+            return;
+        }
     char *s_k = lds + wave * P::kScratchBytes;
     float (*s_acc)[kMaxGroup][kRow] = reinterpret_cast<float (*)[kMaxGroup][kRow]>(lds + kWaves * P::kScratchBytes);
     float (*s_m)[kMaxGroup] = reinterpret_cast<float (*)[kMaxGroup]>(lds + kWaves * P::kScratchBytes + kWaves * kMaxGroup * kRow * 4);
@@ -190,7 +194,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     const int t0 = shared + c_private * a.chunk_tokens;
     const int t1 = min(L, t0 + a.chunk_tokens);
     // single-chunk mode with an append: the newest token comes as a row of k_new / v_new and goes into the pool from here
-    const bool newest = P::kAppendInPlace && a.k_new != nullptr;
+    constexpr bool newest = NEWEST;
     const int t1_pool = newest ? t1 - 1 : t1;   // tokens the pool holds
 
     // Q^T operand: lane&15 = head n of the block; rows past the block's heads are zero
@@ -270,10 +274,16 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
 template <class P>
 static void launch_one(const SplitArgs &a, dim3 g, dim3 b, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
 {
-    if (start || stop)
-        hipExtLaunchKernelGGL(split_kernel<P>, g, b, 0, stream, start, stop, 0, a);
-    else
-        hipLaunchKernelGGL(split_kernel<P>, g, b, 0, stream, a);
+    auto go = [&](auto kernel) {
+        if (start || stop)
+            hipExtLaunchKernelGGL(kernel, g, b, 0, stream, start, stop, 0, a);
+        else
+            hipLaunchKernelGGL(kernel, g, b, 0, stream, a);
+    };
+    if (a.group_items) return go(split_kernel<P, true, false>);   // (never with an append)
+    if constexpr (P::kAppendInPlace)
+        if (a.k_new) return go(split_kernel<P, false, true>);
+    go(split_kernel<P, false, false>);
 }
 
 hipError_t launch_split(const SplitArgs &a, int head_dim, int kv_dtype, hipStream_t stream,

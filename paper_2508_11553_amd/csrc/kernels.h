@@ -91,13 +91,23 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
 //                 3 sequences of 1 k - 6 k, 50 - 400 queries, 32/8 heads       137 /  92 /  49 /  40
 // (Taken with 16 blocks on the general kernel; the kernels that bf16 pools have for 16 blocks take 4 - 7 % less: 259, 540 and 1828 us where 296, 579
 // and 1885 stand, the other machine's share taken out: 272, 560, 1909.)
-__host__ inline int prefill_blocks(int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
+// Short contexts (below kPrefillShort tokens) have few tiles to share: no split, 8 blocks of four waves over fp8 pools and at head_dim 64, 16 blocks
+// over bf16 pools (5 sequences of 89 - 547, 40/8 heads, bf16: 15.0 us against 17.7 with a split; 3 of 182 - 304, 64/8 heads, fp8: 24.5 against 27.4).
+// At head_dim 128 160 workgroups of 16 blocks still beat twice as many halves, which take two turns at 256 compute units (4
+// sequences of 7 k, 16/2 heads: 219 against 251 us).
+constexpr int kPrefillShort = 512;
+__host__ inline int prefill_blocks(int kv_dtype, int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
 {
     const auto workgroups = [&](int blocks) { return (total_q / (blocks * units) + batch) * heads; };   // about
-    if (head_dim == 64) return workgroups(16) >= 2048 ? 16 : workgroups(8) >= 512 ? 8 : workgroups(4) >= 512 || max_context_len < 1024 ? 4 : 2;
-    if (workgroups(16) >= 256 || max_context_len < 256) return 16;
-    if (workgroups(8) >= 256 || max_context_len < 512) return 8;
-    return workgroups(4) >= 256 || max_context_len < 1024 ? 4 : 2;
+    if (head_dim == 64) {
+        if (workgroups(16) >= 2048) return 16;
+        if (workgroups(8) >= 512 || max_context_len < kPrefillShort) return 8;
+        return workgroups(4) >= 512 || max_context_len < 1024 ? 4 : 2;
+    }
+    if (max_context_len < kPrefillShort) return kv_dtype == 0 ? 16 : 8;
+    if (workgroups(16) >= 160) return 16;
+    if (workgroups(8) >= 256) return 8;
+    return workgroups(4) >= 192 || max_context_len < 1024 ? 4 : 2;
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens

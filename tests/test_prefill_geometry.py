@@ -15,7 +15,7 @@ PROGRAM = r"""
 int main(int argc, char **argv)
 {
     if (argc > 3) {
-        printf("%d\n", sd::prefill_blocks(atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])));
+        printf("%d\n", sd::prefill_blocks(0, atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])));
         return 0;
     }
     const int q_blocks = atoi(argv[1]), pairs = atoi(argv[2]);
@@ -58,12 +58,12 @@ def test_every_item_is_dealt_once_and_to_every_die_alike(program, q_blocks, pair
 
 
 def block_case(blocks, d):
-    """(lens, queries, Hq, Hkv): a small batch that the rule gives workgroups of `blocks` column blocks, with sequences on both
+    """(lens, queries, Hq, Hkv): a small batch that the rule gives workgroups of `blocks` column blocks (bf16 pools), with sequences on both
     sides of a page, a tile, a round and a workgroup's rows."""
     edge = [1, 15, 16, 17, 31, 33, 129, 255, 256, 257]
     if d == 128:
-        lens, q, Hq, Hkv = {16: (edge * 4, [1, 3, 17, 33] * 10, 16, 8),
-                            8: (edge + [700, 512], [300] * 12, 16, 8),
+        lens, q, Hq, Hkv = {16: (edge * 4 + [600], [1, 3, 17, 33] * 10 + [40], 16, 8),
+                            8: ([700, 512, 400, 129, 33], [1000] * 5, 16, 8),
                             4: (edge[4:] + [700], [120] * 7, 8, 4),
                             2: (edge[4:] + [1030, 1500], [70] * 8, 8, 4)}[blocks]
     else:
