@@ -53,12 +53,12 @@ SD_DEV unsigned cvt_pk_bf16(float lo, float hi)
 }
 
 // two e4m3fn codes (one 16-bit half of w) -> packed bf16 pair, exact.  The
-// instruction applies only the power-of-two part of its scale operand; 1.0
+// instruction applies only the power-of-two part of its scale operand: 1.0
 // leaves the values as they are.
 template <bool HI>
-SD_DEV unsigned cvt_pk_bf16_fp8(unsigned w)
+SD_DEV unsigned cvt_pk_bf16_fp8(unsigned w, float power = 1.0f)
 {
-    return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, HI));
+    return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, power, HI));
 }
 
 // K/V bytes that one wave uses once per launch are loaded with the
@@ -647,15 +647,28 @@ struct Bf16Path {
     }
 };
 
-// Scales of a tile of an fp8 pool that is parked as bf16: {k_scale, k_scale} and {log2 |v_scale|, log2 |v_scale|} of its two pages,
-// then 1 / |v_scale| as three bf16 parts (hi, mid, lo, and a zero), each twice in a word: [part][page].
-constexpr int kPageScalesBytes = 48;
-// A negative V scale turns the signs of its page's codes (the weights are positive); a V scale of 0 zeroes them and counts as 1.
-SD_DEV unsigned sign_codes(float v_scale) { return v_scale < 0.f ? 0x80808080u : 0u; }
-SD_DEV void park_scales(char *dst, int half, float ks, float vs, int lane)
+// A page's V scale in two factors: `fold`, which the weights carry, and a power of two that the codes take as they are converted (1 for
+// any ordinary scale).  Weights have fp32's exponent range only as long as the pages of a row lie less than that apart, so
+// fold is kept within [2^-40, 2^40); the codes' bf16 form has room for the rest and stays exact.  A scale of 0 counts as 1 (its codes are zeroed).
+struct ValueScale {
+    float fold, power;
+};
+SD_DEV ValueScale value_scale(float vs)
 {
     const float v = vs != 0.f ? __builtin_fabsf(vs) : 1.0f;
-    const float inv = 1.0f / v;
+    const int e = __builtin_amdgcn_frexp_expf(v);   // v = m * 2^e, m in [0.5, 1)
+    const int out = e - max(-39, min(e, 40));
+    return ValueScale{__builtin_ldexpf(v, -out), __builtin_ldexpf(1.0f, out)};
+}
+
+// Scales of a tile of an fp8 pool that is parked as bf16: {k_scale, k_scale} and {log2 fold, log2 fold} of its two pages,
+// then 1 / fold as three bf16 parts (hi, mid, lo, and a zero), each twice in a word: [part][page].
+constexpr int kPageScalesBytes = 48;
+// A negative V scale turns the signs of its page's codes (the weights are positive).
+SD_DEV unsigned sign_codes(float v_scale) { return v_scale < 0.f ? 0x80808080u : 0u; }
+SD_DEV void park_scales(char *dst, int half, float ks, float fold, int lane)
+{
+    const float inv = 1.0f / fold;
     const float hi = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, inv) & 0xffff0000u);
     const float mid = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, inv - hi) & 0xffff0000u);
     const float lo = inv - hi - mid;   // at most 8 significant bits are left
@@ -666,7 +679,7 @@ SD_DEV void park_scales(char *dst, int half, float ks, float vs, int lane)
     }
     if (lane == 0) {
         *reinterpret_cast<float *>(dst + half * 4) = ks;
-        *reinterpret_cast<float *>(dst + 8 + half * 4) = __builtin_log2f(v);
+        *reinterpret_cast<float *>(dst + 8 + half * 4) = __builtin_log2f(fold);
     }
 }
 
@@ -741,12 +754,11 @@ struct Fp8Path {
                     u32x4{cvt_pk_bf16_fp8<false>(lo), cvt_pk_bf16_fp8<true>(lo), cvt_pk_bf16_fp8<false>(hi), cvt_pk_bf16_fp8<true>(hi)};
             }
         }
-        const unsigned flip = sign_codes(r.vs), keep = r.vs != 0.f ? 0xffffffffu : 0u;
+        const unsigned flip = sign_codes(r.vs);
+        const int end = r.vs != 0.f ? t_end : 0;   // tokens that do not exist, or whose V is 0 by its scale
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            r.v[j] = (r.v[j] & u32x2{keep, keep}) ^ u32x2{flip, flip};
-            if (tok0 + 4 * (lane >> 4) + j >= t_end) r.v[j] = u32x2{0, 0};   // tokens that do not exist
-        }
+        for (int j = 0; j < 4; ++j) r.v[j] = tok0 + 4 * (lane >> 4) + j >= end ? u32x2{0, 0} : r.v[j] ^ u32x2{flip, flip};
+        const ValueScale vs = value_scale(r.vs);
         char *vdst = slot + kImageBytes + lane * 16 + half * 8;
 #pragma unroll
         for (int w = 0; w < 2; ++w)
@@ -754,11 +766,11 @@ struct Fp8Path {
             for (int hi = 0; hi < 2; ++hi) {
                 unsigned f[4];   // codes 4w + 2hi and the next one of four tokens
 #pragma unroll
-                for (int j = 0; j < 4; ++j) f[j] = hi ? cvt_pk_bf16_fp8<true>(r.v[j][w]) : cvt_pk_bf16_fp8<false>(r.v[j][w]);
+                for (int j = 0; j < 4; ++j) f[j] = hi ? cvt_pk_bf16_fp8<true>(r.v[j][w], vs.power) : cvt_pk_bf16_fp8<false>(r.v[j][w], vs.power);
                 *reinterpret_cast<u32x2 *>(vdst + (4 * w + 2 * hi) * 1024) = u32x2{pack_lo(f[0], f[1]), pack_lo(f[2], f[3])};
                 *reinterpret_cast<u32x2 *>(vdst + (4 * w + 2 * hi + 1) * 1024) = u32x2{pack_hi(f[0], f[1]), pack_hi(f[2], f[3])};
             }
-        park_scales(slot + B::kParkedBytes, half, r.ks, r.vs, lane);
+        park_scales(slot + B::kParkedBytes, half, r.ks, vs.fold, lane);
     }
 
     // fp8 pools take new tokens through kv_append_fp8 (a page's scale may have to change)
@@ -989,7 +1001,7 @@ struct Fp8Path64 {
     }
 
     // four codes -> four bf16
-    SD_DEV static u32x2 cvt4(unsigned w) { return u32x2{cvt_pk_bf16_fp8<false>(w), cvt_pk_bf16_fp8<true>(w)}; }
+    SD_DEV static u32x2 cvt4(unsigned w, float power = 1.0f) { return u32x2{cvt_pk_bf16_fp8<false>(w, power), cvt_pk_bf16_fp8<true>(w, power)}; }
 
     // One page on its own, as in the 128-wide fp8 path.
     static constexpr int kImageBytes = B::kImageBytes;
@@ -1019,17 +1031,19 @@ struct Fp8Path64 {
             const u32x2 lo = cvt4(r.k[2 * hh]), hi = cvt4(r.k[2 * hh + 1]);
             *reinterpret_cast<u32x4 *>(kdst + ((2 * (lane & 3) + hh) ^ (row % B::kPieces)) * 16) = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
-        const unsigned flip = sign_codes(r.vs), keep = r.vs != 0.f ? 0xffffffffu : 0u;
+        const unsigned flip = sign_codes(r.vs);
+        const int end = r.vs != 0.f ? t_end : 0;   // tokens that do not exist, or whose V is 0 by its scale
+        const ValueScale vs = value_scale(r.vs);
         u32x2 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = cvt4(tok0 + 4 * (lane >> 4) + j >= t_end ? 0u : (r.v[j] & keep) ^ flip);
+        for (int j = 0; j < 4; ++j) v[j] = cvt4(tok0 + 4 * (lane >> 4) + j >= end ? 0u : r.v[j] ^ flip, vs.power);
         char *vdst = slot + kImageBytes + lane * 16 + half * 8;
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
             *reinterpret_cast<u32x2 *>(vdst + 2 * w * 1024) = u32x2{pack_lo(v[0][w], v[1][w]), pack_lo(v[2][w], v[3][w])};
             *reinterpret_cast<u32x2 *>(vdst + (2 * w + 1) * 1024) = u32x2{pack_hi(v[0][w], v[1][w]), pack_hi(v[2][w], v[3][w])};
         }
-        park_scales(slot + B::kParkedBytes, half, r.ks, r.vs, lane);
+        park_scales(slot + B::kParkedBytes, half, r.ks, vs.fold, lane);
     }
 
     // The lane's 16 codes are two 16-byte pieces of the bf16 row; they go where the bf16 path's k_store

@@ -639,6 +639,21 @@ def test_prefix_entry_point_fp8(sd, d):
     check_fp8(gpu_attend_prefix(wl, chunk_tokens=512), oracle_full(wl))
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_prefix_entry_point_fp8_value_scales_far_apart(sd, d):
+    """As for the causal pass: pages of a shared prefix whose V scales are next to nothing keep their share of the weights."""
+    sizes = [4, 16]
+    session_of, prefix_len = np.repeat(np.arange(2), sizes), np.repeat([1024 + 5, 2048], sizes)
+    lens = prefix_len + np.random.default_rng(6).integers(1, 700, size=len(session_of))
+    wl = workloads.make_custom(lens, 16, 2, d, "fp8", seed=411, session_of=session_of, prefix_len=prefix_len)
+    small = np.float32([1, 2.0 ** -124, 1e-39, 1, -(2.0 ** -120), 2.0 ** -149, 0, 1e-30])
+    for b in (0, sizes[0]):
+        pages = wl.block_table[b, :prefix_len[b] // 16]
+        pattern = np.resize(small, len(pages))[:, None]
+        wl.v_scales[pages] = np.where(pattern == 1, wl.v_scales[pages], pattern)
+    check_fp8(gpu_attend_prefix(wl, chunk_tokens=512), oracle_full(wl))
+
+
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("scale", [-0.09, 0.0])
 def test_prefix_entry_point_with_negative_and_zero_scale(sd, scale, kv_dtype):

@@ -193,6 +193,27 @@ def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("blocks", [16, 8, 4, 2])
+def test_fp8_value_scales_far_apart(sd, blocks, d):
+    """V scales of any size side by side in a row: pages whose values are next to nothing keep their share of the weights (2^-124 times
+    a weight is no normal bf16 number any more, 2^-149 not even an fp32 one), and values of 2^100 drown the rest without harm."""
+    from tests.test_prefill_geometry import block_case
+    lens, nq, Hq, Hkv = block_case(blocks, d)
+    wl, q, q_start = make(lens, nq, Hq, Hkv, d, "fp8", seed=350 + blocks + d)
+    small = np.float32([1, 2.0 ** -124, 1e-39, 1, -(2.0 ** -120), 2.0 ** -149, 1e-30])
+    for b, factor in ((len(lens) - 1, 1.0), (len(lens) - 2, 2.0 ** 100)):
+        pages = wl.block_table[b, :(lens[b] + 15) // 16]
+        scales = wl.v_scales[pages] * np.float32(factor)
+        pattern = np.resize(small, len(pages))[:, None]
+        wl.v_scales[pages] = np.where(pattern == 1, scales, pattern)
+    got, want = gpu(wl, q, q_start), ref(wl, q, q_start)
+    big = slice(q_start[len(lens) - 2], q_start[len(lens) - 1])
+    got[big] *= np.float32(2.0 ** -100)
+    want[big] *= 2.0 ** -100
+    check(got, want, "fp8")
+
+
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("blocks", [16, 2])
 def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, blocks, d):
     """K and V rows of the last 20 tokens are NaN and infinite: rows that end 64 tokens (a tile and a wave's rows) before them
