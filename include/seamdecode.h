@@ -85,10 +85,12 @@ const char *sd_strerror(int code);
 /* hipError_t (as int) of the last failing HIP call made by this thread; 0 if none. */
 int sd_last_hip_error(void);
 
-/* The split-K chunk (tokens) the library uses for this shape; <= 0 is an SD_E* code.
+/* The split-K chunk (tokens) the chunked passes use for this shape; <= 0 is an SD_E* code.
    With shape->chunk_tokens == 0 it is chosen from the shape alone, taking sequences
    to average 55 % of max_context_len; a call with shared prefixes then cuts its chunks
-   shorter where its groups hold fewer distinct tokens than that. */
+   shorter where its group arguments (num_groups, max_group_size, max_shared_len) tell
+   of fewer distinct tokens than that.  Nothing else enters: a larger workspace changes
+   neither the chunk nor a bit of the result. */
 int sd_chunk_tokens(const sd_shape *shape);
 
 /* The chunk that balances the split pass for a batch whose sequences hold

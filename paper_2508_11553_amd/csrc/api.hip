@@ -117,9 +117,9 @@ WsLayout ws_layout(const sd_shape *s, int S)
 // sequence (shared lengths are taken to average 60 % of their bound, the rest half of what is left).  Measured optimum
 // over eleven batches: about 1.3 times the share of a workgroup slot, down to 256 tokens (us per step, this rule against the
 // shape's: 8 groups of 7, prefixes of 1 k - 9 k, 64/8 heads 91 : 142; 10 of 6, 0.4 k - 1.8 k, 28/4 heads 26 : 38; 3 of 3, 0.6 k - 2.2 k,
-// 16/2 heads 20 : 34; 16 of 16, 2 k - 16 k, 32/8 heads 459 : 460).  The workspace is the one the shape asks for: a
-// chunk whose slots do not fit into it is doubled until they do (the shape's chunk fits).
-int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_shared_len, size_t workspace_bytes)
+// 16/2 heads 20 : 34; 16 of 16, 2 k - 16 k, 32/8 heads 459 : 460).  The workspace is the one the shape asks for, however large the
+// caller's is: a chunk whose slots do not fit into it is doubled until they do (the shape's chunk fits).
+int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_shared_len)
 {
     const int from_shape = pick_chunk(s);
     if (s->chunk_tokens || num_groups <= 0 || max_shared_len <= 0 || max_group_size <= 0) return from_shape;
@@ -134,7 +134,8 @@ int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_
         if (rc < rb) best = c;
     }
     const int64_t heads = (int64_t)s->num_kv_heads * sd::head_blocks(G);
-    while (best < from_shape && (ws_layout(s, num_chunks(s, best)).total > workspace_bytes || num_chunks(s, best) * s->batch * heads > 1 << 22)) best *= 2;
+    const size_t workspace = sd_workspace_bytes(s);
+    while (best < from_shape && (ws_layout(s, num_chunks(s, best)).total > workspace || num_chunks(s, best) * s->batch * heads > 1 << 22)) best *= 2;
     return std::min(best, from_shape);
 }
 
@@ -394,7 +395,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     if (shape->kv_dtype == SD_FP8_E4M3 && (bad_ptr(k_scales) || bad_ptr(v_scales))) return SD_EINVAL;
     if (num_groups > 0 && (bad_ptr(group_start) || bad_ptr(shared_len) || max_group_size < 1)) return SD_EINVAL;
     if (!(scale == scale)) return SD_EINVAL;
-    int chunk = prefix_chunk(shape, num_groups, max_group_size, max_shared_len, own_scratch ? 0 : workspace_bytes);
+    int chunk = prefix_chunk(shape, num_groups, max_group_size, max_shared_len);
     if ((num_groups == 0 || max_shared_len == 0) && short_enough(shape)) chunk = std::max(chunk, (shape->max_context_len + 127) / 128 * 128);
     const int S = num_chunks(shape, chunk);
     const WsLayout w = ws_layout(shape, S);

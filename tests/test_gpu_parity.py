@@ -620,13 +620,27 @@ def test_prefix_entry_point_matches_oracle(sd, Hq, Hkv, d, chunk):
 @pytest.mark.parametrize("Hq,Hkv,sizes,prefix,most", [
     (8, 2, [1, 2, 9, 16], [300, 700, 33, 1029], 400),      # short chunks: the groups hold few tokens
     (28, 4, [16, 5], [2500, 256], 130),                    # two workgroups of branches per group
-    (64, 1, [150, 150], [500, 260], 1200),                 # the shortest chunk's slots do not fit the workspace
+    (64, 1, [150, 150], [500, 260], 1200),                 # the shape's own chunk: one per sequence
+    (4, 1, [750, 750], [448, 300], 160),                   # the slots of a shorter chunk would not fit the workspace
 ])
 def test_prefix_entry_point_with_the_library_s_chunk(sd, Hq, Hkv, sizes, prefix, most):
     session_of, prefix_len = np.repeat(np.arange(len(sizes)), sizes), np.repeat(prefix, sizes)
     lens = prefix_len + np.random.default_rng(Hq).integers(0, most, size=len(session_of), endpoint=True)
     wl = workloads.make_custom(lens, Hq, Hkv, 128, seed=430 + Hq, session_of=session_of, prefix_len=prefix_len)
     check(gpu_attend_prefix(wl), oracle_full(wl))
+
+
+def test_prefix_result_does_not_depend_on_the_size_of_the_workspace(sd):
+    import torch
+    # 1500 branches of two prefixes: a larger workspace would hold the slots of shorter chunks
+    session_of, prefix_len = np.repeat(np.arange(2), 750), np.repeat([448, 300], 750)
+    lens = prefix_len + np.random.default_rng(64).integers(0, 160, size=1500, endpoint=True)
+    wl = workloads.make_custom(lens, 4, 1, 128, seed=494, session_of=session_of, prefix_len=prefix_len)
+    dw = device_workload(wl)
+    a = dw.attend_prefix().clone()
+    dw.ws_bytes *= 16
+    dw.workspace = torch.empty(dw.ws_bytes, dtype=torch.uint8, device=dw.device)
+    assert torch.equal(a, dw.attend_prefix())
 
 
 @pytest.mark.parametrize("d", [128, 64])
