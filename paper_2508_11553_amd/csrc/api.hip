@@ -125,7 +125,7 @@ int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_
     if (s->chunk_tokens || num_groups <= 0 || max_shared_len <= 0 || max_group_size <= 0) return from_shape;
     const int G = s->num_q_heads / s->num_kv_heads;
     const int seqs_per_wg = sd::kWaves * sd::units_per_block(G);
-    const double subs = (max_group_size + seqs_per_wg - 1) / seqs_per_wg;
+    const double subs = (double)(((int64_t)max_group_size + seqs_per_wg - 1) / seqs_per_wg);
     const double tokens = 0.6 * max_shared_len * std::min(num_groups, s->batch) * subs + 0.5 * ((double)s->max_context_len - max_shared_len) * s->batch;
     const double target = std::max(256.0, 1.3 * tokens * s->num_kv_heads * sd::head_blocks(G) / kMaxRangeWorkgroups);
     int best = 256;
@@ -135,7 +135,7 @@ int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_
     }
     const int64_t heads = (int64_t)s->num_kv_heads * sd::head_blocks(G);
     const size_t workspace = sd_workspace_bytes(s);
-    while (best < from_shape && (ws_layout(s, num_chunks(s, best)).total > workspace || num_chunks(s, best) * s->batch * heads > 1 << 22)) best *= 2;
+    while (best < from_shape && (ws_layout(s, num_chunks(s, best)).total > workspace || (int64_t)num_chunks(s, best) * s->batch * heads > 1 << 22)) best *= 2;
     return std::min(best, from_shape);
 }
 
@@ -529,7 +529,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     sa.group_start = shared_chunks ? group_start : nullptr;
     sa.shared_len = shared_chunks ? shared_len : nullptr;
     sa.num_groups = shared_chunks ? num_groups : 0;
-    sa.group_subs = shared_chunks ? (max_group_size + seqs_per_wg - 1) / seqs_per_wg : 0;
+    sa.group_subs = shared_chunks ? (int32_t)(((int64_t)max_group_size + seqs_per_wg - 1) / seqs_per_wg) : 0;
     const uint64_t group_items = (uint64_t)shared_chunks * (uint64_t)sa.num_groups * (uint64_t)sa.group_subs *
                                  (uint64_t)(sa.Hkv * sa.HB);
     sa.grid_chunks = shared_chunks ? S : S - 1;  // the extra slot exists only where a shared prefix splits a chunk

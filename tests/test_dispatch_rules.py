@@ -1,0 +1,57 @@
+"""The host's rules that pick kernels and sizes (CPU only): the library's own functions, compiled for the host with
+UndefinedBehaviorSanitizer."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2508_11553_amd import build as sd_build
+from tests.test_kernel_resources import CSRC
+
+PROGRAM = r"""
+#include "api.hip"
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+int main(int argc, char **argv)
+{
+    int v[16] = {};
+    for (int i = 2; i < argc && i < 18; ++i) v[i - 2] = atoi(argv[i]);
+    // batch, query heads, KV heads, head_dim, KV type, max_context_len come first
+    const sd_shape s = {v[0], v[1], v[2], v[3], 16, 1, (v[5] + 15) / 16, v[4], v[5], 0};
+    if (!strcmp(argv[1], "prefix_chunk")) {   // ... num_groups, max_group_size, max_shared_len
+        const int c = prefix_chunk(&s, v[6], v[7], v[8]);
+        printf("%d %d %d\n", c, pick_chunk(&s), ws_layout(&s, num_chunks(&s, c)).total <= sd_workspace_bytes(&s));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if shutil.which(sd_build.HIPCC) is None and not os.path.exists(sd_build.HIPCC):
+        pytest.skip("needs hipcc")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.hip").write_text(PROGRAM)
+    # only host functions run, so the kernels' launch functions stay undefined
+    r = subprocess.run([sd_build.HIPCC, "--offload-host-only", "-std=c++17", f"-I{CSRC}", "-Xarch_host", "-fsanitize=undefined",
+                        "-Wl,--unresolved-symbols=ignore-all", str(d / "rules.hip"), "-o", str(d / "rules")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def call(*args):
+        r = subprocess.run([str(d / "rules")] + [str(a) for a in args], capture_output=True, text=True, check=True)
+        assert "runtime error" not in r.stderr, r.stderr
+        return [int(x) for x in r.stdout.split()]
+    return call
+
+
+@pytest.mark.parametrize("shape,groups", [
+    ((1500, 4, 1, 128, 0, 608), (2, 750, 448)),             # the slots of the chunk it would like do not fit the workspace
+    ((64, 32, 8, 128, 0, 65536), (4, 2**31 - 1, 4096)),     # group bounds as loose as the type allows
+    ((2**23, 8, 2, 128, 0, 2**21), (1, 16, 2**21)),         # chunks x sequences beyond 32 bits
+    ((1, 1, 1, 64, 1, 16), (1, 1, 16)),
+])
+def test_prefix_chunk_stays_within_its_bounds(rule, shape, groups):
+    chunk, from_shape, fits = rule("prefix_chunk", *shape, *groups)
+    assert fits and 128 <= chunk <= from_shape
