@@ -55,3 +55,17 @@ def rule(tmp_path_factory):
 def test_prefix_chunk_stays_within_its_bounds(rule, shape, groups):
     chunk, from_shape, fits = rule("prefix_chunk", *shape, *groups)
     assert fits and 128 <= chunk <= from_shape
+
+
+@pytest.mark.parametrize("shape,groups", [
+    ((161, 40, 8, 64, 0, 411), (13, 20, 384)),       # a chunk or two per sequence
+    ((46, 32, 4, 128, 0, 14880), (16, 5, 14048)),    # three quarters of the shape's chunk
+])
+def test_prefix_chunk_is_the_shape_s_where_a_shorter_one_does_not_pay(rule, shape, groups):
+    chunk, from_shape, _ = rule("prefix_chunk", *shape, *groups)
+    assert chunk == from_shape
+
+
+def test_prefix_chunk_follows_the_groups(rule):
+    chunk, from_shape, _ = rule("prefix_chunk", 56, 64, 8, 128, 0, 11500, 8, 7, 9000)
+    assert 2 * chunk <= from_shape
