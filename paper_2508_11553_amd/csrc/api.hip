@@ -144,20 +144,19 @@ int prefix_chunk(const sd_shape *s, int num_groups, int max_group_size, int max_
 }
 
 // Whether a batch goes one workgroup per (sequence, KV head) although the chunk rule would cut its sequences.  Against the range
-// pass that saves the second launch, the search for the pieces and the borders between sequences inside them, and loses
-// when few workgroups walk long sequences or the longest ends last.  By the K/V bytes of the longest sequence and the
-// workgroups; measured, us per step, single pass : range pass, over bf16 pools with head_dim 128 (512 bytes per token):
-//   up to 1100 tokens   8 workgroups 9.8 : 13.2, 64 14.1 : 15.5, 200 16.6 : 25, 512 35 : 43
-//   1500                8 workgroups 17 : 13, 64 18.1 : 18.2, 128 19 : 22, 320 36 : 37, 600 53 : 55, 900 69 : 78
-//   2200 - 3000         128 workgroups 30 : 28, 200 34 : 39, 256 44 : 50, 400 76 : 70 (one per compute unit and no more)
+// pass that saves the second launch, the search for the pieces and the borders between sequences inside them.  A workgroup
+// that walks a long sequence alone while the rest of the chip has nothing left to do loses, and the host knows neither how the lengths are
+// spread nor how many are long: so the line is the length at which a lone workgroup (four waves, a 32-token tile at a time each)
+// still ends within a few percent of the range pass, whatever the other sequences hold.  us per step, single pass : range pass, one
+// sequence of that length beside 7 of 50 tokens, 28/4 heads; then 60 of that length, 16/4 heads:
+//   bf16, head_dim 128   1025 11.3 : 12.1  1500 13.5 : 12.0  3000 22.2 : 12.6;   960 18.5 : 27.3   1500 29 : 37
+//   bf16, head_dim 64   1100 7.6 : 10.4  1600 9.2 : 10.3   2300 11.6 : 10.9;                     1600 16.2 : 24.1
+//   fp8, head_dim 128   1280 11.7 : 11.8 2300 18.0 : 12.3;                                       1280 13.6 : 22.7
+//   fp8, head_dim 64    1280 10.0 : 10.1 3000 19.3 : 11.0;                                       1280 10.9 : 16.8
 bool short_enough(const sd_shape *s)
 {
     if (s->chunk_tokens) return false;
-    const int64_t bytes = (int64_t)s->max_context_len * s->head_dim * 2 * (s->kv_dtype == SD_BF16 ? 2 : 1);
-    const int64_t workgroups = (int64_t)s->batch * s->num_kv_heads * sd::head_blocks(s->num_q_heads / s->num_kv_heads);
-    if (bytes <= 576 << 10) return true;
-    if (bytes <= 768 << 10) return workgroups >= 64;
-    return bytes <= 1536 << 10 && workgroups >= 160 && workgroups <= 256;
+    return s->max_context_len <= (s->kv_dtype == SD_BF16 ? (s->head_dim == 128 ? 1024 : 1600) : 1280);
 }
 
 // The device address of `scratch` is asked for once per device, with that device current, and kept.

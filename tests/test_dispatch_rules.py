@@ -23,6 +23,8 @@ int main(int argc, char **argv)
     if (!strcmp(argv[1], "prefix_chunk")) {   // ... num_groups, max_group_size, max_shared_len
         const int c = prefix_chunk(&s, v[6], v[7], v[8]);
         printf("%d %d %d\n", c, pick_chunk(&s), ws_layout(&s, num_chunks(&s, c)).total <= sd_workspace_bytes(&s));
+    } else if (!strcmp(argv[1], "short_enough")) {
+        printf("%d\n", short_enough(&s));
     }
 }
 """
@@ -69,3 +71,12 @@ def test_prefix_chunk_is_the_shape_s_where_a_shorter_one_does_not_pay(rule, shap
 def test_prefix_chunk_follows_the_groups(rule):
     chunk, from_shape, _ = rule("prefix_chunk", 56, 64, 8, 128, 0, 11500, 8, 7, 9000)
     assert 2 * chunk <= from_shape
+
+
+@pytest.mark.parametrize("batch", [1, 16, 40, 64, 1024])
+@pytest.mark.parametrize("kv_dtype,d,limit", [(0, 128, 1024), (0, 64, 1600), (1, 128, 1280), (1, 64, 1280)])
+def test_single_pass_is_bounded_by_what_one_sequence_may_cost(rule, kv_dtype, d, limit, batch):
+    """The lengths are not known here: one sequence of a batch may be as long as the bound and the rest empty, so the number of
+    sequences must not move the line."""
+    assert rule("short_enough", batch, 28, 4, d, kv_dtype, limit) == [1]
+    assert rule("short_enough", batch, 28, 4, d, kv_dtype, limit + 1) == [0]

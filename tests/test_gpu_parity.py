@@ -42,6 +42,16 @@ def gpu_attend(wl, **kw):
     return out.cpu().numpy()
 
 
+def took_the_range_pass(dw, call=None):
+    """Whether a decode call of this workload cuts the batch into ranges: that pass leaves its tile offsets in the workspace,
+    a workgroup per whole sequence leaves nothing there."""
+    import torch
+    dw.workspace.fill_(0xa5)
+    (call or dw.attend)()
+    torch.cuda.synchronize()
+    return bool((dw.workspace[:256] != 0xa5).any())
+
+
 def oracle_full(wl, k_pages=None, v_pages=None):
     return oracle.paged_decode_attention(wl.q, wl.k_pages if k_pages is None else k_pages,
                                          wl.v_pages if v_pages is None else v_pages, wl.block_table,
@@ -87,6 +97,18 @@ def test_results_do_not_depend_on_chunk_beyond_rounding(sd):
 def test_two_runs_are_bitwise_equal(sd):
     wl = workloads.make_custom([700, 1500, 64, 4000], 28, 4, 128, seed=8)
     assert np.array_equal(gpu_attend(wl), gpu_attend(wl))
+
+
+@pytest.mark.parametrize("kv_dtype,d,longest,short", [("bf16", 128, 3000, 1024), ("bf16", 64, 2300, 1600), ("fp8", 128, 3000, 1280), ("fp8", 64, 4600, 1280)])
+@pytest.mark.parametrize("batch", [2, 40, 64])
+def test_one_long_sequence_among_short_ones_is_spread_over_the_chip(sd, batch, kv_dtype, d, longest, short):
+    wl = workloads.make_custom([50, longest] + [50] * (batch - 2), 28, 4, d, kv_dtype, seed=21)
+    dw = device_workload(wl)
+    assert took_the_range_pass(dw)
+    (check_fp8 if kv_dtype == "fp8" else check)(dw.out.cpu().numpy(), oracle_full(wl))
+    dw = device_workload(workloads.make_custom([short, 50], 28, 4, d, kv_dtype, seed=22))
+    assert not took_the_range_pass(dw)
+    (check_fp8 if kv_dtype == "fp8" else check)(dw.out.cpu().numpy(), oracle_full(dw.wl))
 
 
 def test_zero_length_sequences_give_zero_rows(sd):
