@@ -53,21 +53,27 @@ SD_DEV int64_t partial_slot(int r, int gv, int Hv, int o0, int per)
     return ((int64_t)r * Hv + gv) * 2 + (o0 > r * per ? 1 : 0);
 }
 
-// Combines the partials that the ranges of `parts` hold for up to kMergeRows query heads of one
+// Combines the partials that the ranges of `parts` hold for up to NL * kMergeRows query heads of one
 // (sequence, head block), heads r0 .. r0 + rows - 1 of the block, and writes columns [col0, col0 + 64) of their rows of
-// `out` starting at row0.  16 lanes take a row, 16 bytes each, and PB partials are fetched at
+// `out` starting at row0.  16 / NL lanes take a row, NL times 16 bytes each, and PB partials are fetched at
 // a time, all loads in flight together, so up to PB partials cost one trip to memory.  a.groups
-// waves take turns over the batches of PB partials (this one is number `group`) and group 0
+// waves (NL == 1 only) take turns over the batches of PB partials (this one is number `group`) and group 0
 // adds their sums up through `lds`.  Partials are folded in a fixed order with a running maximum.
-template <int D>
+template <int D, int NL>
 SD_DEV void combine_parts(const RangeMergeArgs &a, const LiveParts &parts, int gv, int Hv, int o0, int per,
                           int r0, int rows, int64_t row0, int col0, int lane, int group, float *lds)
 {
-    constexpr int PB = kMergeParts;
-    const int mr = lane >> 4, col = col0 + (lane & 15) * 4;
+    constexpr int PB = NL > 2 ? kMergeParts / 2 : kMergeParts;
+    constexpr int kLanes = 16 / NL;
+    const int mr = lane / kLanes, col = col0 + lane % kLanes * 4;
     const bool mine = mr < rows;
+    struct Piece {   // what the lane holds of a row
+        f32x4 w[NL];
+    };
     float M = -INFINITY, den = 0.f;
-    f32x4 num = {0, 0, 0, 0};
+    Piece num;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) num.w[j] = f32x4{0, 0, 0, 0};
     auto fold = [&](const auto &m, const auto &l, const auto &v, auto count) {
         float Mn = M;
 #pragma unroll
@@ -75,45 +81,52 @@ SD_DEV void combine_parts(const RangeMergeArgs &a, const LiveParts &parts, int g
         const float shrink = __builtin_amdgcn_exp2f(M - Mn);  // first batch: exp2(-inf) = 0 on zeros
         M = Mn;
         den *= shrink;
-        num *= shrink;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) num.w[j] *= shrink;
 #pragma unroll
         for (int p = 0; p < count; ++p) {
             const float w = __builtin_amdgcn_exp2f(m[p] - M);
             den += w * l[p];
-            num += w * v[p];
+#pragma unroll
+            for (int j = 0; j < NL; ++j) num.w[j] += w * v[p].w[j];
         }
     };
     if (mine)
-        for (int base = group * PB; base < parts.count; base += a.groups * PB) {
+        for (int base = group * PB; base < parts.count; base += (NL == 1 ? a.groups : 1) * PB) {
             float m[PB], l[PB];
-            f32x4 v[PB];
+            Piece v[PB];
 #pragma unroll
             for (int p = 0; p < PB; ++p) {
                 const bool valid = base + p < parts.count;   // wave-uniform
                 const int64_t ps = partial_slot(parts.range(valid ? base + p : 0), gv, Hv, o0, per);
                 m[p] = valid ? a.ws_m[ps * kMaxGroup + r0 + mr] : -INFINITY;
                 l[p] = valid ? a.ws_l[ps * kMaxGroup + r0 + mr] : 0.f;
-                v[p] = valid ? *reinterpret_cast<const f32x4 *>(a.ws_acc + (ps * a.rows_stride + r0 + mr) * D + col) : f32x4{0, 0, 0, 0};
+                const float *src = a.ws_acc + (ps * a.rows_stride + r0 + mr) * D + col;
+#pragma unroll
+                for (int j = 0; j < NL; ++j) v[p].w[j] = valid ? *reinterpret_cast<const f32x4 *>(src + j * kLanes * 4) : f32x4{0, 0, 0, 0};
             }
             fold(m, l, v, std::integral_constant<int, PB>{});
         }
-    if (a.groups > 1) {   // [group][lane]: sums, then maximum and weight sum
-        const int used = min(a.groups, (parts.count + PB - 1) / PB);   // later groups had nothing to do
-        float *at = lds + (group * 64 + lane) * 4, *head = lds + a.groups * 64 * 4 + (group * 64 + lane) * 2;
-        if (group > 0 && group < used) {
-            *reinterpret_cast<f32x4 *>(at) = num;
-            *reinterpret_cast<f32x2 *>(head) = f32x2{M, den};
+    if constexpr (NL == 1)
+        if (a.groups > 1) {   // [group][lane]: sums, then maximum and weight sum
+            const int used = min(a.groups, (parts.count + PB - 1) / PB);   // later groups had nothing to do
+            float *at = lds + (group * 64 + lane) * 4, *head = lds + a.groups * 64 * 4 + (group * 64 + lane) * 2;
+            if (group > 0 && group < used) {
+                *reinterpret_cast<f32x4 *>(at) = num.w[0];
+                *reinterpret_cast<f32x2 *>(head) = f32x2{M, den};
+            }
+            __syncthreads();
+            if (group > 0) return;
+            for (int w = 1; w < used; ++w) {
+                const f32x2 h = *reinterpret_cast<const f32x2 *>(head + w * 64 * 2);
+                const float m[1] = {h[0]}, l[1] = {h[1]};
+                const Piece v[1] = {*reinterpret_cast<const f32x4 *>(at + w * 64 * 4)};
+                fold(m, l, v, std::integral_constant<int, 1>{});
+            }
         }
-        __syncthreads();
-        if (group > 0) return;
-        for (int w = 1; w < used; ++w) {
-            const f32x2 h = *reinterpret_cast<const f32x2 *>(head + w * 64 * 2);
-            const float m[1] = {h[0]}, l[1] = {h[1]};
-            const f32x4 v[1] = {*reinterpret_cast<const f32x4 *>(at + w * 64 * 4)};
-            fold(m, l, v, std::integral_constant<int, 1>{});
-        }
-    }
-    if (mine) *reinterpret_cast<f32x4 *>(a.out + (row0 + mr) * D + col) = num / den;
+    if (mine)
+#pragma unroll
+        for (int j = 0; j < NL; ++j) *reinterpret_cast<f32x4 *>(a.out + (row0 + mr) * D + col + j * kLanes * 4) = num.w[j] / den;
 }
 
 // Two waves per SIMD, also for the probe, whose few registers would otherwise let the dispatcher
@@ -379,8 +392,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // Merge pass of the range design.  A sequence that one range held whole was written by the wave
-// that walked it; a sequence that was cut is combined here.  One workgroup per item and slice of kMergeRows
-// query heads: a.groups sets of waves (a wave of a set takes 64 columns); an item is a (sequence, head block) when
+// that walked it; a sequence that was cut is combined here.  One workgroup per item and NL slices of kMergeRows
+// query heads (merge_width): a.groups sets of waves (a wave of a set takes 64 columns); an item is a (sequence, head block) when
 // the batch has fewer sequences than the grid has ranges, else a (range, head block): the range pass leaves, per range,
 // a record of the cut sequence whose first part lies there (at most one).
 //
@@ -389,15 +402,15 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 // host gives small batches more sets (merge_groups), and heads are spread over workgroups because one compute unit
 // would take 16 us for the 2 MB of parts that 16 heads leave.  Against one workgroup of two waves per item, us per decode step:
 // 3 sequences of 9 k - 33 k, 32/8 heads 33.7 -> 31.1; one of 20 k, 32/8 heads 30.0 -> 23.2, fp8, 32/4 heads 29.9 -> 20.6;
-// two of 9 k - 39 k, 32/2 heads 43 -> 22; batches of 8 and more unchanged.
-template <int D>
-__global__ __launch_bounds__(D * kMaxMergeGroups) void range_merge_kernel(RangeMergeArgs a)
+// two of 9 k - 39 k, 32/2 heads 43 -> 22; batches of 8 and more unchanged.  Many items keep their heads together (NL > 1).
+template <int D, int NL>
+__global__ __launch_bounds__(NL == 1 ? D * kMaxMergeGroups : D) void range_merge_kernel(RangeMergeArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float merge_lds[];
     const int Hv = a.Hkv * a.HB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = wave % (D / 64), group = wave / (D / 64);
-    const int r0 = blockIdx.y * kMergeRows;
+    const int r0 = blockIdx.y * (NL * kMergeRows);
     const int gv = blockIdx.x % Hv;
     int b, o0, o1, T;
     if (a.by_sequence) {
@@ -415,7 +428,7 @@ __global__ __launch_bounds__(D * kMaxMergeGroups) void range_merge_kernel(RangeM
     const LiveParts parts = live_parts(o0, o1, T, per);
     const HeadBlock hb = head_block(gv, a.G, a.HB);
     if (parts.count == 1 || r0 >= hb.rows) return;   // everything so far was workgroup-uniform
-    combine_parts<D>(a, parts, gv, Hv, o0, per, r0, min(kMergeRows, hb.rows - r0), (int64_t)b * a.Hq + hb.head0 + r0, part * 64, lane, group,
+    combine_parts<D, NL>(a, parts, gv, Hv, o0, per, r0, min(NL * kMergeRows, hb.rows - r0), (int64_t)b * a.Hq + hb.head0 + r0, part * 64, lane, group,
                      merge_lds + part * a.groups * (kMergeLdsBytes / 4));
 }
 
@@ -423,7 +436,8 @@ hipError_t launch_range_merge(const RangeMergeArgs &a, int head_dim, hipStream_t
 {
     const unsigned items = (unsigned)(a.by_sequence ? a.B : a.ranges) * (unsigned)(a.Hkv * a.HB);
     if (items == 0 || a.B == 0) return hipSuccess;
-    const dim3 grid(items, (unsigned)(a.rows_stride + kMergeRows - 1) / kMergeRows);
+    const int width = merge_width(items, a.rows_stride, a.groups);
+    const dim3 grid(items, (unsigned)(a.rows_stride + width * kMergeRows - 1) / (width * kMergeRows));
     const size_t lds = a.groups > 1 ? (size_t)(head_dim / 64 * a.groups) * kMergeLdsBytes : 0;
     auto go = [&](auto kernel) {
         if (start || stop)
@@ -432,9 +446,9 @@ hipError_t launch_range_merge(const RangeMergeArgs &a, int head_dim, hipStream_t
             hipLaunchKernelGGL(kernel, grid, dim3(head_dim * a.groups), lds, stream, a);
     };
     if (head_dim == 128)
-        go(range_merge_kernel<128>);
+        width == 4 ? go(range_merge_kernel<128, 4>) : width == 2 ? go(range_merge_kernel<128, 2>) : go(range_merge_kernel<128, 1>);
     else if (head_dim == 64)
-        go(range_merge_kernel<64>);
+        width == 4 ? go(range_merge_kernel<64, 4>) : width == 2 ? go(range_merge_kernel<64, 2>) : go(range_merge_kernel<64, 1>);
     else
         return hipErrorNotSupported;
     return hipGetLastError();

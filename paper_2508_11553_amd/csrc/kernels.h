@@ -228,6 +228,21 @@ __host__ inline int merge_groups(int rblocks, int batch)
     while (groups < kMaxMergeGroups && groups * kMergeParts < parts) groups *= 2;
     return groups;
 }
+// Slices of kMergeRows heads of an item that one workgroup of the merge pass takes together: 1, 2 or 4.  Slices of their own spread the parts
+// of few items over the chip; where the items alone fill it, they only multiply the workgroups that go through the
+// pass's chain of dependent reads.  Merge pass, us with a slice per workgroup : all of them in one:
+//   4 slices    256 items   64 sequences, 64/2 heads, d = 128 4.6 : 4.3, the same with one of 24 k tokens 17.6 : 21.8
+//               512         128 sequences, 64/4 heads, d = 64 4.8 : 4.2, 64 sequences, 128/4 heads, d = 128 6.6 : 4.7
+//              1024         128 sequences, 128/8 heads, d = 64 6.6 : 4.4, with one of 5 k tokens 9.5 : 6.2
+//              2048         1373 sequences, one of 4 k and the rest of 67 tokens, 64/4 heads, d = 64 11.3 : 6.4
+//   2 slices   1200         300 sequences with one of 5 k tokens, 32/4 heads, d = 64 5.5 : 6.0
+//              2048         300 sequences with one of 5 k tokens, 64/8 heads, d = 64 6.2 : 5.1
+__host__ inline int merge_width(int64_t items, int rows, int groups)
+{
+    if (groups > 1 || rows <= kMergeRows) return 1;   // several waves per part share their sums through LDS, a slice at a time
+    if (rows <= 2 * kMergeRows) return items >= 2048 ? 2 : 1;
+    return items >= 512 ? 4 : 1;
+}
 
 struct MergeArgs {
     const float *ws_m, *ws_l, *ws_acc;

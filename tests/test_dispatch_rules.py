@@ -25,6 +25,8 @@ int main(int argc, char **argv)
         printf("%d %d %d\n", c, pick_chunk(&s), ws_layout(&s, num_chunks(&s, c)).total <= sd_workspace_bytes(&s));
     } else if (!strcmp(argv[1], "short_enough")) {
         printf("%d\n", short_enough(&s));
+    } else if (!strcmp(argv[1], "merge_width")) {   // items, rows, groups
+        printf("%d\n", sd::merge_width(v[0], v[1], v[2]));
     }
 }
 """
@@ -80,3 +82,9 @@ def test_single_pass_is_bounded_by_what_one_sequence_may_cost(rule, kv_dtype, d,
     sequences must not move the line."""
     assert rule("short_enough", batch, 28, 4, d, kv_dtype, limit) == [1]
     assert rule("short_enough", batch, 28, 4, d, kv_dtype, limit + 1) == [0]
+
+
+@pytest.mark.parametrize("items,rows,groups,width", [(512, 16, 1, 4), (2048, 16, 1, 4), (2048, 9, 1, 4), (2048, 8, 1, 2), (2048, 4, 1, 1),
+                                                     (256, 16, 1, 1), (1024, 8, 1, 1), (2048, 16, 2, 1)])
+def test_merge_pass_cuts_heads_only_where_items_are_few(rule, items, rows, groups, width):
+    assert rule("merge_width", items, rows, groups) == [width]

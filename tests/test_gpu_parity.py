@@ -169,6 +169,25 @@ def test_few_long_sequences_leave_many_parts(sd, lens, Hq, Hkv, d):
     check(gpu_attend(wl), oracle_full(wl))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,batch", [
+    (128, 8, 64), (72, 8, 64), (40, 2, 128),         # 512 items by sequence with 16, 9 and 16 + 4 heads: kept together
+    (128, 8, 63), (64, 8, 256),                      # fewer items, or 8 heads: a slice of 4 heads per workgroup
+    (64, 8, 300), (40, 8, 300), (128, 8, 300),       # more sequences than ranges: 8, 5 and 16 heads together
+])
+def test_merge_pass_over_many_items(sd, Hq, Hkv, batch, d):
+    """One sequence of 20000 tokens leaves more parts than one trip to memory fetches (8 or 16), the others are cut once or not at all."""
+    import torch
+    lens = [20000] + [20 + (37 * i) % 90 for i in range(batch - 1)]
+    wl = workloads.make_custom(lens, Hq, Hkv, d, seed=910 + Hq + d)
+    dw = device_workload(wl, chunk_tokens=128)
+    assert took_the_range_pass(dw)
+    dw.out.fill_(float("nan"))
+    got = dw.attend().clone()
+    torch.cuda.synchronize()
+    check(got.cpu().numpy(), oracle_full(wl))
+
+
 def test_more_sequences_than_ranges(sd):
     """1300 short sequences: more than the grid has ranges per head, so the merge pass works from the records the
     range pass leaves per range; ranges of twelve tiles cut many of the sequences, inside workgroups and between them."""
