@@ -22,7 +22,7 @@
 // Large calls: each wave carries its rows through the whole range with the
 // online softmax, so there is no split and no merge.  Small calls, whose query blocks
 // would leave compute units idle, take smaller blocks and split their range over the waves of
-// the workgroup (prefill_blocks): kSplit neighbouring waves own the same rows and
+// the workgroup (prefill_plan): kSplit neighbouring waves own the same rows and
 // every kSplit-th tile each, and add up their (max, sum, weighted sum) through LDS at
 // the end.  Nothing leaves the workgroup, so no workspace is needed.
 #include <cfloat>
@@ -695,17 +695,17 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
         else
             hipLaunchKernelGGL(kernel, g, b, 0, stream, a);
     };
-    // the instances for the four block sizes of prefill_blocks: waves, tiles of a round, split, column blocks per wave, waves per SIMD
+    // the instances for the plans: waves, tiles of a round, split, column blocks per wave, waves per SIMD
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
-        switch (a.blocks) {
-        case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us, 89 - 547, 40/8 heads 15.0 against 18.5)
+        switch (a.plan.blocks) {
+        case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us)
             if constexpr (std::is_same<P, Bf16Path<128>>::value)
-                if (a.max_context_len >= kPrefillShort) return go(prefill_pingpong_kernel, 8);
+                if (a.plan.phases) return go(prefill_pingpong_kernel, 8);
             return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
         case 8:
             if constexpr (P::kScaled)
-                if (a.max_context_len < kPrefillShort) return go(prefill_wide_kernel<P, 4, 2, 1, 2, 2>, 4);
+                if (a.plan.split == 1) return go(prefill_wide_kernel<P, 4, 2, 1, 2, 2>, 4);
             return go(prefill_wide_kernel<P, 8, 4, 2, 2, 2>, 8);
         case 4: return go(prefill_wide_kernel<P, 8, 4, 4, 2, 2>, 8);
         default: return go(prefill_wide_kernel<P, 8, 8, 8, 2, 2>, 8);
@@ -713,7 +713,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     };
     auto narrow = [&](auto path) {   // head_dim 64: half the operands per tile, so a wave has room for four blocks, or a compute unit for three workgroups
         typedef decltype(path) P;
-        switch (a.blocks) {
+        switch (a.plan.blocks) {
         case 16:
             if constexpr (std::is_same<P, Bf16Path<64>>::value)
                 return go(prefill_direct_kernel<4>, 4);

@@ -120,7 +120,7 @@ SD_DEV void combine_parts(const RangeMergeArgs &a, const LiveParts &parts, int g
             for (int w = 1; w < used; ++w) {
                 const f32x2 h = *reinterpret_cast<const f32x2 *>(head + w * 64 * 2);
                 const float m[1] = {h[0]}, l[1] = {h[1]};
-                const Piece v[1] = {*reinterpret_cast<const f32x4 *>(at + w * 64 * 4)};
+                const Piece v[1] = {{{*reinterpret_cast<const f32x4 *>(at + w * 64 * 4)}}};
                 fold(m, l, v, std::integral_constant<int, 1>{});
             }
         }

@@ -74,6 +74,12 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
     const int rest = pairs % kXcds, classes = prefill_classes(rest);
     return (unsigned)(pairs / kXcds * kXcds) * (unsigned)q_blocks + (rest ? (unsigned)(rest * classes) * (unsigned)((q_blocks + classes - 1) / classes) : 0u);
 }
+// How a call of the causal pass is cut: column blocks of 16 query rows that a workgroup owns (16, 8, 4 or 2), the waves that share the
+// range of a block, and whether the workgroups run in two phases (bf16 pools with head_dim 128).
+struct PrefillPlan {
+    int blocks, split;
+    bool phases;
+};
 // Column blocks of 16 query rows that one workgroup of the causal pass owns: 16, 8, 4 or 2.  Large blocks share a
 // tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several waves
 // share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip:
@@ -89,6 +95,8 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
 //                 16 whole prompts of 200 - 1000, 32/8 heads                    72 /  61 / 109 / 225
 //                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      203 / 161 / 157 / 222
 //                 3 sequences of 1 k - 6 k, 50 - 400 queries, 32/8 heads       137 /  92 /  49 /  40
+// The two phases leave the matrix pipe to the waves in turn, also to those without rows: by the share of the 16 blocks that the average
+// sequence's queries fill, time against one phase: up to 0.1 1.27, 0.2 1.22, 0.3 1.14, 0.5 1.04, 0.8 to 1 0.97, above 4 0.95.
 // (Taken with 16 blocks on the general kernel; the kernels that bf16 pools have for 16 blocks take 4 - 7 % less: 259, 540 and 1828 us where 296, 579
 // and 1885 stand, the other machine's share taken out: 272, 560, 1909.)
 // Short contexts (below kPrefillShort tokens) have few tiles to share: no split, 8 blocks of four waves over fp8 pools and at head_dim 64, 16 blocks
@@ -96,18 +104,18 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
 // At head_dim 128 160 workgroups of 16 blocks still beat twice as many halves, which take two turns at 256 compute units (4
 // sequences of 7 k, 16/2 heads: 219 against 251 us).
 constexpr int kPrefillShort = 512;
-__host__ inline int prefill_blocks(int kv_dtype, int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
+__host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
 {
     const auto workgroups = [&](int blocks) { return (total_q / (blocks * units) + batch) * heads; };   // about
     if (head_dim == 64) {
-        if (workgroups(16) >= 2048) return 16;
-        if (workgroups(8) >= 512 || max_context_len < kPrefillShort) return 8;
-        return workgroups(4) >= 512 || max_context_len < 1024 ? 4 : 2;
+        if (workgroups(16) >= 2048) return PrefillPlan{16, 1, false};
+        if (workgroups(8) >= 512 || max_context_len < kPrefillShort) return PrefillPlan{8, 1, false};
+        return workgroups(4) >= 512 || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }
-    if (max_context_len < kPrefillShort) return kv_dtype == 0 ? 16 : 8;
-    if (workgroups(16) >= 160) return 16;
-    if (workgroups(8) >= 256) return 8;
-    return workgroups(4) >= 192 || max_context_len < 1024 ? 4 : 2;
+    if (max_context_len < kPrefillShort) return kv_dtype == 0 ? PrefillPlan{16, 1, false} : PrefillPlan{8, 1, false};
+    if (workgroups(16) >= 160) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+    if (workgroups(8) >= 256) return PrefillPlan{8, 2, false};
+    return workgroups(4) >= 192 || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens
@@ -266,8 +274,8 @@ struct PrefillArgs {
     uint32_t q_keep;             // 0 when scale == 0 (all scores are zero: zero queries, scale 1), else all ones
     int32_t B, Hq, Hkv, G, HB, max_blocks, max_context_len;  // HB: head blocks per KV head, ceil(G / 16)
     int32_t total_q, max_q_len;  // rows of q; host-known bound on the rows of one sequence
-    int32_t blocks;              // column blocks of 16 rows that a workgroup owns (see prefill_blocks)
-    int32_t q_blocks;            // workgroups (blocks x 16/G query tokens each) that cover max_q_len
+    PrefillPlan plan;
+    int32_t q_blocks;            // workgroups (plan.blocks x 16/G query tokens each) that cover max_q_len
 };
 
 struct AppendArgs {

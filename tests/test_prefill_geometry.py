@@ -15,7 +15,8 @@ PROGRAM = r"""
 int main(int argc, char **argv)
 {
     if (argc > 3) {
-        printf("%d\n", sd::prefill_blocks(0, atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])));
+        const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
+        printf("%d %d %d\n", p.blocks, p.split, p.phases);
         return 0;
     }
     const int q_blocks = atoi(argv[1]), pairs = atoi(argv[2]);
@@ -74,9 +75,22 @@ def block_case(blocks, d):
     return lens, [min(n, L) for n, L in zip(q, lens)], Hq, Hkv
 
 
+def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None):
+    """(column blocks of a workgroup, waves that share a block's range, two phases) of a call."""
+    G = Hq // Hkv
+    args = (d, sum(q), len(lens), Hkv * ((G + 15) // 16), 16 // G if G <= 8 else 1, bound or max(lens), int(kv_dtype == "fp8"))
+    got = subprocess.run([program] + [str(x) for x in args], capture_output=True, text=True, check=True)
+    return tuple(int(x) for x in got.stdout.split())
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("blocks", [16, 8, 4, 2])
 def test_the_block_cases_are_what_they_say(program, blocks, d):
-    lens, q, Hq, Hkv = block_case(blocks, d)
-    got = subprocess.run([program] + [str(x) for x in (d, sum(q), len(lens), Hkv, 16 // (Hq // Hkv), max(lens))], capture_output=True, text=True, check=True)
-    assert int(got.stdout) == blocks
+    assert plan(program, *block_case(blocks, d), d)[0] == blocks
+
+
+def test_two_phases_only_where_most_waves_have_rows(program):
+    """49 sequences with a query or two each: the waves without rows would take their turn at the matrix pipe all the same."""
+    assert plan(program, [43] * 24 + [2539] * 25, [1] * 49, 128, 4, 128)[2] == 0
+    assert plan(program, [8192] * 16, [2048] * 16, 32, 8, 128) == (16, 1, 1)
+
