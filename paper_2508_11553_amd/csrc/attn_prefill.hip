@@ -713,12 +713,9 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     };
     auto narrow = [&](auto path) {   // head_dim 64: half the operands per tile, so a wave has room for four blocks, or a compute unit for three workgroups
         typedef decltype(path) P;
+        if constexpr (std::is_same<P, Bf16Path<64>>::value)
+            if (a.plan.blocks == 16) return go(prefill_direct_kernel<4>, 4);
         switch (a.plan.blocks) {
-        case 16:
-            if constexpr (std::is_same<P, Bf16Path<64>>::value)
-                return go(prefill_direct_kernel<4>, 4);
-            else
-                return go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);   // (four blocks per wave do not fit beside the codes)
         case 8: return go(prefill_wide_kernel<P, 4, 2, 1, 2, 3>, 4);
         case 4: return go(prefill_wide_kernel<P, 4, 4, 4, 4, 2>, 4);
         default: return go(prefill_wide_kernel<P, 8, 8, 8, 2, 2>, 8);

@@ -80,42 +80,45 @@ struct PrefillPlan {
     int blocks, split;
     bool phases;
 };
-// Column blocks of 16 query rows that one workgroup of the causal pass owns: 16, 8, 4 or 2.  Large blocks share a
-// tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several waves
-// share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip:
-// head_dim 128 runs one workgroup per compute unit, head_dim 64 two or three, and blocks of 16 beat blocks of 8 there
-// only from four rounds of the chip on.  A wave keeps at least four tiles of the longest range to itself.
-// Measured, us with 16 / 8 / 4 / 2 blocks:
-//   head_dim 128, 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads      150 /  98 /  91 / 100
-//                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      296 / 278 / 360 / 419
-//                 8 sequences of 2 k - 8 k, 512 - 1400 queries, 32/8 heads     579 / 634 / 834 / -
-//                 1 sequence of 3000, 64 queries, 16/2 heads                    88 /  58 /  42 /  30
-//                 10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads        36 /  27 /  21 /  26
-//   head_dim 64   16 sequences of 8192, 2048 queries, 32/8 heads              1885 / 2029 / 2373 / 3678
-//                 16 whole prompts of 200 - 1000, 32/8 heads                    72 /  61 / 109 / 225
-//                 6 sequences of 2 k - 8 k, 100 - 700 queries, 32/8 heads      203 / 161 / 157 / 222
-//                 3 sequences of 1 k - 6 k, 50 - 400 queries, 32/8 heads       137 /  92 /  49 /  40
+// Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
+// waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
+// workgroup per compute unit at head_dim 128, which runs one at a time, and one at head_dim 64, which runs two or three.  Workgroups whose
+// rows are mostly empty end early, and long ranges gain more by being shared, so both move the line up.  Short
+// contexts (below kPrefillShort tokens) have few tiles to share: no split.  The lines were fitted to 4200 random calls (1 to 64 sequences of 1 to
+// 12000 tokens, 1 to 3000 queries each, 1 to 32 heads per KV head, bounds tight and 4 and 16 times too wide), each timed with every
+// block size.  Geometric mean of the time with 16 / 8, 8 / 4 and 4 / 2 blocks, by workgroups of the larger block (bf16, tight bounds):
+//   workgroups       64 - 95  96 - 127  128 - 159  160 - 191  192 - 255  256 - 383  512 - 767  1024 and more
+//   head_dim 128  16   1.32     1.22       1.10       1.04       0.96       0.91       0.86       0.76
+//                  8   1.27     1.18       1.06       0.98       0.96       0.90       0.78       0.74
+//                  4   1.20     1.11       0.99       0.87       0.86       0.92       0.80       0.72
+//   head_dim 64   16   1.33     1.34       1.31       1.20       1.28       1.15       1.05       1.02; from 4096 on 0.96
+//                  8   1.52     1.40       1.31       1.27       1.34       1.12       0.97       0.77
+//                  4   1.41     1.33       1.46       0.92       0.98       0.79       0.81       0.54
+// Contexts of 2048 tokens and more, whose last workgroup runs longer, move the lines up again.  At head_dim 64 blocks of 16 are
+// for bf16 pools (over fp8 pools they take 1.1 to 1.2 of the time of 8 from 256 workgroups on).
 // The two phases leave the matrix pipe to the waves in turn, also to those without rows: by the share of the 16 blocks that the average
 // sequence's queries fill, time against one phase: up to 0.1 1.27, 0.2 1.22, 0.3 1.14, 0.5 1.04, 0.8 to 1 0.97, above 4 0.95.
-// (Taken with 16 blocks on the general kernel; the kernels that bf16 pools have for 16 blocks take 4 - 7 % less: 259, 540 and 1828 us where 296, 579
-// and 1885 stand, the other machine's share taken out: 272, 560, 1909.)
-// Short contexts (below kPrefillShort tokens) have few tiles to share: no split, 8 blocks of four waves over fp8 pools and at head_dim 64, 16 blocks
-// over bf16 pools (5 sequences of 89 - 547, 40/8 heads, bf16: 15.0 us against 17.7 with a split; 3 of 182 - 304, 64/8 heads, fp8: 24.5 against 27.4).
-// At head_dim 128 160 workgroups of 16 blocks still beat twice as many halves, which take two turns at 256 compute units (4
-// sequences of 7 k, 16/2 heads: 219 against 251 us).
 constexpr int kPrefillShort = 512;
 __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
 {
-    const auto workgroups = [&](int blocks) { return (total_q / (blocks * units) + batch) * heads; };   // about
+    const auto filled = [&](int blocks, int of) { return total_q * of >= (int64_t)blocks * units * batch; };   // a block's share of 1 / of, on average
+    const auto workgroups = [&](int blocks) {   // about: a sequence's last one is half full
+        const int64_t n = total_q / (blocks * units) + batch / 2;
+        return (n > batch ? n : batch) * heads;
+    };
+    const bool deep = max_context_len >= 2048;
     if (head_dim == 64) {
-        if (workgroups(16) >= 2048) return PrefillPlan{16, 1, false};
-        if (workgroups(8) >= 512 || max_context_len < kPrefillShort) return PrefillPlan{8, 1, false};
-        return workgroups(4) >= 512 || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+        if (kv_dtype == 0 && workgroups(16) >= 2048 && filled(16, 2)) return PrefillPlan{16, 1, false};
+        if (max_context_len < kPrefillShort || workgroups(8) >= (deep ? 512 : 256)) return PrefillPlan{8, 1, false};
+        return workgroups(4) >= (max_context_len >= 4096 ? 384 : deep ? 256 : 128) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }
     if (max_context_len < kPrefillShort) return kv_dtype == 0 ? PrefillPlan{16, 1, false} : PrefillPlan{8, 1, false};
-    if (workgroups(16) >= 160) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
-    if (workgroups(8) >= 256) return PrefillPlan{8, 2, false};
-    return workgroups(4) >= 192 || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+    // (for 8 blocks the cost over all calls is flat between 128 and 192; 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads have 228: 98 : 91 us with 4)
+    const auto enough = [&](int blocks) { return workgroups(blocks) * 4 >= (blocks == 8 || !filled(blocks, 2) ? 192 : 128) * (deep ? 5 : 4); };
+    if (enough(16)) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+    if (enough(8)) return PrefillPlan{8, 2, false};
+    // (10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads: 4 blocks 19, 2 blocks 23 us)
+    return enough(4) || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens

@@ -65,12 +65,12 @@ def block_case(blocks, d):
     if d == 128:
         lens, q, Hq, Hkv = {16: (edge * 4 + [600], [1, 3, 17, 33] * 10 + [40], 16, 8),
                             8: ([700, 512, 400, 129, 33], [1000] * 5, 16, 8),
-                            4: (edge[4:] + [700], [120] * 7, 8, 4),
+                            4: (edge[4:] + [700], [120] * 7, 16, 8),
                             2: (edge[4:] + [1030, 1500], [70] * 8, 8, 4)}[blocks]
     else:
-        lens, q, Hq, Hkv = {16: (edge * 7, [1, 3, 17, 33, 2] * 14, 32, 32),
+        lens, q, Hq, Hkv = {16: ([129, 145, 160, 130] * 16 + edge, [160] * 74, 32, 32),
                             8: (edge + edge[2:], [1, 40, 130] * 6, 32, 32),
-                            4: (edge[4:] + [700], [120] * 7, 8, 4),
+                            4: (edge[4:] + [700], [120] * 7, 16, 8),
                             2: (edge[4:] + [1030, 1500], [70] * 8, 8, 4)}[blocks]
     return lens, [min(n, L) for n, L in zip(q, lens)], Hq, Hkv
 
@@ -94,3 +94,13 @@ def test_two_phases_only_where_most_waves_have_rows(program):
     assert plan(program, [43] * 24 + [2539] * 25, [1] * 49, 128, 4, 128)[2] == 0
     assert plan(program, [8192] * 16, [2048] * 16, 32, 8, 128) == (16, 1, 1)
 
+
+def test_workgroups_that_fill_the_chip_are_not_cut_further(program):
+    assert plan(program, [60] * 59 + [1185], [49] * 60, 8, 2, 64, bound=18960)[0] == 4
+    assert plan(program, [348] * 18, [32] * 18, 32, 4, 64, bound=1392)[0] >= 4
+
+
+def test_16_blocks_at_head_dim_64_are_for_bf16_pools_and_full_workgroups(program):
+    assert plan(program, [1500] * 50, [280] * 50, 128, 4, 64, "fp8") == (8, 1, 0)
+    assert plan(program, [92] * 61, [15] * 61, 32, 32, 64) == (8, 1, 0)
+    assert plan(program, [3000] * 8, [3000] * 8, 32, 8, 64) == (16, 1, 0)
