@@ -52,6 +52,22 @@ def took_the_range_pass(dw, call=None):
     return bool((dw.workspace[:256] != 0xa5).any())
 
 
+ONE_TILE = -1   # as min_range: ranges of one 32-token tile and up
+
+
+def with_ranges(lens, *args, min_range, **kw):
+    """(workload, its upload) for a call whose ranges hold at least `min_range` tokens.  With 0 the library takes batches
+    of short sequences whole; ONE_TILE gives it a length bound so loose that it does not."""
+    if min_range != ONE_TILE:
+        wl = workloads.make_custom(lens, *args, **kw)
+        return wl, device_workload(wl, chunk_tokens=min_range)
+    wl = workloads.make_custom(lens, *args, **dict(kw, max_blocks_per_seq=400))
+    wl.max_context_len = 6400
+    dw = device_workload(wl)
+    assert took_the_range_pass(dw)
+    return wl, dw
+
+
 def oracle_full(wl, k_pages=None, v_pages=None):
     return oracle.paged_decode_attention(wl.q, wl.k_pages if k_pages is None else k_pages,
                                          wl.v_pages if v_pages is None else v_pages, wl.block_table,
@@ -119,15 +135,14 @@ def test_zero_length_sequences_give_zero_rows(sd):
 
 
 @pytest.mark.parametrize("kv_dtype,d", [("bf16", 64), ("bf16", 128), ("fp8", 128), ("fp8", 64)])
-@pytest.mark.parametrize("min_range", [0, 128, 640, 4096])
+@pytest.mark.parametrize("min_range", [0, ONE_TILE, 128, 640, 4096])
 def test_whole_and_cut_sequences_in_one_launch(sd, kv_dtype, d, min_range):
     """Ranges of at least `min_range` tokens: from one tile per wave (every sequence cut into many partials
-    that the last wave combines) to one wave holding the whole batch (every sequence written by the wave that
-    walked it).  Empty sequences must get their zero rows and every element of `out` must be written."""
+    that the merge pass combines) to ranges that hold whole sequences (written by the wave that walked them); 0 and
+    4096 take every sequence whole, a workgroup each.  Empty sequences must get their zero rows and every element of `out` must be written."""
     import torch
     lens = [0, 40, 1, 513, 0, 640, 639, 16, 17, 0]
-    wl = workloads.make_custom(lens, 8, 2, d, kv_dtype, seed=12, max_blocks_per_seq=41)
-    dw = device_workload(wl, chunk_tokens=min_range)
+    wl, dw = with_ranges(lens, 8, 2, d, kv_dtype, seed=12, max_blocks_per_seq=41, min_range=min_range)
     dw.out.fill_(float("nan"))
     got = dw.attend().clone()
     torch.cuda.synchronize()
@@ -142,16 +157,16 @@ def test_whole_and_cut_sequences_in_one_launch(sd, kv_dtype, d, min_range):
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", [(8, 2, 128, "bf16"), (16, 1, 64, "bf16"), (8, 2, 128, "fp8"), (40, 2, 128, "bf16"), (8, 2, 64, "fp8")])
-@pytest.mark.parametrize("min_range", [0, 128, 256, 384, 640])
+@pytest.mark.parametrize("min_range", [0, ONE_TILE, 128, 256, 384, 640])
 def test_parts_handed_over_inside_a_workgroup(sd, Hq, Hkv, d, kv_dtype, min_range):
     """The four waves of a workgroup walk neighbouring ranges and hand their parts of one sequence to the first of
     them through LDS.  Sequences of 1 .. 64 tiles against ranges of 1, 4, 8, 12 and 20 tiles put the sequence borders
     at every position of a workgroup's four ranges: runs that hold a whole sequence (written directly), runs that leave one
-    part, runs that end because the next range holds a border, sequences spread over several workgroups."""
+    part, runs that end because the next range holds a border, sequences spread over several workgroups.  (With 0 some of
+    the pools take the sequences whole.)"""
     import torch
     lens = [32 * k - (k % 3) for k in (1, 2, 3, 4, 5, 7, 8, 9, 12, 13, 16, 17, 23, 29, 31, 40, 47, 64)] + [1, 33, 0, 449, 97, 225, 31, 161]
-    wl = workloads.make_custom(lens, Hq, Hkv, d, kv_dtype, seed=77 + min_range + d)
-    dw = device_workload(wl, chunk_tokens=min_range)
+    wl, dw = with_ranges(lens, Hq, Hkv, d, kv_dtype, seed=77 + max(min_range, 0) + d, min_range=min_range)
     dw.out.fill_(float("nan"))
     got = dw.attend().clone()
     torch.cuda.synchronize()
@@ -263,18 +278,19 @@ def test_constant_v_returns_the_constant(sd):
     assert np.abs(got - workloads.bf16_bits_to_f32(np.uint16([c]))[0]).max() <= 1e-6
 
 
-@pytest.mark.parametrize("min_range", [0, 4096])
+@pytest.mark.parametrize("min_range", [0, ONE_TILE, 4096])
 def test_fp8_constant_v_returns_the_constant(sd, min_range):
     """fp8 pools: pages with different (power-of-two) V scales whose codes all decode to 0.5.  The weight sum runs
-    over the rounded weights the product uses, so the constant comes back to fp32 rounding; both with sequences cut
-    across waves and with one workgroup per sequence."""
-    wl = workloads.make_custom([1, 5, 33, 200, 1300], 8, 2, 128, "fp8", seed=11, poison=False)
+    over the rounded weights the product uses, so the constant comes back to fp32 rounding; with the longest sequence
+    cut by the library's rule, with every sequence cut across waves, and with one workgroup per sequence."""
+    wl, dw = with_ranges([1, 5, 33, 200, 1300], 8, 2, 128, "fp8", seed=11, poison=False, min_range=min_range)
     codes = {0.25: 0x40, 0.5: 0x38, 2.0: 0x28}      # 2.0, 1.0, 0.25 in e4m3fn: code value x scale = 0.5
     for p in range(wl.num_pages):
         s = (0.25, 0.5, 2.0)[p % 3]
         wl.v_scales[p, :] = np.float32(s)
         wl.v_pages[p] = codes[s]
-    got = gpu_attend(wl, chunk_tokens=min_range)
+    dw.set_pool(wl.k_pages, wl.v_pages, wl.k_scales, wl.v_scales)
+    got = dw.attend().cpu().numpy()
     assert np.abs(got - 0.5).max() <= 1e-6
 
 
@@ -335,16 +351,16 @@ def test_kv_append_is_bit_exact_and_append_then_attend_matches(sd):
 
 
 @pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (28, 4, 128), (8, 1, 64), (32, 1, 128)])
-@pytest.mark.parametrize("min_range", [0, 256, 4096])
+@pytest.mark.parametrize("min_range", [0, ONE_TILE, 256, 4096])
 def test_append_and_attend_in_one_call(sd, Hq, Hkv, d, min_range):
     """paged_decode_attention_append = kv_append of every sequence's newest token + attention over it: pool bytes equal
     the oracle's append bit for bit, the output matches the oracle run over the appended pool.  Lengths put the
     newest token first in its page, last in its page, alone in the sequence, first of a new tile; one sequence is
-    empty.  Ranges of 4096 tokens cover every sequence, which takes the single-pass path."""
+    empty.  Ranges of 4096 tokens cover every sequence, which takes the single-pass path; so does 0, but for the longest
+    sequence over pools with 128-wide heads."""
     import torch
     lens = [1, 2, 16, 17, 32, 33, 34, 0, 64, 65, 513, 700, 1025, 1]
-    wl = workloads.make_custom(lens, Hq, Hkv, d, seed=500 + Hq + d, append=True)
-    dw = device_workload(wl, chunk_tokens=min_range)
+    wl, dw = with_ranges(lens, Hq, Hkv, d, seed=500 + Hq + d, append=True, min_range=min_range)
     dw.out.fill_(float("nan"))
     out = dw.append_and_attend()
     torch.cuda.synchronize()
@@ -364,6 +380,25 @@ def test_append_and_attend_in_one_call(sd, Hq, Hkv, d, min_range):
     # and the pool now serves the plain call with the same result up to rounding order
     plain = dw.attend().cpu().numpy()
     assert np.abs(got - plain).max() <= ALARM_ABS + ALARM_REL * np.abs(plain).max()
+
+
+@pytest.mark.parametrize("longest,whole", [(700, False), (128, True)])
+def test_append_and_attend_above_the_range_pass_s_limit(sd, longest, whole):
+    """4097 sequences: with one that is longer than the chunk the rows go into the pool ahead of the chunked passes; otherwise the
+    workgroup of a sequence takes its row as in smaller batches."""
+    import torch
+    lens = [int(x) for x in np.random.default_rng(10).integers(0, 90, size=4097)]
+    lens[17] = longest
+    wl = workloads.make_custom(lens, 4, 2, 64, seed=91, append=True)
+    dw = device_workload(wl, chunk_tokens=128)
+    assert (wl.max_context_len <= 128) == whole
+    out = dw.append_and_attend()
+    torch.cuda.synchronize()
+    k_ref, v_ref = wl.k_pages.copy(), wl.v_pages.copy()
+    oracle.kv_append(wl.k_new, wl.v_new, wl.seq_ids, wl.positions, k_ref, v_ref, wl.block_table)
+    k_gpu, v_gpu = dw.pools_to_host()
+    assert np.array_equal(k_gpu, k_ref) and np.array_equal(v_gpu, v_ref)
+    check(out.cpu().numpy(), oracle_full(wl, k_ref, v_ref))
 
 
 def test_append_and_attend_rejects_fp8_pools(sd):
@@ -564,13 +599,13 @@ def test_fp8_poison_is_never_read(sd):
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(8, 1), (8, 2), (64, 8), (28, 4), (16, 1), (40, 2), (1, 1)])
-@pytest.mark.parametrize("min_range", [0, 128, 4096])
+@pytest.mark.parametrize("min_range", [0, ONE_TILE, 128, 4096])
 def test_fp8_head_dim_64(sd, Hq, Hkv, min_range):
     """fp8 pools with 64-wide heads: the range pass (ranges of one tile and of 128 tokens) and the
     workgroup-per-sequence kernel (ranges that cover every sequence), on lengths around page and tile edges."""
     lens = [1, 2, 15, 16, 17, 31, 32, 33, 64, 65, 127, 129, 300, 511, 512, 513, 1025, 2049, 0]
-    wl = workloads.make_custom(lens, Hq, Hkv, 64, "fp8", seed=340 + Hq)
-    check_fp8(gpu_attend(wl, chunk_tokens=min_range), oracle_full(wl))
+    wl, dw = with_ranges(lens, Hq, Hkv, 64, "fp8", seed=340 + Hq, min_range=min_range)
+    check_fp8(dw.attend().cpu().numpy(), oracle_full(wl))
 
 
 def test_fp8_head_dim_64_every_code_decodes_exactly_on_the_device(sd):
