@@ -2,9 +2,9 @@
 
 A kernel whose tile registers end up in scratch memory, or that no longer fits two waves per SIMD,
 still computes the right thing and silently loses half its bandwidth, so the resource remarks of
-the compiler are checked: the decode kernels (range pass, its probe, split pass) and the 8-wave
-causal kernel use no scratch memory and spill no vector registers, and keep at least two waves
-per SIMD.
+the compiler are checked: the decode kernels (range pass, its probe, split pass, merge of the ranges) and the
+causal kernels (the general one, the one in two phases, the one that loads straight into LDS; every instance of
+them) use no scratch memory and spill no vector registers, and keep at least two waves per SIMD.
 """
 import os
 import re
@@ -37,8 +37,9 @@ def resource_remarks(source, tmp_path):
 
 
 @pytest.mark.skipif(shutil.which(sd_build.HIPCC) is None and not os.path.exists(sd_build.HIPCC), reason="needs hipcc")
-@pytest.mark.parametrize("source,kernels,least", [("attn_range.hip", "range_kernel", 3), ("attn_split.hip", "split_kernel", 3),
-                                                   ("attn_prefill.hip", "prefill_wide_kernel", 1)])
+@pytest.mark.parametrize("source,kernels,least", [("attn_range.hip", "range_kernel", 8), ("attn_range.hip", "range_merge_kernel", 6),
+                                                   ("attn_split.hip", "split_kernel", 10), ("attn_prefill.hip", "prefill_wide_kernel", 15),
+                                                   ("attn_prefill.hip", "prefill_pingpong_kernel", 1), ("attn_prefill.hip", "prefill_direct_kernel", 1)])
 def test_decode_kernels_keep_their_tiles_in_registers(source, kernels, least, tmp_path):
     remarks = {k: v for k, v in resource_remarks(source, tmp_path).items() if kernels in k}
     assert len(remarks) >= least, list(remarks)
