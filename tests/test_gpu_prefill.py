@@ -9,6 +9,7 @@ import oracle
 import workloads
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 from tests.test_gpu_parity import check as check_decode, check_fp8, device_workload, sd  # noqa: F401  (sd is a fixture)
+from tests.test_prefill_geometry import PLANS, block_case, plan, program, stretch_case  # noqa: F401  (program is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -24,8 +25,8 @@ def check(got, ref, kv_dtype="bf16"):
         check_decode(got, ref, alarm_scale=2.0)
 
 
-def make(lens, nq, Hq, Hkv, d, kv_dtype="bf16", seed=0):
-    wl = workloads.make_custom(lens, Hq, Hkv, d, kv_dtype, seed=seed)
+def make(lens, nq, Hq, Hkv, d, kv_dtype="bf16", seed=0, **kw):
+    wl = workloads.make_custom(lens, Hq, Hkv, d, kv_dtype, seed=seed, **kw)
     rng = np.random.default_rng(seed + 1)
     q_start = np.concatenate([[0], np.cumsum(nq)]).astype(np.int32)
     q = f32_to_bf16_bits(rng.standard_normal((int(q_start[-1]), Hq, d)).astype(np.float32))
@@ -66,6 +67,28 @@ def test_negative_and_zero_scale(sd, scale, kv_dtype):
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
 
 
+def stretch(kv_dtype, d, plan, seed, **kw):
+    """A call that takes the plan, and which of its sequences to hold against the oracle (all but those of the large batches that repeat)."""
+    lens, nq, Hq, Hkv = stretch_case(plan, d)
+    return (*make(lens, nq, Hq, Hkv, d, kv_dtype, seed=seed, **kw), lens, min(len(lens), 4) if len(lens) > 9 else len(lens))
+
+
+def check_first(wl, q, q_start, seqs, kv_dtype, got=None):
+    """The rows of the first `seqs` sequences against the oracle, which is given nothing else."""
+    got = gpu(wl, q, q_start) if got is None else got
+    rows = q_start[seqs]
+    want = oracle.paged_prefill_attention(q[:rows], q_start[:seqs + 1], wl.k_pages, wl.v_pages, wl.block_table[:seqs], wl.context_lens[:seqs],
+                                          wl.scale, wl.k_scales, wl.v_scales, wl.kv_dtype)
+    check(got[:rows], want, kv_dtype)
+
+
+@pytest.mark.parametrize("kv_dtype,d,plan", PLANS)
+@pytest.mark.parametrize("scale", [-0.11, 0.0])
+def test_negative_and_zero_scale_in_every_kernel(sd, scale, kv_dtype, d, plan):
+    wl, q, q_start, _, seqs = stretch(kv_dtype, d, plan, 63, scale=scale)
+    check_first(wl, q, q_start, seqs, kv_dtype)
+
+
 def test_one_query_per_sequence_equals_the_decode_step(sd):
     import torch
     lens = [1, 15, 16, 17, 200, 513, 1500]
@@ -99,6 +122,17 @@ def test_constant_v_returns_the_constant(sd, kv_dtype, d):
         want = 0.25
     got = gpu(wl, q, q_start)
     assert np.abs(got - want).max() <= 2e-6 * abs(want) + 1e-7
+
+
+@pytest.mark.parametrize("kv_dtype,d,plan", PLANS)
+def test_constant_v_returns_the_constant_in_every_kernel(sd, kv_dtype, d, plan):
+    wl, q, q_start, _, _ = stretch(kv_dtype, d, plan, 52)
+    if kv_dtype == "bf16":
+        wl.v_pages[...] = 0x3ec0          # 0.375
+    else:
+        wl.v_pages[...] = 0x3c            # e4m3fn 1.5
+        wl.v_scales[...] = np.float32(0.25)
+    assert np.abs(gpu(wl, q, q_start) - 0.375).max() <= 2e-6
 
 
 def test_sequences_without_queries_with_too_many_and_empty(sd):
@@ -146,17 +180,8 @@ def test_long_stretch_at_a_rollout_shape(sd):
         check(got[r:r + 1], one)
 
 
-@pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("bf16", 64), ("fp8", 128), ("fp8", 64)])
-@pytest.mark.parametrize("shape", ["ramp", "jumps", "decay"])
-def test_scores_that_outgrow_the_running_reference(sd, shape, d, kv_dtype):
-    """Keys whose size depends on the position, so that a row's largest score moves all along the
-    range: steadily (ramp: the exponent's reference has to follow many times), in rare leaps far
-    beyond anything seen before (jumps: weights of earlier tokens underflow at once), or not at
-    all after the first tiles (decay: the reference stays where the first tile put it).  bf16 pools:
-    every K row is scaled; fp8 pools: every page's K scale (a page's tokens grow together)."""
-    lens, nq = [1500, 777, 96], [400, 777, 96]
-    wl, q, q_start = make(lens, nq, 8, 2, d, kv_dtype, seed=900 + d)
-
+def grow(wl, lens, shape, kv_dtype):
+    """Scales the keys of a workload by a factor of their position."""
     def factor(t):
         if shape == "ramp":
             return 1.0 + 0.03 * t
@@ -174,7 +199,29 @@ def test_scores_that_outgrow_the_running_reference(sd, shape, d, kv_dtype):
         for b, L in enumerate(lens):
             first = np.arange(0, L, 16)
             wl.k_scales[wl.block_table[b, first // 16], :] *= factor(first + 15)[:, None].astype(np.float32)
+
+
+@pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("bf16", 64), ("fp8", 128), ("fp8", 64)])
+@pytest.mark.parametrize("shape", ["ramp", "jumps", "decay"])
+def test_scores_that_outgrow_the_running_reference(sd, shape, d, kv_dtype):
+    """Keys whose size depends on the position, so that a row's largest score moves all along the
+    range: steadily (ramp: the exponent's reference has to follow many times), in rare leaps far
+    beyond anything seen before (jumps: weights of earlier tokens underflow at once), or not at
+    all after the first tiles (decay: the reference stays where the first tile put it).  bf16 pools:
+    every K row is scaled; fp8 pools: every page's K scale (a page's tokens grow together)."""
+    lens, nq = [1500, 777, 96], [400, 777, 96]
+    wl, q, q_start = make(lens, nq, 8, 2, d, kv_dtype, seed=900 + d)
+    grow(wl, lens, shape, kv_dtype)
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
+
+
+@pytest.mark.parametrize("kv_dtype,d,plan", PLANS)
+@pytest.mark.parametrize("shape", ["ramp", "jumps", "decay"])
+def test_scores_that_outgrow_the_running_reference_in_every_kernel(sd, shape, kv_dtype, d, plan):
+    """The same in every way a call can be cut: the kernels keep references of their own, and the parts of a split range meet with theirs."""
+    wl, q, q_start, lens, seqs = stretch(kv_dtype, d, plan, 950 + d)
+    grow(wl, lens, shape, kv_dtype)
+    check_first(wl, q, q_start, seqs, kv_dtype)
 
 
 @pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("bf16", 64), ("fp8", 128), ("fp8", 64)])
@@ -182,7 +229,6 @@ def test_scores_that_outgrow_the_running_reference(sd, shape, d, kv_dtype):
 def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
     """Each size of a workgroup's row block (the small ones split the range over the waves) at its edges; one sequence's fp8
     scales include a V scale of 0 and a negative one, which are turned into codes when a page is parked."""
-    from tests.test_prefill_geometry import block_case
     lens, nq, Hq, Hkv = block_case(blocks, d)
     wl, q, q_start = make(lens, nq, Hq, Hkv, d, kv_dtype, seed=300 + blocks + d)
     if kv_dtype == "fp8":
@@ -197,7 +243,6 @@ def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
 def test_fp8_value_scales_far_apart(sd, blocks, d):
     """V scales of any size side by side in a row: pages whose values are next to nothing keep their share of the weights (2^-124 times
     a weight is no normal bf16 number any more, 2^-149 not even an fp32 one), and values of 2^100 drown the rest without harm."""
-    from tests.test_prefill_geometry import block_case
     lens, nq, Hq, Hkv = block_case(blocks, d)
     wl, q, q_start = make(lens, nq, Hq, Hkv, d, "fp8", seed=350 + blocks + d)
     small = np.float32([1, 2.0 ** -124, 1e-39, 1, -(2.0 ** -120), 2.0 ** -149, 1e-30])
@@ -213,16 +258,18 @@ def test_fp8_value_scales_far_apart(sd, blocks, d):
     check(got, want, "fp8")
 
 
-@pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("blocks", [16, 2])
-def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, blocks, d):
+@pytest.mark.parametrize("blocks,d,L,want", [
+    (16, 128, 300, (16, 1, 0)), (16, 128, 600, (16, 1, 1)), (2, 128, 1100, (2, 8, 0)),   # short contexts, two phases, split ranges
+    (16, 64, 300, (16, 1, 0)), (2, 64, 1100, (2, 8, 0)),
+])
+def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, program, blocks, d, L, want):
     """K and V rows of the last 20 tokens are NaN and infinite: rows that end 64 tokens (a tile and a wave's rows) before them
     do not change.  Many sequences of one length, so that waves past their own rows still ride along with their workgroup."""
     B, Hq, Hkv = (40, 16, 8) if blocks == 16 else (1, 8, 4)
     if d == 64 and blocks == 16:
         B, Hq, Hkv = 64, 32, 32
-    L = 300 if blocks == 16 else 1100
     lens, nq = [L] * B, [150] * B
+    assert plan(program, lens, nq, Hq, Hkv, d) == want
     wl, q, q_start = make(lens, nq, Hq, Hkv, d, seed=77)
     want = gpu(wl, q, q_start)
     for b in range(B):

@@ -75,6 +75,27 @@ def block_case(blocks, d):
     return lens, [min(n, L) for n, L in zip(q, lens)], Hq, Hkv
 
 
+def stretch_case(plan, d):
+    """(lens, queries, Hq, Hkv): sequences of 1500, 777 and 96 tokens, or many of 600, that take the plan (blocks, split, phases)."""
+    long, many = [1500, 777, 96], [600] * 22 + [33, 511]
+    return {
+        (128, (16, 1, 1)): (long, [400, 400, 96], 64, 8),          # two phases
+        (128, (16, 1, 0)): (many, [20] * 24, 32, 16),              # one phase: few queries per sequence
+        (128, (8, 2, 0)): (long, [600, 777, 96], 16, 8),
+        (128, (8, 1, 0)): ([511, 300, 96], [400, 300, 96], 16, 8),   # short contexts over fp8 pools
+        (128, (4, 4, 0)): (long, [400, 200, 96], 16, 8),
+        (128, (2, 8, 0)): (long, [100, 77, 96], 8, 2),
+        (64, (16, 1, 0)): ([700, 450, 320, 129] * 16, [128] * 64, 64, 32),
+        (64, (8, 1, 0)): (long * 3, [400, 400, 96] * 3, 16, 8),
+        (64, (4, 4, 0)): (long, [400, 777, 96], 16, 8),
+        (64, (2, 8, 0)): (long, [100, 77, 96], 8, 2),
+    }[d, plan]
+
+
+PLANS = [("bf16", 128, (16, 1, 1))] + [(kv, 128, p) for kv in ("bf16", "fp8") for p in ((16, 1, 0), (8, 2, 0), (4, 4, 0), (2, 8, 0))] + \
+    [("fp8", 128, (8, 1, 0)), ("bf16", 64, (16, 1, 0))] + [(kv, 64, p) for kv in ("bf16", "fp8") for p in ((8, 1, 0), (4, 4, 0), (2, 8, 0))]
+
+
 def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None):
     """(column blocks of a workgroup, waves that share a block's range, two phases) of a call."""
     G = Hq // Hkv
@@ -87,6 +108,11 @@ def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None):
 @pytest.mark.parametrize("blocks", [16, 8, 4, 2])
 def test_the_block_cases_are_what_they_say(program, blocks, d):
     assert plan(program, *block_case(blocks, d), d)[0] == blocks
+
+
+@pytest.mark.parametrize("kv_dtype,d,want", PLANS)
+def test_the_stretch_cases_are_what_they_say(program, kv_dtype, d, want):
+    assert plan(program, *stretch_case(want, d), d, kv_dtype) == want
 
 
 def test_two_phases_only_where_most_waves_have_rows(program):
