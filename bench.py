@@ -159,6 +159,18 @@ def cpu_baseline(cfg, wall_target=10.0):
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 peak
 
 
+def calibration_copy(device):
+    """1 GiB read + 1 GiB written by a plain device-to-device copy, three times: the byte counters of a
+    profiler run are scaled by what they report for this known transfer."""
+    import torch
+
+    src_t = torch.empty(1 << 28, dtype=torch.int32, device=device).fill_(1)
+    dst_t = torch.empty_like(src_t)
+    for _ in range(3):
+        dst_t.copy_(src_t)
+    torch.cuda.synchronize()
+
+
 def prefill_main(args):
     """--prefill: the causal multi-query pass (paged_prefill_attention) at a resume shape: every
     sequence re-computes attention for the last `nq` of its L stored tokens.  One step = one call.
@@ -200,6 +212,8 @@ def prefill_main(args):
         call(timer)
     torch.cuda.synchronize()
     kernel_ms = float(np.mean(timer.read()[0]))
+    if args.copy_calibration:
+        calibration_copy(dw.device)
     pairs = B * Hq * sum(L - nq + i + 1 for i in range(nq))
     flops = 4.0 * d * pairs
     rec = {
@@ -433,14 +447,7 @@ def run_config(cfg, args):
                  "what": "the range pass's own walk (same grid, ranges and loads) with the arithmetic taken out"}
 
     if args.copy_calibration:
-        # 1 GiB read + 1 GiB written by a plain device-to-device copy: the byte counters of a
-        # profiler run are scaled by what they report for this known transfer
-        src_t = torch.empty(1 << 28, dtype=torch.int32, device=dw.device).fill_(1)
-        dst_t = torch.empty_like(src_t)
-        for _ in range(3):
-            dst_t.copy_(src_t)
-        torch.cuda.synchronize()
-        del src_t, dst_t
+        calibration_copy(dw.device)
 
     value = sb["step"] / (ms_per_step * 1e-3) / 1e9
     # MFMA flops the main kernel issues: QK^T and PV on 16-row tiles, 2 * 16 * d * 2 flops per token and KV head;

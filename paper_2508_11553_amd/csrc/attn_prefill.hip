@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
 // one wave of a SIMD issues matrix instructions the other does its exponentials.  Tiles are asked for four ahead, into one of
 // six slots: a slot is read last (V, by the late waves) two tiles after it was due, and filled again from then on.
 //
-// What bounds it (16 x 8192 / 2048 queries, 32/8 heads: 3.45 -> 3.22 ms on one machine, 1.2 PFLOP/s): the matrix pipe is busy 57 % of the
+// What bounds it (16 x 8192 / 2048 queries, 32/8 heads: 3.45 -> 3.22 ms on one machine, 1.2 PFLOP/s): the matrix pipe is busy 55 % of the
 // time; without the loads into LDS the kernel takes 0.88 of its time, without any operand reads 0.9, without the exponentials 0.99, with
 // matrix instructions and barriers alone 0.70.  Operand reads and loads moved between the two phases, and more of
 // them beside the matrix instructions, gave 3.25 - 3.35 ms.

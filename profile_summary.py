@@ -25,7 +25,9 @@ COPY_KIB = float(1 << 20)
 KERNEL_SOURCES = {
     "range_kernel": ("attn_range.hip", "attn_tile.h", "kernels.h"),
     "split_kernel": ("attn_split.hip", "attn_tile.h", "kernels.h"),
-    "prefill_kernel": ("attn_prefill.hip", "attn_tile.h", "kernels.h"),
+    "prefill_pingpong_kernel": ("attn_prefill.hip", "attn_tile.h", "kernels.h"),
+    "prefill_direct_kernel": ("attn_prefill.hip", "attn_tile.h", "kernels.h"),
+    "prefill_wide_kernel": ("attn_prefill.hip", "attn_tile.h", "kernels.h"),
 }
 
 
@@ -70,6 +72,9 @@ def main():
     ap.add_argument("--fetch", required=True)
     ap.add_argument("--write", required=True)
     ap.add_argument("--mfma", default=None, help="optional fourth run: --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES")
+    ap.add_argument("--sq", action="append", default=[], metavar="DIR:COUNTER,COUNTER,...",
+                    help="a further counter run of the main kernel (repeatable): its directory and the counters it collected")
+    ap.add_argument("--flops", type=float, default=None, help="flops of one launch of the main kernel, for its rate")
     ap.add_argument("--bench-args", required=True,
                     help="the arguments bench.py was given in the kernel-trace run, --config N included (for the header)")
     ap.add_argument("--pmc-bench-args", required=True, help="the arguments of the counter runs")
@@ -83,9 +88,13 @@ def main():
     if a.mfma:
         print(f"    rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES --output-format csv -d {a.mfma} -o run -- "
               f"python3 bench.py {a.pmc_bench_args}")
+    sq = [(d, names.split(",")) for d, names in (x.split(":") for x in a.sq)]
+    for d, names in sq:
+        print(f"    rocprofv3 --pmc {' '.join(names)} --output-format csv -d {d} -o run -- python3 bench.py {a.pmc_bench_args}")
     print(f"    python profile_summary.py --workload '{a.workload}' --kernel {a.kernel} --bench-args='{a.bench_args}' "
           f"--pmc-bench-args='{a.pmc_bench_args}' --kernel-trace {a.kernel_trace} "
-          f"--fetch {a.fetch} --write {a.write}" + (f" --mfma {a.mfma}" if a.mfma else "") + "\n")
+          f"--fetch {a.fetch} --write {a.write}" + (f" --mfma {a.mfma}" if a.mfma else "")
+          + "".join(f" --sq {x}" for x in a.sq) + (f" --flops {a.flops:.6g}" if a.flops else "") + "\n")
 
     print("## Kernel durations (--kernel-trace --stats)\n")
     print("| kernel | calls | avg us | min us | max us | % of GPU time |")
@@ -97,6 +106,10 @@ def main():
                 name = name[:67] + "..."
             print(f"| `{name}` | {r['Calls']} | {float(r['AverageNs']) / 1e3:.2f} | {float(r['MinNs']) / 1e3:.2f} | "
                   f"{float(r['MaxNs']) / 1e3:.2f} | {float(r['Percentage']):.2f} |")
+            if a.flops and a.kernel in r["Name"]:
+                rate = f"{a.flops:.4e} flops per launch: {a.flops / float(r['AverageNs']) / 1e3:.0f} TFLOP/s on average, {a.flops / float(r['MinNs']) / 1e3:.0f} at best"
+    if a.flops:
+        print("\n" + rate + ".")
 
     fetch, write = counters(a.fetch, "FETCH_SIZE"), counters(a.write, "WRITE_SIZE")
     ff, fvals = calibration(fetch)
@@ -127,6 +140,29 @@ def main():
             bz, cz = statistics.mean(busy[name]), statistics.mean(cu[name])
             short = name if len(name) <= 70 else name[:67] + "..."
             print(f"| `{short}` | {bz:.3g} | {cz:.3g} | {100.0 * bz / (4.0 * cz):.1f} |")
+    if sq:
+        print("\n## Further counters of the main kernel (--pmc, sums over the chip, averages over its dispatches)\n")
+        v = {}
+        for d, names in sq:
+            for n in names:
+                v[n] = statistics.mean(x for k, xs in counters(d, n).items() if a.kernel in k for x in xs)
+        print("| counter | value | reading |")
+        print("|---|---|---|")
+        simd, cu = 4 * v.get("SQ_BUSY_CU_CYCLES", 0), v.get("SQ_BUSY_CU_CYCLES", 0)
+        mfma, wave = v.get("SQ_INSTS_MFMA", 0), v.get("SQ_WAVE_CYCLES", 0)
+        reading = {
+            "SQ_BUSY_CU_CYCLES": lambda x: f"x 4 SIMDs = {4 * x:.4g} SIMD cycles",
+            "SQ_VALU_MFMA_BUSY_CYCLES": lambda x: simd and f"matrix pipe busy {100 * x / simd:.1f} % of SIMD cycles",
+            "SQ_VALU_MFMA_COEXEC_CYCLES": lambda x: simd and f"matrix pipe and vector ALU busy together {100 * x / simd:.1f} % of SIMD cycles",
+            "SQ_ACTIVE_INST_VALU": lambda x: simd and f"x 4 = {400 * x / simd:.1f} % of SIMD cycles (MFMA issue included)",
+            "SQ_LDS_IDX_ACTIVE": lambda x: cu and f"LDS busy {100 * x / cu:.1f} % of CU cycles",
+            "SQ_INSTS_VALU": lambda x: mfma and f"{x / mfma - 1:.2f} other vector instructions per MFMA",
+            "SQ_INSTS_VALU_TRANS_F32": lambda x: mfma and f"{x / mfma:.2f} per MFMA",
+            "SQ_INSTS_LDS": lambda x: mfma and f"{x / mfma:.2f} per MFMA",
+            "SQ_WAIT_INST_ANY": lambda x: wave and f"a wave waits to issue {100 * x / wave:.0f} % of its life",
+        }
+        for n, x in v.items():
+            print(f"| {n} | {x:.4g} | {reading.get(n, lambda _: '')(x) or ''} |")
     print()
     tag = source_hash(a.kernel)
     for name, t in total.items():
