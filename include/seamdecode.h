@@ -71,7 +71,9 @@ typedef struct {
     int32_t max_blocks_per_seq; /* row stride of block_table */
     int32_t kv_dtype;           /* SD_BF16 or SD_FP8_E4M3 */
     int32_t max_context_len;    /* host-known upper bound on context_lens[]; lengths above it
-                                   are treated as max_context_len; <= 16 * max_blocks_per_seq */
+                                   are treated as max_context_len; <= 16 * max_blocks_per_seq.
+                                   Kernels and block sizes are chosen by it: the longest length
+                                   of the step serves better than the table's capacity */
     int32_t chunk_tokens;       /* split-K chunk in tokens: 0 = library default, else a
                                    multiple of 128 in [128, 65536] */
 } sd_shape;
@@ -203,10 +205,11 @@ int kv_copy_pages(const sd_shape *shape, const int32_t *src_pages, const int32_t
  * head) and all waves carry the same load whatever the mix of lengths.  A wave
  * that holds a whole sequence writes its `out` rows itself; of a sequence cut
  * across ranges each wave leaves (max, sum, weighted sum) in `workspace`.  Merge
- * pass: combines the parts of every cut sequence in range order (results are
+ * pass: combines the parts of every cut sequence in a fixed order (results are
  * reproducible bit for bit).  shape->chunk_tokens, when non-zero, is the least
- * number of tokens a range holds.  Batches of short sequences run one kernel, a
- * workgroup per (sequence, KV head).  Larger batches take the chunked passes of
+ * number of tokens a range holds.  Where max_context_len is short (1024 to 1600
+ * tokens, by pool type) or fits one chunk, one kernel runs, a workgroup per
+ * (sequence, KV head).  Larger batches take the chunked passes of
  * paged_decode_attention_prefix.  Results do not depend on the physical
  * placement of pages.
  *
