@@ -96,29 +96,33 @@ struct PrefillPlan {
 //                  4   1.41     1.33       1.46       0.92       0.98       0.79       0.81       0.54
 // Contexts of 2048 tokens and more, whose last workgroup runs longer, move the lines up again.  At head_dim 64 blocks of 16 are
 // for bf16 pools (over fp8 pools they take 1.1 to 1.2 of the time of 8 from 256 workgroups on).
+// The grid has room for max_q_len queries of every sequence, and workgroups that find none cost their start: 55 sequences of up to 45 queries under a
+// bound of 1302, 4/1 heads 14.6 / 20.8 / 27.5 / 37.8 us with 16 / 8 / 4 / 2 blocks (1155, 2255, 4510 and 8965 workgroups).  No smaller blocks than
+// a grid of 4096 allows.
 // The two phases leave the matrix pipe to the waves in turn, also to those without rows: by the share of the 16 blocks that the average
 // sequence's queries fill, time against one phase: up to 0.1 1.27, 0.2 1.22, 0.3 1.14, 0.5 1.04, 0.8 to 1 0.97, above 4 0.95.
 constexpr int kPrefillShort = 512;
-__host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t total_q, int batch, int heads, int units, int max_context_len)
+__host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)
 {
     const auto filled = [&](int blocks, int of) { return total_q * of >= (int64_t)blocks * units * batch; };   // a block's share of 1 / of, on average
     const auto workgroups = [&](int blocks) {   // about: a sequence's last one is half full
         const int64_t n = total_q / (blocks * units) + batch / 2;
         return (n > batch ? n : batch) * heads;
     };
+    const auto small_grid = [&](int blocks) { return (int64_t)((max_q_len + blocks * units - 1) / (blocks * units)) * batch * heads <= 4096; };
     const bool deep = max_context_len >= 2048;
     if (head_dim == 64) {
         if (kv_dtype == 0 && workgroups(16) >= 2048 && filled(16, 2)) return PrefillPlan{16, 1, false};
-        if (max_context_len < kPrefillShort || workgroups(8) >= (deep ? 512 : 256)) return PrefillPlan{8, 1, false};
-        return workgroups(4) >= (max_context_len >= 4096 ? 384 : deep ? 256 : 128) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+        if (max_context_len < kPrefillShort || workgroups(8) >= (deep ? 512 : 256) || !small_grid(4)) return PrefillPlan{8, 1, false};
+        return workgroups(4) >= (max_context_len >= 4096 ? 384 : deep ? 256 : 128) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }
     if (max_context_len < kPrefillShort) return kv_dtype == 0 ? PrefillPlan{16, 1, false} : PrefillPlan{8, 1, false};
     // (for 8 blocks the cost over all calls is flat between 128 and 192; 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads have 228: 98 : 91 us with 4)
     const auto enough = [&](int blocks) { return workgroups(blocks) * 4 >= (blocks == 8 || !filled(blocks, 2) ? 192 : 128) * (deep ? 5 : 4); };
-    if (enough(16)) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
-    if (enough(8)) return PrefillPlan{8, 2, false};
+    if (enough(16) || !small_grid(8)) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+    if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
     // (10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads: 4 blocks 19, 2 blocks 23 us)
-    return enough(4) || max_context_len < 1024 ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+    return enough(4) || max_context_len < 1024 || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens

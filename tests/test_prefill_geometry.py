@@ -15,7 +15,7 @@ PROGRAM = r"""
 int main(int argc, char **argv)
 {
     if (argc > 3) {
-        const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
+        const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[8]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
         printf("%d %d %d\n", p.blocks, p.split, p.phases);
         return 0;
     }
@@ -96,10 +96,10 @@ PLANS = [("bf16", 128, (16, 1, 1))] + [(kv, 128, p) for kv in ("bf16", "fp8") fo
     [("fp8", 128, (8, 1, 0)), ("bf16", 64, (16, 1, 0))] + [(kv, 64, p) for kv in ("bf16", "fp8") for p in ((8, 1, 0), (4, 4, 0), (2, 8, 0))]
 
 
-def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None):
+def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
     """(column blocks of a workgroup, waves that share a block's range, two phases) of a call."""
     G = Hq // Hkv
-    args = (d, sum(q), len(lens), Hkv * ((G + 15) // 16), 16 // G if G <= 8 else 1, bound or max(lens), int(kv_dtype == "fp8"))
+    args = (d, sum(q), len(lens), Hkv * ((G + 15) // 16), 16 // G if G <= 8 else 1, bound or max(lens), int(kv_dtype == "fp8"), max_q or max(q))
     got = subprocess.run([program] + [str(x) for x in args], capture_output=True, text=True, check=True)
     return tuple(int(x) for x in got.stdout.split())
 
@@ -130,3 +130,11 @@ def test_16_blocks_at_head_dim_64_are_for_bf16_pools_and_full_workgroups(program
     assert plan(program, [1500] * 50, [280] * 50, 128, 4, 64, "fp8") == (8, 1, 0)
     assert plan(program, [92] * 61, [15] * 61, 32, 32, 64) == (8, 1, 0)
     assert plan(program, [3000] * 8, [3000] * 8, 32, 8, 64) == (16, 1, 0)
+
+
+def test_a_loose_bound_on_the_queries_keeps_the_grid_small(program):
+    lens, q = [76] * 55, [23] * 54 + [45]
+    assert plan(program, lens, q, 4, 1, 128, bound=548) == (4, 4, 0)
+    assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=sum(q)) == (8, 2, 0)
+    assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=20 * sum(q))[0] == 16
+    assert plan(program, [2000] * 8, [100] * 8, 16, 4, 64, max_q=20000)[0] == 8
