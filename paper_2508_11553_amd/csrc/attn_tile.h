@@ -649,16 +649,19 @@ struct Bf16Path {
 
 // A page's V scale in two factors: `fold`, which the weights carry, and a power of two that the codes take as they are converted (1 for
 // any ordinary scale).  Weights have fp32's exponent range only as long as the pages of a row lie less than that apart, so
-// fold is kept within [2^-40, 2^40); the codes' bf16 form has room for the rest and stays exact.  A scale of 0 counts as 1 (its codes are zeroed).
+// fold is kept within [2^-40, 2^40) (down to 2^-62 for subnormal scales); the codes' bf16 form has room for the rest and stays exact.  A scale
+// of 0 counts as 1 (its codes are zeroed).  Integer arithmetic on the wave-uniform scale: the scalar unit does it.
 struct ValueScale {
     float fold, power;
 };
 SD_DEV ValueScale value_scale(float vs)
 {
-    const float v = vs != 0.f ? __builtin_fabsf(vs) : 1.0f;
-    const int e = __builtin_amdgcn_frexp_expf(v);   // v = m * 2^e, m in [0.5, 1)
-    const int out = e - max(-39, min(e, 40));
-    return ValueScale{__builtin_ldexpf(v, -out), __builtin_ldexpf(1.0f, out)};
+    const unsigned u = __builtin_bit_cast(unsigned, vs) & 0x7fffffffu;
+    const int e = (int)(u >> 23);   // biased by 127
+    const int out = e - max(127 - 40, min(e, 127 + 39));
+    const float v = __builtin_bit_cast(float, u != 0 ? u : 0x3f800000u);
+    return ValueScale{u != 0 ? v * __builtin_bit_cast(float, (unsigned)(127 - out) << 23) : 1.0f,
+                      u != 0 ? __builtin_bit_cast(float, (unsigned)(127 + out) << 23) : 1.0f};
 }
 
 // Scales of a tile of an fp8 pool that is parked as bf16: {k_scale, k_scale} and {log2 fold, log2 fold} of its two pages,
@@ -679,7 +682,7 @@ SD_DEV void park_scales(char *dst, int half, float ks, float fold, int lane)
     }
     if (lane == 0) {
         *reinterpret_cast<float *>(dst + half * 4) = ks;
-        *reinterpret_cast<float *>(dst + 8 + half * 4) = __builtin_log2f(fold);
+        *reinterpret_cast<float *>(dst + 8 + half * 4) = __builtin_amdgcn_logf(fold);   // log2; fold is a normal number
     }
 }
 
