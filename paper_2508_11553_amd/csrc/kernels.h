@@ -109,7 +109,7 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
         const int64_t n = total_q / (blocks * units) + batch / 2;
         return (n > batch ? n : batch) * heads;
     };
-    const auto small_grid = [&](int blocks) { return (int64_t)((max_q_len + blocks * units - 1) / (blocks * units)) * batch * heads <= 4096; };
+    const auto small_grid = [&](int blocks) { return ((int64_t)max_q_len + blocks * units - 1) / (blocks * units) * batch * heads <= 4096; };
     const bool deep = max_context_len >= 2048;
     if (head_dim == 64) {
         if (kv_dtype == 0 && workgroups(16) >= 2048 && filled(16, 2)) return PrefillPlan{16, 1, false};

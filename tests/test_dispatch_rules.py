@@ -25,6 +25,10 @@ int main(int argc, char **argv)
         printf("%d %d %d\n", c, pick_chunk(&s), ws_layout(&s, num_chunks(&s, c)).total <= sd_workspace_bytes(&s));
     } else if (!strcmp(argv[1], "short_enough")) {
         printf("%d\n", short_enough(&s));
+    } else if (!strcmp(argv[1], "prefill_plan")) {   // ... total_q, max_q_len
+        const int G = s.num_q_heads / s.num_kv_heads;
+        const sd::PrefillPlan p = sd::prefill_plan(s.kv_dtype, s.head_dim, v[6], v[7], s.batch, s.num_kv_heads * sd::head_blocks(G), sd::units_per_block(G), s.max_context_len);
+        printf("%d %d\n", p.blocks, p.split);
     } else if (!strcmp(argv[1], "merge_width")) {   // items, rows, groups
         printf("%d\n", sd::merge_width(v[0], v[1], v[2]));
     }
@@ -88,3 +92,13 @@ def test_single_pass_is_bounded_by_what_one_sequence_may_cost(rule, kv_dtype, d,
                                                      (256, 16, 1, 1), (1024, 8, 1, 1), (2048, 16, 2, 1)])
 def test_merge_pass_cuts_heads_only_where_items_are_few(rule, items, rows, groups, width):
     assert rule("merge_width", items, rows, groups) == [width]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kv_dtype", [0, 1])
+@pytest.mark.parametrize("batch,total_q,max_q", [(1, 1, 1), (1, 2**31 - 1, 2**31 - 1), (2**20, 2**31 - 1, 2**31 - 1), (2**20, 1, 1), (3, 100, 2**31 - 1)])
+def test_prefill_plan_at_the_ends_of_its_arguments(rule, batch, total_q, max_q, kv_dtype, d):
+    blocks, split = rule("prefill_plan", batch, 8, 2, d, kv_dtype, 2**21, total_q, max_q)
+    assert (blocks, split) in {(16, 1), (8, 1), (8, 2), (4, 4), (2, 8)}
+    if batch > 1:
+        assert split <= 2   # a grid of more than 4096 workgroups takes the largest blocks there are
