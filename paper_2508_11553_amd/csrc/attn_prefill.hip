@@ -32,6 +32,60 @@
 
 namespace sd {
 
+// Sum of x over the lanes up to this one (DPP: lanes without a source add 0).
+SD_DEV int wave_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8: within rows of 16
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+SD_DEV int wave_max(int x)   // of values >= 0
+{
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+// The sequences of a batch as prefill_pick asks for them, one to a lane.
+struct WaveSequences {
+    int end, blocks;
+    SD_DEV WaveSequences(const PrefillArgs &a, int lane) : end(0), blocks(0)
+    {
+        int qs = 0, next = 0, L = 0;
+        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], L = a.context_lens[lane];
+        {
+            const int nq = min(next - qs, a.max_q_len);
+            L = max(0, min(L, a.max_context_len));
+            // rounded up; a.reciprocal = 2^32 / tokens of a workgroup, rounded up: exact below 2^24
+            if (lane < a.B && qs >= 0 && nq > 0 && (int64_t)qs + nq <= a.total_q) {
+                blocks = (int)__umulhi((unsigned)(nq + a.round_up), a.reciprocal);
+                end = (int)__umulhi((unsigned)(L + a.round_up), a.reciprocal);
+            }
+        }
+    }
+    SD_DEV int top() const { return wave_max(end); }
+    template <class F>
+    SD_DEV int sum(F f) const { return __builtin_amdgcn_readlane(wave_scan(f(end, blocks)), 63); }
+    struct Found {
+        int b, before, end, blocks;
+    };
+    template <class F>
+    SD_DEV Found find(F f, int m) const
+    {
+        const int own = f(end, blocks), incl = wave_scan(own);
+        const int b = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > m) | 1ull << 63);   // m is less than the sum
+        return Found{b, __builtin_amdgcn_readlane(incl - own, b), __builtin_amdgcn_readlane(end, b), __builtin_amdgcn_readlane(blocks, b)};
+    }
+};
+
 // Which query rows a wave owns (everything but `n`-dependent values is wave-uniform).
 struct PrefillRows {
     HeadBlock hb;
@@ -48,13 +102,19 @@ struct PrefillRows {
     SD_DEV bool find(const PrefillArgs &a, int groups, int group, int blocks)
     {
         const int Hv = a.Hkv * a.HB;
-        const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
-        if (item.block >= a.q_blocks) return false;
-        const int jb = a.q_blocks - 1 - item.block;
-        hb = head_block(item.pair % Hv, a.G, a.HB);
-        b = item.pair / Hv;
         tpb = units_per_block(a.G);
         const int tpw = blocks * tpb;   // query tokens per wave
+        int seq, head, jb;
+        if (a.plan.order) {   // head fastest
+            const PrefillBlock at = prefill_pick(WaveSequences(a, threadIdx.x & 63), (int)(blockIdx.x / Hv), a.plan.order);
+            seq = at.b, head = blockIdx.x % Hv, jb = at.block;
+        } else {
+            const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
+            seq = item.pair / Hv, head = item.pair % Hv, jb = a.q_blocks - 1 - item.block;
+        }
+        if (jb < 0) return false;
+        b = seq;
+        hb = head_block(head, a.G, a.HB);
         qs = a.q_start[b];
         nq = min(a.q_start[b + 1] - qs, a.max_q_len);
         const int i0 = jb * groups * tpw;
@@ -686,7 +746,8 @@ __global__ __launch_bounds__(512, 2) void prefill_pingpong_kernel(PrefillArgs a)
 hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipStream_t stream, hipEvent_t start,
                           hipEvent_t stop)
 {
-    const unsigned grid = prefill_grid(a.q_blocks, a.B * a.Hkv * a.HB);
+    const unsigned pairs = (unsigned)a.B * (unsigned)(a.Hkv * a.HB);
+    const unsigned grid = a.plan.order ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
     if (grid == 0) return hipSuccess;
     auto go = [&](auto kernel, int waves) {
         const dim3 g(grid), b(waves * 64);

@@ -74,11 +74,45 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
     const int rest = pairs % kXcds, classes = prefill_classes(rest);
     return (unsigned)(pairs / kXcds * kXcds) * (unsigned)q_blocks + (rest ? (unsigned)(rest * classes) * (unsigned)((q_blocks + classes - 1) / classes) : 0u);
 }
+// Longest first.  The order in which the query blocks of a batch start when the kernel looks at the lengths: by the class of their
+// range (eighths or quarters of the longest, counted in blocks), descending; within a class sequence after sequence, late blocks first, so that
+// neighbours still walk the same K/V together.  A block takes as long as its range, and a list that starts long items late ends late.  The
+// heads of a block go to the dies in turn, whatever sequence it is from, so no die is left with the longest sequences either.
+//
+// `s` gives every sequence's query blocks and where its last one ends (in blocks, rounded up): sum(f) = sum of f(end, blocks) over the sequences,
+// top() = the largest end, find(f, m) = the sequence in which the running sum of f passes m, and that sum before it.
+// 2^32 / tokens, rounded up: the high half of x times it is x / tokens for x < 2^24 and tokens <= 256 (a workgroup has at least two).
+__host__ inline uint32_t reciprocal_of(unsigned tokens) { return (uint32_t)((((uint64_t)1 << 32) + tokens - 1) / tokens); }
+constexpr int kMaxOrderedBatch = 64;   // sequences whose ends and blocks one wave holds, one to a lane
+struct PrefillBlock {
+    int b, block;   // block < 0: there is no k-th block
+};
+template <class Sequences>
+__host__ __device__ inline PrefillBlock prefill_pick(const Sequences &s, int k, int classes)
+{
+    const int top = s.top();
+    // blocks of a sequence that end above the lower edge of class c
+    const auto above = [top, classes](int c, int end, int blocks) {
+        const int n = c == 0 ? blocks : end - (int)((uint64_t)top * (unsigned)c / (unsigned)classes);
+        return n < 0 ? 0 : n < blocks ? n : blocks;
+    };
+    if (s.sum([above](int end, int blocks) { return above(0, end, blocks); }) <= k) return PrefillBlock{0, -1};
+    int lo = 0, hi = classes, higher = 0;   // block k lies in a class of [lo, hi); `higher` blocks end above hi's edge
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        const int n = s.sum([above, mid](int end, int blocks) { return above(mid, end, blocks); });
+        if (n > k) lo = mid;
+        else hi = mid, higher = n;
+    }
+    const auto at = s.find([above, lo, hi](int end, int blocks) { return above(lo, end, blocks) - above(hi, end, blocks); }, k - higher);
+    return PrefillBlock{at.b, at.blocks - 1 - above(hi, at.end, at.blocks) - (k - higher - at.before)};
+}
 // How a call of the causal pass is cut: column blocks of 16 query rows that a workgroup owns (16, 8, 4 or 2), the waves that share the
 // range of a block, and whether the workgroups run in two phases (bf16 pools with head_dim 128).
 struct PrefillPlan {
     int blocks, split;
     bool phases;
+    int order;      // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
 };
 // Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
 // waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
@@ -123,6 +157,25 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
     if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
     // (10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads: 4 blocks 19, 2 blocks 23 us)
     return enough(4) || max_context_len < 1024 || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+}
+
+// Classes of a call's order, 0: dealt pair by pair.  A workgroup finds its block in about 0.8 us (the lengths come from memory, then
+// a hundred dependent instructions), so a call whose workgroups all run at once, or of a single sequence, is dealt: six sequences of 800 tokens, 40 queries,
+// 8/2 heads, d = 64 8.2 : 9.1 us, dealt : longest first.  So are short contexts, whose time goes into reading queries and writing rows as much as into their
+// ranges, and which do better with long and short blocks side by side: nine of 274 - 453, 64/8 heads, whole prompts 73 : 80.  Otherwise:
+//   5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads 89 : 75; 10 of 1.1 k - 1.8 k, 9 - 36 queries, 28/4 38 : 25; 10 of 8 k, 168 - 506
+//   queries, 16/2 415 : 244; 12 fp8 of 2.5 k - 8 k, 700 - 2048 queries, 32/8 1276 : 1225; 8 prompts of 1.5 k - 4 k, d = 64 413 : 403;
+//   16 of 8192 with 2048 each, 32/8 3283 : 3296 with four classes, 3315 with eight, 3600 with 32 (fewer blocks of a sequence side by side).
+// 64 calls of 1000 tokens and more: 1.09 times as fast, up to 1.7; eight classes do as well as 32.
+__host__ inline int prefill_order(const PrefillPlan &plan, int head_dim, int64_t total_q, int units, int batch, int heads, int q_blocks, int max_context_len)
+{
+    if (batch == 1 || batch > kMaxOrderedBatch || max_context_len < kPrefillShort) return 0;
+    // workgroups the chip holds at once (a compute unit one to three: registers, or LDS for the tiles)
+    const int slots = 256 * (plan.split == 1 && plan.blocks == 8 ? (head_dim == 64 ? 3 : 2) : head_dim == 64 && plan.blocks != 2 ? 2 : 1);
+    const int64_t blocks = total_q / (plan.blocks * units);
+    // (dealt pair by pair, dies get alike only if every die gets the same heads)
+    if ((int64_t)q_blocks * batch * heads <= slots || (heads % kXcds == 0 && (blocks + batch) * heads <= slots)) return 0;
+    return blocks * heads >= 1536 ? 4 : 8;
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens
@@ -282,6 +335,8 @@ struct PrefillArgs {
     int32_t B, Hq, Hkv, G, HB, max_blocks, max_context_len;  // HB: head blocks per KV head, ceil(G / 16)
     int32_t total_q, max_q_len;  // rows of q; host-known bound on the rows of one sequence
     PrefillPlan plan;
+    uint32_t reciprocal;         // of the query tokens of a workgroup: 2^32 / tokens, rounded up (plan.order)
+    int32_t round_up;            // query tokens of a workgroup - 1
     int32_t q_blocks;            // workgroups (plan.blocks x 16/G query tokens each) that cover max_q_len
 };
 

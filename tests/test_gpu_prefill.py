@@ -278,3 +278,17 @@ def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, program,
             wl.k_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 3 else 0xff80
     got = gpu(wl, q, q_start).reshape(B, 150, Hq, d)
     assert np.array_equal(got[:, :150 - 84], want.reshape(B, 150, Hq, d)[:, :150 - 84])
+
+
+@pytest.mark.parametrize("B", [2, 64, 65])
+@pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", [(6, 2, 128, "bf16"), (4, 4, 64, "bf16"), (8, 2, 128, "fp8")])
+def test_longest_first_calls(sd, Hq, Hkv, d, kv_dtype, B):
+    """Batches whose workgroups find their block by the lengths (2 and 64 sequences) and the first that is dealt pair by pair again: sequences without
+    queries, with more queries than tokens, empty ones, and a length bound above all of them."""
+    rng = np.random.default_rng(B)
+    lens = [1100, 530] + [int(x) for x in rng.integers(0, 300, B - 2)]
+    nq = [700, 530] + [int(x) for x in rng.integers(0, 60, B - 2)]
+    if B > 2:
+        lens[5], nq[5], nq[6], nq[7] = 0, 9, 0, lens[7] + 20
+    wl, q, q_start = make(lens, nq, Hq, Hkv, d, kv_dtype, seed=90 + B)
+    check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
