@@ -41,6 +41,55 @@ SD_DEV int shared_tokens(const SplitArgs &a, int b)
     return max(0, min(min(a.shared_len[b], a.max_shared_len), L)) & ~(kPage - 1);
 }
 
+// The k-th of n sequences with the longest first: by the class (eighths of the longest) of the tokens that key(i) says sequence i brings,
+// descending, in order within a class.  Every wave works it out for itself, 64 sequences to a register, counted by ballots; about 1 us that the
+// other workgroup of the compute unit mostly hides, but not from workgroups of a few tiles: if none of the n is long, the order stays.
+template <class Key>
+SD_DEV int longest_first(int sequences, int k, int lane, Key key)
+{
+    constexpr int kPer = kMaxOrderedItems / 64;
+    const int per = (sequences + 63) / 64;
+    int x[kPer], top = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        x[i] = -1;   // no sequence
+        if (i < per && i * 64 + lane < sequences) x[i] = key(i * 64 + lane);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) top = max(top, x[i]);
+    top = wave_max(top);
+    if (top < kWorthOrdering) return k;
+    const auto edge = [top](int c) { return c == 0 ? -1 : (int)((uint64_t)top * (unsigned)c / 8); };
+    const auto above = [&](int t) {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (i >= per) break;   // wave-uniform
+            n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[i] > t));
+        }
+        return n;
+    };
+    int lo = 0, hi = 8, higher = 0;   // sequence k lies in a class of [lo, hi); `higher` sequences lie above
+#pragma unroll
+    for (int step = 4; step > 0; step /= 2) {
+        const int n = above(edge(lo + step));
+        if (n > k) lo += step;
+        else hi = lo + step, higher = n;
+    }
+    const int t0 = edge(lo), t1 = hi == 8 ? INT_MAX : edge(hi);
+    int left = k - higher;
+    for (int i = 0; i < kPer; ++i) {
+        const uint64_t in = __builtin_amdgcn_ballot_w64(x[i] > t0 && x[i] <= t1);
+        const int n = __builtin_popcountll(in);
+        if (left < n) {   // its lane: the one with `left` members of the class below it
+            const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(in >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in, 0));
+            return i * 64 + __builtin_ctzll(__builtin_amdgcn_ballot_w64(below == left) & in);
+        }
+        left -= n;
+    }
+    return 0;   // not reached: k < sequences
+}
+
 // Shared-prefix item: one workgroup owns one whole chunk of a group's shared
 // prefix for one KV head and up to 64 query rows: wave w owns the 16 rows of
 // column block w (G heads each of 16/G consecutive sequences of the group).
@@ -175,8 +224,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     const unsigned item = P::kDealByDie ? xcd_deal(blockIdx.x - a.group_items, gridDim.x - a.group_items, Hv) : blockIdx.x - a.group_items;
     const HeadBlock hb = head_block(item % Hv, a.G, a.HB);
     const int g = hb.g;
-    const int b = (item / Hv) % a.B;
+    int b = (item / Hv) % a.B;
     const int from_end = a.grid_chunks - 1 - (int)(item / (Hv * a.B));
+    if (from_end == 0 && b >= a.order.from) {   // last (or only) chunks are of all lengths; groups are counted from the batch's end
+        const int group_end = a.B - (a.B - 1 - b) / a.order.group * a.order.group, first = max(a.order.from, group_end - a.order.group);
+        b = first + longest_first(group_end - first, b - first, lane, [&](int s) {
+            const int own = max(0, min(a.context_lens[first + s], a.max_context_len)) - (GROUPS ? shared_tokens(a, first + s) : 0);
+            return own <= a.chunk_tokens ? own : (own - 1) % a.chunk_tokens + 1;
+        });
+    }
 
     const int L = max(0, min(a.context_lens[b], a.max_context_len));
     // slots of a shared prefix belong to the shared-prefix items; the others start where the prefix ends

@@ -185,6 +185,28 @@ __host__ inline int prefill_order(const PrefillPlan &plan, int head_dim, int64_t
 // is cut at the same places for every member of a group.
 __host__ __device__ inline int shared_slots(int sh, int chunk) { return (sh + chunk - 1) / chunk; }
 
+// Order of the sequences' last (or only) chunks in the split pass: longest first within groups of sequences, for two reasons.  The pass ends when
+// its last workgroup does, and long ones that start last leave the chip idle: that takes the batch's last sequences, about two rounds of
+// workgroups.  And a die that is dealt whole sequences (fp8; bf16 with fewer than 8 KV heads) gets more tokens than its neighbours,
+// unless sequences of like length are dealt in turn: that takes all of them, and costs every workgroup about 1 us, so it is for
+// lengths of 2048 and more.  us per step, in batch order : last group only : all groups
+//   1024 fp8 sequences of 512 - 4096, 64/8 heads 825 : 817 : 793       800 fp8 of 100 - 8000, 32/4 563 : 537 : 527
+//   16 x 16 branches of 64 - 4096, 32/8 458 : 434 : 432                1000 bf16 of 100 - 4000, 16/2 364 : 356 : 350
+//   1024 fp8 of 64 - 1024, 64/8 221 : 219 : 228                        600 bf16 of 100 - 2000, 32/8 418 : 409 : 409
+// Batches whose workgroups all run at once, or under 1024 tokens (300 us of short workgroups gain nothing), keep their order.
+constexpr int kMaxOrderedItems = 256;   // sequences whose lengths a wave holds, four to a lane
+constexpr int kWorthOrdering = 1024;
+struct SplitOrder {
+    int group, from;   // sequences of a group; the first sequence that belongs to one (`batch`: none)
+};
+__host__ inline SplitOrder split_order(int batch, int heads, int longest)   // longest: bound on the tokens of a chunk
+{
+    const bool deep = longest >= 2048;
+    const int round = (deep ? 2048 : 1024) / heads;
+    const int group = round < 64 ? 64 : round < kMaxOrderedItems ? round : kMaxOrderedItems;
+    if ((int64_t)batch * heads <= 512 || longest < kWorthOrdering) return SplitOrder{group, batch};
+    return SplitOrder{group, deep || batch < group ? 0 : batch - group};
+}
 // Arguments of the split-K pass (by value, lives in kernel-argument memory).
 struct SplitArgs {
     const uint16_t *q;           // [B][Hq][D] bf16
@@ -216,6 +238,7 @@ struct SplitArgs {
     uint32_t group_items;        // grid entries that serve shared prefixes (they come first)
     int32_t max_shared_len;      // host-known bound on shared_len[]; larger values are clamped to it
     int32_t grid_chunks;         // chunk slots the plain part of the grid spans (S, or S-1 without groups)
+    SplitOrder order;            // of the sequences' last chunks
 };
 
 // Hand-over inside a workgroup.  The four waves of a workgroup walk neighbouring pieces (ranges 4i ..

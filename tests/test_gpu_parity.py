@@ -1037,3 +1037,27 @@ def test_one_call_decode_step_replays_from_a_hip_graph(sd):
     oracle.kv_append(kn, wl.v_new, wl.seq_ids, wl.positions, k, v, wl.block_table)
     wl.q = q
     check(got.cpu().numpy(), oracle_full(wl, k, v))
+
+
+# ---------------------------------------------------------------- order of the split pass's items
+@pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("fp8", 128), ("fp8", 64)])
+@pytest.mark.parametrize("batch,longest", [(513, 1100), (600, 2100), (256, 2100)])
+def test_longest_first_items_serve_every_sequence(sd, batch, longest, kv_dtype, d):
+    """A workgroup per (sequence, head), found by the lengths: the batch's last sequences only (1100), all of them in groups of which the first is
+    short (600 = 88 + 256 + 256), or a single group; empty sequences, and groups without a long one, which keep their order."""
+    lens = [int(x) for x in np.random.default_rng(batch).integers(0, 70, size=batch)]
+    lens[batch - 3], lens[batch // 2], lens[7] = longest, longest - 65, 0
+    wl = workloads.make_custom(lens, 8, 4, d, kv_dtype, seed=batch)
+    dw = device_workload(wl, chunk_tokens=4096)
+    dw.out.fill_(float("nan"))
+    got = dw.attend().cpu().numpy()
+    (check_fp8 if kv_dtype == "fp8" else check)(got, oracle_full(wl))
+
+
+@pytest.mark.parametrize("chunk", [1024, 2048])
+def test_longest_first_items_behind_shared_prefixes(sd, chunk):
+    session_of, prefix_len = np.repeat(np.arange(30), 10), np.repeat(np.arange(30) * 16, 10)
+    lens = prefix_len + np.random.default_rng(chunk).integers(0, 60, size=300)
+    lens[[4, 150, 299]] += [chunk, chunk + 40, 2 * chunk - 70]
+    wl = workloads.make_custom(lens, 8, 2, 128, seed=chunk, session_of=session_of, prefix_len=prefix_len)
+    check(gpu_attend_prefix(wl, chunk_tokens=chunk), oracle_full(wl))
