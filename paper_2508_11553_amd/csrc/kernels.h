@@ -117,10 +117,27 @@ struct PrefillPlan {
 // Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
 // waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
 // workgroup per compute unit at head_dim 128, which runs one at a time, and one at head_dim 64, which runs two or three.  Workgroups whose
-// rows are mostly empty end early, and long ranges gain more by being shared, so both move the line up.  Short
-// contexts (below kPrefillShort tokens) have few tiles to share: no split.  The lines were fitted to 4200 random calls (1 to 64 sequences of 1 to
+// rows are mostly empty end early, and long ranges gain more by being shared, so both move the line up.
+// The lines over bf16 pools at head_dim 128 are fitted to 1740 random calls (1 to 24 sequences of 200 to 16 k tokens, 8 to 2048 queries, heads as in
+// perf/cases.py), each timed with every block size; the rule costs 2 % over the best size of each call.
+// (The cost is flat for 8 blocks from 2048 tokens on between 192 and 256 workgroups; 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads have 208: 87 us
+// with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
+// 4 / 2 blocks by workgroups of the larger block, half of its rows in use or more:
+//   workgroups              24 - 95   96 - 134   135 - 191   192 - 270   271 - 383   384 - 542   543 and more
+//   under 512 tokens   16    1.17      1.12        0.82        0.86        0.84        0.79       0.73
+//                       8    1.24      1.07        0.80        0.84        0.86        0.75       0.71
+//                       4    1.24      1.02        0.75        0.82        0.84        0.76       0.72
+//   under 2048         16    1.41      1.35        1.02        0.94        0.83        0.83       0.78
+//                       8    1.38      1.32        0.93        0.85        0.89        0.78       0.76
+//                       4    1.37      1.10        0.82        0.79        0.88        0.76       0.73
+//   6000 and more      16    1.79      1.67        1.33        1.08        1.14        0.95       0.94
+//                       8    1.57      1.43        1.13        0.94        0.96        0.86       0.87
+//                       4    1.60      1.43        1.06        0.97        1.00        0.90       0.88
+// (Under 512 tokens a single wave used to walk the range alone: two sequences of 131 - 397 tokens, 220 queries, 8/2 heads 18.5 -> 9.5 us.)
+// The other lines were fitted to 4200 random calls (1 to 64 sequences of 1 to
 // 12000 tokens, 1 to 3000 queries each, 1 to 32 heads per KV head, bounds tight and 4 and 16 times too wide), each timed with every
-// block size.  Geometric mean of the time with 16 / 8, 8 / 4 and 4 / 2 blocks, by workgroups of the larger block (bf16, tight bounds):
+// block size; there contexts below kPrefillShort tokens are not split.  Geometric mean of the time with 16 / 8, 8 / 4 and 4 / 2 blocks, by workgroups of
+// the larger block (tight bounds; head_dim 128 as the kernel for fp8 pools takes it):
 //   workgroups       64 - 95  96 - 127  128 - 159  160 - 191  192 - 255  256 - 383  512 - 767  1024 and more
 //   head_dim 128  16   1.32     1.22       1.10       1.04       0.96       0.91       0.86       0.76
 //                  8   1.27     1.18       1.06       0.98       0.96       0.90       0.78       0.74
@@ -150,10 +167,20 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
         if (max_context_len < kPrefillShort || workgroups(8) >= (deep ? 512 : 256) || !small_grid(4)) return PrefillPlan{8, 1, false};
         return workgroups(4) >= (max_context_len >= 4096 ? 384 : deep ? 256 : 128) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }
-    if (max_context_len < kPrefillShort) return kv_dtype == 0 ? PrefillPlan{16, 1, false} : PrefillPlan{8, 1, false};
-    // (for 8 blocks the cost over all calls is flat between 128 and 192; 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads have 228: 98 : 91 us with 4)
+    if (kv_dtype == 0) {
+        const int depth = max_context_len < kPrefillShort ? 0 : max_context_len < 1024 ? 1 : !deep ? 2 : 3;
+        const auto enough = [&](int blocks) {
+            const int line[4][3] = {{128, 128, 96}, {144, 144, 96}, {144, 144, 128}, {288, 240, 160}};
+            return workgroups(blocks) * 4 >= (int64_t)line[depth][blocks == 16 ? 0 : blocks == 8 ? 1 : 2] * (filled(blocks, 2) ? 4 : 5);
+        };
+        if (enough(16) || !small_grid(8)) return PrefillPlan{16, 1, depth > 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+        if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
+        return enough(4) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+    }
+    if (max_context_len < kPrefillShort) return PrefillPlan{8, 1, false};
+    // (for 8 blocks the cost over all calls is flat between 128 and 192)
     const auto enough = [&](int blocks) { return workgroups(blocks) * 4 >= (blocks == 8 || !filled(blocks, 2) ? 192 : 128) * (deep ? 5 : 4); };
-    if (enough(16) || !small_grid(8)) return PrefillPlan{16, 1, kv_dtype == 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+    if (enough(16) || !small_grid(8)) return PrefillPlan{16, 1, false};
     if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
     // (10 sequences of 480 - 947, 43 - 129 queries, 8/2 heads: 4 blocks 19, 2 blocks 23 us)
     return enough(4) || max_context_len < 1024 || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};

@@ -138,3 +138,19 @@ def test_a_loose_bound_on_the_queries_keeps_the_grid_small(program):
     assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=sum(q)) == (8, 2, 0)
     assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=20 * sum(q))[0] == 16
     assert plan(program, [2000] * 8, [100] * 8, 16, 4, 64, max_q=20000)[0] == 8
+
+
+EDGES = [1, 16, 31, 32, 33, 63, 65, 127, 128, 129, 255, 257, 290]   # contexts that end at pages, tiles and rounds of 2, 4 and 8 tiles
+
+
+def direct_case(blocks, short):
+    """(lens, queries, Hq, Hkv) over bf16 pools, head_dim 128, that take 8, 4 or 2 column blocks, with contexts below 512 tokens or not."""
+    Hq, Hkv, most = {8: (28, 4, 75), 4: (28, 4, 30), 2: (8, 2, 20)}[blocks]
+    lens = EDGES + [300 if short else 777]
+    return lens, [min(L, most) for L in lens], Hq, Hkv
+
+
+@pytest.mark.parametrize("blocks", [8, 4, 2])
+@pytest.mark.parametrize("short", [True, False])
+def test_short_and_longer_contexts_take_every_split(program, blocks, short):
+    assert plan(program, *direct_case(blocks, short), 128) == (blocks, 16 // blocks, 0)
