@@ -134,10 +134,19 @@ struct PrefillPlan {
 //                       8    1.57      1.43        1.13        0.94        0.96        0.86       0.87
 //                       4    1.60      1.43        1.06        0.97        1.00        0.90       0.88
 // (Under 512 tokens a single wave used to walk the range alone: two sequences of 131 - 397 tokens, 220 queries, 8/2 heads 18.5 -> 9.5 us.)
+// At head_dim 64 over bf16 pools the lines of 8 and 4 blocks are fitted to 900 such calls; the rule costs 1 % over the best size of each call, the lines further
+// down, which stay for fp8 pools, 6 % (three of 278 - 457 tokens, 2 - 16 queries, 16/2 heads 12.0 against 6.9 us with 2 blocks).
+//   workgroups              under 96   96 - 127   128 - 191   192 - 255   256 - 383   384 - 511   512 - 767   768 - 1023   1024 and more
+//   under 512 tokens    8    0.95        0.92       0.81        0.82        0.69        0.67        0.61         0.59       0.51
+//                       4    1.46        1.32       1.16        1.18        0.95        0.91        0.96         0.87       0.85
+//   under 2048          8    1.42        1.27       1.17        1.18        0.99        0.80        0.79         0.69       0.64
+//                       4    1.61        1.52       1.22        1.23        0.98        0.83        0.96         0.85       0.85
+//   4096 and more       8    2.12        1.89       1.76        1.72        1.45        1.31        1.13         1.07       0.96
+//                       4    1.95        1.68       1.47        1.35        1.09        0.91        0.98         0.90       0.86
 // The other lines were fitted to 4200 random calls (1 to 64 sequences of 1 to
 // 12000 tokens, 1 to 3000 queries each, 1 to 32 heads per KV head, bounds tight and 4 and 16 times too wide), each timed with every
 // block size; there contexts below kPrefillShort tokens are not split.  Geometric mean of the time with 16 / 8, 8 / 4 and 4 / 2 blocks, by workgroups of
-// the larger block (tight bounds; head_dim 128 as the kernel for fp8 pools takes it):
+// the larger block (tight bounds; as the kernels that park through registers take them):
 //   workgroups       64 - 95  96 - 127  128 - 159  160 - 191  192 - 255  256 - 383  512 - 767  1024 and more
 //   head_dim 128  16   1.32     1.22       1.10       1.04       0.96       0.91       0.86       0.76
 //                  8   1.27     1.18       1.06       0.98       0.96       0.90       0.78       0.74
@@ -164,6 +173,12 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
     const bool deep = max_context_len >= 2048;
     if (head_dim == 64) {
         if (kv_dtype == 0 && workgroups(16) >= 2048 && filled(16, 2)) return PrefillPlan{16, 1, false};
+        if (kv_dtype == 0) {
+            const int line[5][2] = {{96, 192}, {320, 160}, {320, 256}, {640, 320}, {1024, 384}};
+            const int *at = line[max_context_len < kPrefillShort ? 0 : max_context_len < 1024 ? 1 : !deep ? 2 : max_context_len < 4096 ? 3 : 4];
+            if (workgroups(8) >= at[0] || !small_grid(4)) return PrefillPlan{8, 1, false};
+            return workgroups(4) >= at[1] || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
+        }
         if (max_context_len < kPrefillShort || workgroups(8) >= (deep ? 512 : 256) || !small_grid(4)) return PrefillPlan{8, 1, false};
         return workgroups(4) >= (max_context_len >= 4096 ? 384 : deep ? 256 : 128) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }

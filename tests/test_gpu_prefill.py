@@ -9,7 +9,7 @@ import oracle
 import workloads
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 from tests.test_gpu_parity import check as check_decode, check_fp8, device_workload, sd  # noqa: F401  (sd is a fixture)
-from tests.test_prefill_geometry import PLANS, block_case, direct_case, plan, program, stretch_case  # noqa: F401  (program is a fixture)
+from tests.test_prefill_geometry import DIRECT, PLANS, block_case, direct_case, plan, program, stretch_case  # noqa: F401  (program is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -294,12 +294,11 @@ def test_longest_first_calls(sd, Hq, Hkv, d, kv_dtype, B):
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
 
 
-@pytest.mark.parametrize("blocks", [8, 4, 2])
-@pytest.mark.parametrize("short", [True, False])
-def test_split_ranges_that_end_at_pages_tiles_and_rounds(sd, blocks, short):
+@pytest.mark.parametrize("d,blocks,short", DIRECT)
+def test_split_ranges_that_end_at_pages_tiles_and_rounds(sd, d, blocks, short):
     """Slots of the pool past a sequence's end hold NaN and infinity: what is loaded for tokens that do not exist must not reach any row."""
-    lens, nq, Hq, Hkv = direct_case(blocks, short)
-    wl, q, q_start = make(lens, nq, Hq, Hkv, 128, seed=120 + blocks)
+    lens, nq, Hq, Hkv = direct_case(blocks, short, d)
+    wl, q, q_start = make(lens, nq, Hq, Hkv, d, seed=120 + blocks)
     for b, L in enumerate(lens):
         if L % 16:
             page = wl.block_table[b, L // 16]

@@ -143,14 +143,16 @@ def test_a_loose_bound_on_the_queries_keeps_the_grid_small(program):
 EDGES = [1, 16, 31, 32, 33, 63, 65, 127, 128, 129, 255, 257, 290]   # contexts that end at pages, tiles and rounds of 2, 4 and 8 tiles
 
 
-def direct_case(blocks, short):
-    """(lens, queries, Hq, Hkv) over bf16 pools, head_dim 128, that take 8, 4 or 2 column blocks, with contexts below 512 tokens or not."""
+def direct_case(blocks, short, d):
+    """(lens, queries, Hq, Hkv) over bf16 pools that take 8, 4 or 2 column blocks, with contexts below 512 tokens or not."""
     Hq, Hkv, most = {8: (28, 4, 75), 4: (28, 4, 30), 2: (8, 2, 20)}[blocks]
     lens = EDGES + [300 if short else 777]
     return lens, [min(L, most) for L in lens], Hq, Hkv
 
 
-@pytest.mark.parametrize("blocks", [8, 4, 2])
-@pytest.mark.parametrize("short", [True, False])
-def test_short_and_longer_contexts_take_every_split(program, blocks, short):
-    assert plan(program, *direct_case(blocks, short), 128) == (blocks, 16 // blocks, 0)
+DIRECT = [(128, blocks, short) for blocks in (8, 4, 2) for short in (True, False)] + [(64, 4, False), (64, 2, True), (64, 2, False)]
+
+
+@pytest.mark.parametrize("d,blocks,short", DIRECT)
+def test_short_and_longer_contexts_take_every_split(program, d, blocks, short):
+    assert plan(program, *direct_case(blocks, short, d), d) == (blocks, 16 // blocks, 0)
