@@ -14,7 +14,8 @@
 // parked, once per workgroup, and then take the bf16 pools' tile step (12 sequences of 2.5 k to 8 k tokens, 700 to
 // 2048 queries, 32/8 heads: 1.50 -> 1.28 ms against converting K in every consuming wave).
 //
-// Large calls over bf16 pools, whose rows need no conversion, have kernels of their own further down.
+// bf16 pools, whose rows need no conversion, have kernels of their own further down for large calls and for split ranges; the general kernel
+// serves them in one phase (short contexts and few queries per sequence), and at head_dim 64 with blocks of 8.
 //
 // The causal limit is a per-lane token bound in the score mask; a wave stops
 // once a tile starts at or past the last position any of its rows may see.
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(kW * 64, kWavesPerSimd) void prefill_wide_kernel(Pr
 }
 
 // ---------------------------------------------------------------------------
-// bf16 pools, large calls.  K and V rows go from memory straight into LDS, without passing through registers: a tile's
+// bf16 pools, large calls and split ranges.  K and V rows go from memory straight into LDS, without passing through registers: a tile's
 // slot holds K of its two pages and V of its two pages as rows, and the V^T operands are formed by
 // transposing LDS reads.  That leaves the registers and the vector instructions of parking (a fifth of the tile step's) to
 // the tile step.  A row's 16-byte pieces are permuted as they are loaded, so that the reads spread over all banks:
