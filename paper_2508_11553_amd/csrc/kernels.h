@@ -133,6 +133,8 @@ struct PrefillPlan {
 //   6000 and more      16    1.79      1.67        1.33        1.08        1.14        0.95       0.94
 //                       8    1.57      1.43        1.13        0.94        0.96        0.86       0.87
 //                       4    1.60      1.43        1.06        0.97        1.00        0.90       0.88
+// (From 2048 tokens on 192 - 255 workgroups of 16 blocks stay, 257 - 319 are cut: of 185 calls that one line at 288 would move, 10 become slower by more than
+// 8 % with it and 2 with these; the average is the same.)
 // (Under 512 tokens a single wave used to walk the range alone: two sequences of 131 - 397 tokens, 220 queries, 8/2 heads 18.5 -> 9.5 us.)
 // At head_dim 64 over bf16 pools the lines of 8 and 4 blocks are fitted to 900 such calls; the rule costs 1 % over the best size of each call, the lines further
 // down, which stay for fp8 pools, 6 % (three of 278 - 457 tokens, 2 - 16 queries, 16/2 heads 12.0 against 6.9 us with 2 blocks).
@@ -185,10 +187,13 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
     if (kv_dtype == 0) {
         const int depth = max_context_len < kPrefillShort ? 0 : max_context_len < 1024 ? 1 : !deep ? 2 : 3;
         const auto enough = [&](int blocks) {
-            const int line[4][3] = {{128, 128, 96}, {144, 144, 96}, {144, 144, 128}, {288, 240, 160}};
+            const int line[4][3] = {{128, 128, 96}, {144, 144, 96}, {144, 144, 128}, {192, 240, 160}};
             return workgroups(blocks) * 4 >= (int64_t)line[depth][blocks == 16 ? 0 : blocks == 8 ? 1 : 2] * (filled(blocks, 2) ? 4 : 5);
         };
-        if (enough(16) || !small_grid(8)) return PrefillPlan{16, 1, depth > 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+        // a few workgroups of 16 blocks past the 256 that run at once wait for a whole round of them
+        const int64_t w = workgroups(16);
+        const bool just_past = depth == 3 && filled(16, 2) && w > 256 && w < 320;
+        if ((enough(16) && !just_past) || !small_grid(8)) return PrefillPlan{16, 1, depth > 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
         if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
         return enough(4) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }

@@ -156,3 +156,9 @@ DIRECT = [(128, blocks, short) for blocks in (8, 4, 2) for short in (True, False
 @pytest.mark.parametrize("d,blocks,short", DIRECT)
 def test_short_and_longer_contexts_take_every_split(program, d, blocks, short):
     assert plan(program, *direct_case(blocks, short, d), d) == (blocks, 16 // blocks, 0)
+
+
+@pytest.mark.parametrize("batch,blocks", [(11, 8), (12, 16), (15, 16), (16, 16), (17, 8), (19, 8), (20, 16)])
+def test_one_round_of_large_workgroups_stays_and_a_few_more_are_cut(program, batch, blocks):
+    """Long contexts over bf16 pools: 16 workgroups per sequence, 256 of which run at once."""
+    assert plan(program, [4000] * batch, [96] * batch, 32, 8, 128)[0] == blocks
