@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import workloads
+from tests.test_prefill_geometry import LONGEST_FIRST_ITEMS
 
 pytestmark = pytest.mark.gpu
 
@@ -1041,7 +1042,7 @@ def test_one_call_decode_step_replays_from_a_hip_graph(sd):
 
 # ---------------------------------------------------------------- order of the split pass's items
 @pytest.mark.parametrize("kv_dtype,d", [("bf16", 128), ("fp8", 128), ("fp8", 64)])
-@pytest.mark.parametrize("batch,longest", [(513, 1100), (600, 2100), (256, 2100)])
+@pytest.mark.parametrize("batch,longest", sorted(LONGEST_FIRST_ITEMS))
 def test_longest_first_items_serve_every_sequence(sd, batch, longest, kv_dtype, d):
     """A workgroup per (sequence, head), found by the lengths: the batch's last sequences only (1100), all of them in groups of which the first is
     short (600 = 88 + 256 + 256), or a single group; empty sequences, and groups without a long one, which keep their order."""

@@ -9,7 +9,8 @@ import oracle
 import workloads
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 from tests.test_gpu_parity import check as check_decode, check_fp8, device_workload, sd  # noqa: F401  (sd is a fixture)
-from tests.test_prefill_geometry import DIRECT, PLANS, block_case, direct_case, plan, program, stretch_case  # noqa: F401  (program is a fixture)
+from tests.test_prefill_geometry import (DIRECT, FOUR_CLASSES, LONGEST_FIRST, PLANS, block_case, direct_case, longest_first_case, plan, program,  # noqa: F401
+                                         stretch_case)  # (program is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -281,17 +282,18 @@ def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, program,
 
 
 @pytest.mark.parametrize("B", [2, 64, 65])
-@pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", [(6, 2, 128, "bf16"), (4, 4, 64, "bf16"), (8, 2, 128, "fp8")])
+@pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", LONGEST_FIRST)
 def test_longest_first_calls(sd, Hq, Hkv, d, kv_dtype, B):
     """Batches whose workgroups find their block by the lengths (2 and 64 sequences) and the first that is dealt pair by pair again: sequences without
-    queries, with more queries than tokens, empty ones, and a length bound above all of them."""
-    rng = np.random.default_rng(B)
-    lens = [1100, 530] + [int(x) for x in rng.integers(0, 300, B - 2)]
-    nq = [700, 530] + [int(x) for x in rng.integers(0, 60, B - 2)]
-    if B > 2:
-        lens[5], nq[5], nq[6], nq[7] = 0, 9, 0, lens[7] + 20
+    queries, with more queries than tokens, and empty ones."""
+    lens, nq, Hq, Hkv = longest_first_case(B, Hq, Hkv, d)
     wl, q, q_start = make(lens, nq, Hq, Hkv, d, kv_dtype, seed=90 + B)
     check(gpu(wl, q, q_start), ref(wl, q, q_start), kv_dtype)
+
+
+def test_longest_first_calls_in_four_classes(sd):
+    wl, q, q_start = make(*FOUR_CLASSES, seed=97)
+    check(gpu(wl, q, q_start), ref(wl, q, q_start))
 
 
 @pytest.mark.parametrize("d,blocks,short", DIRECT)

@@ -2,21 +2,31 @@
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 from paper_2508_11553_amd import build as sd_build
 from tests.test_kernel_resources import CSRC
 
 PROGRAM = r"""
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 #include "kernels.h"
 int main(int argc, char **argv)
 {
+    if (!strcmp(argv[1], "split")) {
+        const sd::SplitOrder o = sd::split_order(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
+        printf("%d %d\n", o.group, o.from);
+        return 0;
+    }
     if (argc > 3) {
         const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[8]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
-        printf("%d %d %d\n", p.blocks, p.split, p.phases);
+        const int max_q = std::min(atoll(argv[8]), atoll(argv[2])), tokens = p.blocks * atoi(argv[5]);
+        const int order = sd::prefill_order(p, atoi(argv[1]), atoll(argv[2]), atoi(argv[5]), atoi(argv[3]), atoi(argv[4]), (max_q + tokens - 1) / tokens, atoi(argv[6]));
+        printf("%d %d %d %d\n", p.blocks, p.split, p.phases, order);
         return 0;
     }
     const int q_blocks = atoi(argv[1]), pairs = atoi(argv[2]);
@@ -98,6 +108,11 @@ PLANS = [("bf16", 128, (16, 1, 1))] + [(kv, 128, p) for kv in ("bf16", "fp8") fo
 
 def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
     """(column blocks of a workgroup, waves that share a block's range, two phases) of a call."""
+    return plan_and_order(program, lens, q, Hq, Hkv, d, kv_dtype, bound, max_q)[:3]
+
+
+def plan_and_order(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
+    """The same and the classes of the order in which the workgroups start, 0: dealt pair by pair."""
     G = Hq // Hkv
     args = (d, sum(q), len(lens), Hkv * ((G + 15) // 16), 16 // G if G <= 8 else 1, bound or max(lens), int(kv_dtype == "fp8"), max_q or max(q))
     got = subprocess.run([program] + [str(x) for x in args], capture_output=True, text=True, check=True)
@@ -162,3 +177,56 @@ def test_short_and_longer_contexts_take_every_split(program, d, blocks, short):
 def test_one_round_of_large_workgroups_stays_and_a_few_more_are_cut(program, batch, blocks):
     """Long contexts over bf16 pools: 16 workgroups per sequence, 256 of which run at once."""
     assert plan(program, [4000] * batch, [96] * batch, 32, 8, 128)[0] == blocks
+
+
+LONGEST_FIRST = [(6, 2, 128, "bf16"), (4, 4, 64, "bf16"), (8, 2, 128, "fp8")]
+
+
+def longest_first_case(B, Hq, Hkv, d):
+    """(lens, queries, Hq, Hkv) of batches with two long sequences; larger ones also have sequences without queries, with more queries than tokens, and
+    empty ones."""
+    if B == 2:
+        return [2300, 1100], [1400, 1100], *((16, 16) if d == 64 else (Hq, Hkv))
+    rng = np.random.default_rng(B)
+    lens = [1100, 530] + [int(x) for x in rng.integers(0, 300, B - 2)]
+    nq = [700, 530] + [int(x) for x in rng.integers(0, 60, B - 2)]
+    lens[5], nq[5], nq[6], nq[7] = 0, 9, 0, lens[7] + 20
+    return lens, nq, Hq, Hkv
+
+
+@pytest.mark.parametrize("B,classes", [(2, 8), (64, 8), (65, 0)])
+@pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", LONGEST_FIRST)
+def test_the_longest_first_cases_are_what_they_say(program, Hq, Hkv, d, kv_dtype, B, classes):
+    assert plan_and_order(program, *longest_first_case(B, Hq, Hkv, d), d, kv_dtype)[3] == classes
+
+
+FOUR_CLASSES = ([1300, 1200, 1250, 700, 330, 1300, 1100, 40], [1300, 900, 1250, 700, 200, 1100, 1100, 40], 32, 32, 64)   # ragged
+
+
+@pytest.mark.parametrize("call,want", [(FOUR_CLASSES, (8, 1, 0, 4)), (([8000] * 8, [2048] * 8, 32, 8, 128), (16, 1, 1, 4)),
+                                       (([8000] * 8, [1100] * 8, 32, 8, 128), (16, 1, 1, 8))])
+def test_large_calls_are_ordered_in_four_classes(program, call, want):
+    assert plan_and_order(program, *call) == want
+
+
+@pytest.mark.parametrize("lens,q,classes", [([8000], [4096], 0), ([8000, 7000], [512, 512], 0), ([8000, 7000], [528, 512], 8)])
+def test_single_sequences_and_calls_that_run_at_once_are_dealt(program, lens, q, classes):
+    """Workgroups of 32 queries, 256 of which run at once."""
+    assert plan_and_order(program, lens, q, 32, 8, 128) == ((16, 1, 1) if len(lens) == 1 else (8, 2, 0)) + (classes,)
+
+
+LONGEST_FIRST_ITEMS = {   # (sequences, longest): sequences of a group, the first that belongs to one; 4 KV heads
+    (513, 1100): (256, 257),   # the batch's last sequences only
+    (600, 2100): (256, 0),     # all of them, 88 + 256 + 256
+    (256, 2100): (256, 0),     # a single group
+}
+
+
+@pytest.mark.parametrize("batch,heads,longest,want", [(b, 4, n, w) for (b, n), w in LONGEST_FIRST_ITEMS.items()] + [
+    (300, 2, 1024, (256, 44)), (300, 2, 2048, (256, 0)),   # behind shared prefixes, chunks of 1024 and 2048
+    (128, 4, 4096, (256, 128)), (129, 4, 4096, (256, 0)),  # all workgroups run at once, and one sequence more
+    (600, 4, 1023, (256, 600)), (600, 64, 1024, (64, 536)), (600, 4096, 2048, (64, 0)), (200, 4, 1024, (256, 0)),
+])
+def test_order_of_the_split_pass(program, batch, heads, longest, want):
+    got = subprocess.run([program, "split", str(batch), str(heads), str(longest)], capture_output=True, text=True, check=True)
+    assert tuple(map(int, got.stdout.split())) == want
