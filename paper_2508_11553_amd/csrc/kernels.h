@@ -119,9 +119,10 @@ struct PrefillPlan {
 // workgroup per compute unit at head_dim 128, which runs one at a time, and one at head_dim 64, which runs two or three.  Workgroups whose
 // rows are mostly empty end early, and long ranges gain more by being shared, so both move the line up.
 // The lines over bf16 pools at head_dim 128 are fitted to 1740 random calls (1 to 24 sequences of 200 to 16 k tokens, 8 to 2048 queries, heads as in
-// perf/cases.py), each timed with every block size; the rule costs 2 % over the best size of each call.
-// (The cost is flat for 8 blocks from 2048 tokens on between 192 and 256 workgroups; 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads have 208: 87 us
-// with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
+// perf/cases.py), each timed with every block size; the rule costs 1.8 % over the best size of each call on average, 136 calls take more than 1.1 and 64 more than 1.2 of it.
+// (8 or 4 blocks from 2048 tokens on, 800 more calls drawn for it: 0.99 of the time with 8 from 176 workgroups on, 0.94 from 192 to 255.  Which calls do better with 4 is a matter
+// of the context lengths, which are on the device: 1.08 where their mean is under three quarters of the longest, 0.91 otherwise.  5 sequences of 300 - 6000,
+// 17 - 300 queries, 28/4 heads have 220: 87 us with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
 // 4 / 2 blocks by workgroups of the larger block, half of its rows in use or more:
 //   workgroups              24 - 95   96 - 134   135 - 191   192 - 270   271 - 383   384 - 542   543 and more
 //   under 512 tokens   16    1.17      1.12        0.82        0.86        0.84        0.79       0.73
@@ -187,7 +188,7 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
     if (kv_dtype == 0) {
         const int depth = max_context_len < kPrefillShort ? 0 : max_context_len < 1024 ? 1 : !deep ? 2 : 3;
         const auto enough = [&](int blocks) {
-            const int line[4][3] = {{128, 128, 96}, {144, 144, 96}, {144, 144, 128}, {192, 240, 160}};
+            const int line[4][3] = {{128, 128, 96}, {144, 144, 96}, {144, 144, 128}, {192, 192, 160}};
             return workgroups(blocks) * 4 >= (int64_t)line[depth][blocks == 16 ? 0 : blocks == 8 ? 1 : 2] * (filled(blocks, 2) ? 4 : 5);
         };
         // a few workgroups of 16 blocks past the 256 that run at once wait for a whole round of them
