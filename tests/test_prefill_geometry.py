@@ -179,6 +179,12 @@ def test_one_round_of_large_workgroups_stays_and_a_few_more_are_cut(program, bat
     assert plan(program, [4000] * batch, [96] * batch, 32, 8, 128)[0] == blocks
 
 
+@pytest.mark.parametrize("batch,blocks", [(22, 16), (32, 16), (33, 8), (34, 8), (39, 8), (40, 16)])
+def test_one_round_is_counted_by_full_blocks_where_all_are_full(program, batch, blocks):
+    """8 workgroups per sequence without an empty row."""
+    assert plan(program, [4000] * batch, [64] * batch, 32, 8, 128)[0] == blocks
+
+
 @pytest.mark.parametrize("q,blocks", [(176, 4), (184, 8), (216, 8), (232, 8)])
 def test_long_contexts_over_bf16_pools_are_cut_below_8_blocks_where_192_workgroups_are_not_reached(program, q, blocks):
     """Two sequences of long contexts: 184, 192, 224 and 240 workgroups of 8 blocks."""
