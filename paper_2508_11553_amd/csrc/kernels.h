@@ -215,8 +215,13 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
 // ranges, and which do better with long and short blocks side by side: nine of 274 - 453, 64/8 heads, whole prompts 73 : 80.  Otherwise:
 //   5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads 89 : 75; 10 of 1.1 k - 1.8 k, 9 - 36 queries, 28/4 38 : 25; 10 of 8 k, 168 - 506
 //   queries, 16/2 415 : 244; 12 fp8 of 2.5 k - 8 k, 700 - 2048 queries, 32/8 1276 : 1225; 8 prompts of 1.5 k - 4 k, d = 64 413 : 403;
-//   16 of 8192 with 2048 each, 32/8 3283 : 3296 with four classes, 3315 with eight, 3600 with 32 (fewer blocks of a sequence side by side).
-// 64 calls of 1000 tokens and more: 1.09 times as fast, up to 1.7; eight classes do as well as 32.
+//   eight classes do as well as 32; with 32 fewer blocks of a sequence run side by side, which costs large calls a tenth.
+// What finding the block costs grows with the rounds of workgroups, what the order can gain with the walk of one of them.  3020 random calls (512 tokens to 16 k,
+// 2 to 64 sequences, heads as in perf/cases.py, bf16 and fp8), dealt over longest first, by context / 256 against the rounds, and how many lose and gain more than 8 %:
+//                     512 - 767          768 - 1023         1024 - 2047         2048 - 4095         4096 and more
+//   no more rounds    1.10 (14, 103)     1.09 (11, 71)      1.10 (23, 187)      1.11 (14, 233)      1.11 (23, 355)
+//   more               .97 (32, 3)        .99 (7, 7)        1.00 (1, 4)         1.01 (0, 2)
+// From 16 rounds on it is 1.00 at any length (16 of 8192 with 2048 each, 32/8 3283 : 3296 us), and at head_dim 64 under 1024 tokens from one round on.
 __host__ inline int prefill_order(const PrefillPlan &plan, int head_dim, int64_t total_q, int units, int batch, int heads, int q_blocks, int max_context_len)
 {
     if (batch == 1 || batch > kMaxOrderedBatch || max_context_len < kPrefillShort) return 0;
@@ -225,6 +230,8 @@ __host__ inline int prefill_order(const PrefillPlan &plan, int head_dim, int64_t
     const int64_t blocks = total_q / (plan.blocks * units);
     // (dealt pair by pair, dies get alike only if every die gets the same heads)
     if ((int64_t)q_blocks * batch * heads <= slots || (heads % kXcds == 0 && (blocks + batch) * heads <= slots)) return 0;
+    const int reach = head_dim == 64 && max_context_len < 1024 ? 256 : std::min(max_context_len, 16 * 256);
+    if ((blocks + batch / 2) * heads * 256 > (int64_t)slots * reach) return 0;
     return blocks * heads >= 1536 ? 4 : 8;
 }
 

@@ -227,6 +227,19 @@ def test_single_sequences_and_calls_that_run_at_once_are_dealt(program, lens, q,
     assert plan_and_order(program, lens, q, 32, 8, 128) == ((16, 1, 1) if len(lens) == 1 else (8, 2, 0)) + (classes,)
 
 
+@pytest.mark.parametrize("lens,q,Hq,Hkv,d,classes", [
+    ([799] * 8, [780] * 8, 40, 8, 128, 0),            # 4 rounds of 256 workgroups, contexts worth 3
+    ([799] * 5, [780] * 5, 40, 8, 128, 8),            # 2.6
+    ([799] * 5, [780] * 5, 40, 8, 64, 0),             # head_dim 64, contexts under 1024: 1.7 rounds of 768, one at most
+    ([799] * 20, [20] * 19 + [400], 12, 12, 64, 8),   # 0.5; the bound on the queries leaves room for more
+    ([1024] * 5, [780] * 5, 40, 8, 64, 8),
+    ([8192] * 15, [2048] * 15, 32, 8, 128, 4),        # 15.2 rounds
+    ([8192] * 16, [2048] * 16, 32, 8, 128, 0),        # 16.3
+])
+def test_longest_first_only_where_the_rounds_are_few_for_the_context(program, lens, q, Hq, Hkv, d, classes):
+    assert plan_and_order(program, lens, q, Hq, Hkv, d)[3] == classes
+
+
 LONGEST_FIRST_ITEMS = {   # (sequences, longest): sequences of a group, the first that belongs to one; 4 KV heads
     (513, 1100): (256, 257),   # the batch's last sequences only
     (600, 2100): (256, 0),     # all of them, 88 + 256 + 256
