@@ -676,7 +676,7 @@ int paged_prefill_attention(const sd_shape *shape, const void *q, const int32_t 
     a.reciprocal = sd::reciprocal_of((unsigned)tokens_per_wg);
     a.q_blocks = (int32_t)(((int64_t)a.max_q_len + tokens_per_wg - 1) / tokens_per_wg);
     // (the reciprocal is exact below 2^24)
-    a.plan.order = total_q < 1 << 24 && a.max_context_len < 1 << 24 ? sd::prefill_order(a.plan, shape->head_dim, total_q, units, a.B, a.Hkv * a.HB, a.q_blocks, a.max_context_len) : 0;
+    a.plan.order = total_q < 1 << 24 && a.max_context_len < 1 << 24 ? sd::prefill_order(a.plan, shape->kv_dtype, shape->head_dim, total_q, units, a.B, a.Hkv * a.HB, a.q_blocks, a.max_context_len) : 0;
     if ((uint64_t)a.q_blocks * (uint64_t)a.B * (uint64_t)(a.Hkv * a.HB) > 0x7ffffff0ull) return SD_EUNSUPPORTED;
     hipEvent_t none[2] = {nullptr, nullptr};
     hipEvent_t *ev = timer ? &timer->ev[(size_t)timer->calls * 4] : none;

@@ -25,7 +25,7 @@ int main(int argc, char **argv)
     if (argc > 3) {
         const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[8]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
         const int max_q = std::min(atoll(argv[8]), atoll(argv[2])), tokens = p.blocks * atoi(argv[5]);
-        const int order = sd::prefill_order(p, atoi(argv[1]), atoll(argv[2]), atoi(argv[5]), atoi(argv[3]), atoi(argv[4]), (max_q + tokens - 1) / tokens, atoi(argv[6]));
+        const int order = sd::prefill_order(p, atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[5]), atoi(argv[3]), atoi(argv[4]), (max_q + tokens - 1) / tokens, atoi(argv[6]));
         printf("%d %d %d %d\n", p.blocks, p.split, p.phases, order);
         return 0;
     }
@@ -238,6 +238,12 @@ def test_single_sequences_and_calls_that_run_at_once_are_dealt(program, lens, q,
 ])
 def test_longest_first_only_where_the_rounds_are_few_for_the_context(program, lens, q, Hq, Hkv, d, classes):
     assert plan_and_order(program, lens, q, Hq, Hkv, d)[3] == classes
+
+
+@pytest.mark.parametrize("q,heads,d,kv_dtype,classes", [
+    (58, (8, 2), 128, "bf16", 0), (58, (8, 2), 64, "bf16", 0), (58, (8, 2), 128, "fp8", 8), (29, (28, 4), 64, "bf16", 0), (29, (32, 8), 64, "bf16", 8)])
+def test_two_block_workgroups_over_bf16_pools_are_ordered_only_where_a_head_keeps_its_die(program, q, heads, d, kv_dtype, classes):
+    assert plan_and_order(program, [6000, 6300] * 12, [q * 3 // 8, q] * 12, *heads, d, kv_dtype) == (2, 8, 0, classes)
 
 
 LONGEST_FIRST_ITEMS = {   # (sequences, longest): sequences of a group, the first that belongs to one; 4 KV heads
