@@ -224,12 +224,13 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
 // (without the calls of the next paragraph)
 // From 16 rounds on it is 1.00 at any length (16 of 8192 with 2048 each, 32/8 3283 : 3296 us), and at head_dim 64 under 1024 tokens from one round on.
 // In turn over the dies, the blocks of a (sequence, KV head) pair meet on one die only if the heads are a multiple of 8; otherwise several fetch the pair's K/V.  Workgroups of 2
-// blocks, 32 rows, over bf16 pools are bound by that: 24 sequences of 5.7 - 6.4 k, 22 - 58 queries, 8/2 heads fetch 583 MB instead of 156 and take 108 instead
-// of 72 us.  283 such calls .97, down to .58 (d = 64, 2 heads: .91).  Over fp8 pools, half the bytes, they gain: 1.24 and 1.23 with 2 and 4 heads (d = 64 1.19, 1.08).
+// blocks, 32 rows, over bf16 pools are bound by that where many sequences are walked at once: 24 of 5.7 - 6.4 k, 22 - 58 queries, 8/2 heads fetch 583 MB
+// instead of 156 and take 108 instead of 72 us.  1260 such calls, 2 and 4 heads, by sequences: under 12 1.14 (d = 64: 1.07), 12 - 19 .97 (1.00), 20 and more .86
+// (.84, down to .53).  Over fp8 pools, half the bytes, they gain: 1.24 and 1.23 with 2 and 4 heads (d = 64 1.19, 1.08).
 __host__ inline int prefill_order(const PrefillPlan &plan, int kv_dtype, int head_dim, int64_t total_q, int units, int batch, int heads, int q_blocks, int max_context_len)
 {
     if (batch == 1 || batch > kMaxOrderedBatch || max_context_len < kPrefillShort) return 0;
-    if (kv_dtype == 0 && plan.blocks == 2 && heads % kXcds != 0) return 0;
+    if (kv_dtype == 0 && plan.blocks == 2 && heads % kXcds != 0 && batch >= 12) return 0;
     // workgroups the chip holds at once (a compute unit one to three: registers, or LDS for the tiles)
     const int slots = 256 * (plan.split == 1 && plan.blocks == 8 ? (head_dim == 64 ? 3 : 2) : head_dim == 64 && plan.blocks != 2 ? 2 : 1);
     const int64_t blocks = total_q / (plan.blocks * units);

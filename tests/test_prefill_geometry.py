@@ -240,10 +240,11 @@ def test_longest_first_only_where_the_rounds_are_few_for_the_context(program, le
     assert plan_and_order(program, lens, q, Hq, Hkv, d)[3] == classes
 
 
-@pytest.mark.parametrize("q,heads,d,kv_dtype,classes", [
-    (58, (8, 2), 128, "bf16", 0), (58, (8, 2), 64, "bf16", 0), (58, (8, 2), 128, "fp8", 8), (29, (28, 4), 64, "bf16", 0), (29, (32, 8), 64, "bf16", 8)])
-def test_two_block_workgroups_over_bf16_pools_are_ordered_only_where_a_head_keeps_its_die(program, q, heads, d, kv_dtype, classes):
-    assert plan_and_order(program, [6000, 6300] * 12, [q * 3 // 8, q] * 12, *heads, d, kv_dtype) == (2, 8, 0, classes)
+@pytest.mark.parametrize("batch,q,heads,d,kv_dtype,classes", [
+    (24, 58, (8, 2), 128, "bf16", 0), (24, 58, (8, 2), 64, "bf16", 0), (24, 58, (8, 2), 128, "fp8", 8), (24, 29, (28, 4), 64, "bf16", 0),
+    (24, 29, (32, 8), 64, "bf16", 8), (12, 80, (8, 2), 128, "bf16", 0), (11, 90, (8, 2), 128, "bf16", 8), (11, 60, (28, 4), 64, "bf16", 8)])
+def test_two_block_workgroups_over_bf16_pools_of_many_sequences_are_ordered_only_where_a_head_keeps_its_die(program, batch, q, heads, d, kv_dtype, classes):
+    assert plan_and_order(program, [6000 + 20 * b for b in range(batch)], [q * (3 + b % 2 * 5) // 8 for b in range(batch)], *heads, d, kv_dtype) == (2, 8, 0, classes)
 
 
 LONGEST_FIRST_ITEMS = {   # (sequences, longest): sequences of a group, the first that belongs to one; 4 KV heads
