@@ -514,8 +514,9 @@ SD_DEV void leave_parts(const PrefillArgs &a, const PrefillRows &rows, typename 
 // were written to LDS and 400 - 700 in which 96 load instructions (V in 8-byte pieces) went through the address unit.  Loads straight into LDS
 // need no writes and 64 instructions; issued in one go at the start of the round they still hold up the wave's step (2900 cycles), so half of them
 // follow the K operands and half the V^T operands (2350).
+// (Cycles by time stamps, from builds that wrote them out.)
 // One sequence of 8192, 512 queries, 32/8 heads (kSplit 4): 98 -> 78 us; five sequences of 300 - 6000, 17 - 300 queries, 28/4
-// heads (4): 75 -> 60 us; 1740 random calls with kSplit 2: 0.91 of the time.
+// heads, cut to 4 blocks: 75 -> 60 us; 1740 random calls with kSplit 2: 0.91 of the time.
 template <int kSplit>
 __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs a)
 {

@@ -75,6 +75,8 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
     const int rest = pairs % kXcds, classes = prefill_classes(rest);
     return (unsigned)(pairs / kXcds * kXcds) * (unsigned)q_blocks + (rest ? (unsigned)(rest * classes) * (unsigned)((q_blocks + classes - 1) / classes) : 0u);
 }
+// 2^32 / tokens, rounded up: the high half of x times it is x / tokens for x < 2^24 and tokens <= 256 (a workgroup has at least two).
+__host__ inline uint32_t reciprocal_of(unsigned tokens) { return (uint32_t)((((uint64_t)1 << 32) + tokens - 1) / tokens); }
 // Longest first.  The order in which the query blocks of a batch start when the kernel looks at the lengths: by the class of their
 // range (eighths or quarters of the longest, counted in blocks), descending; within a class sequence after sequence, late blocks first, so that
 // neighbours still walk the same K/V together.  A block takes as long as its range, and a list that starts long items late ends late.  The
@@ -82,8 +84,6 @@ __host__ __device__ inline unsigned prefill_grid(int q_blocks, int pairs)
 //
 // `s` gives every sequence's query blocks and where its last one ends (in blocks, rounded up): sum(f) = sum of f(end, blocks) over the sequences,
 // top() = the largest end, find(f, m) = the sequence in which the running sum of f passes m, and that sum before it.
-// 2^32 / tokens, rounded up: the high half of x times it is x / tokens for x < 2^24 and tokens <= 256 (a workgroup has at least two).
-__host__ inline uint32_t reciprocal_of(unsigned tokens) { return (uint32_t)((((uint64_t)1 << 32) + tokens - 1) / tokens); }
 constexpr int kMaxOrderedBatch = 64;   // sequences whose ends and blocks one wave holds, one to a lane
 struct PrefillBlock {
     int b, block;   // block < 0: there is no k-th block
@@ -123,7 +123,7 @@ struct PrefillPlan {
 // perf/cases.py), each timed with every block size; the rule costs 1.8 % over the best size of each call on average, 136 calls take more than 1.1 and 64 more than 1.2 of it.
 // (8 or 4 blocks from 2048 tokens on, 800 more calls drawn for it: 0.99 of the time with 8 from 176 workgroups on, 0.94 from 192 to 255.  Which calls do better with 4 is a matter
 // of the context lengths, which are on the device: 1.08 where their mean is under three quarters of the longest, 0.91 otherwise.  5 sequences of 300 - 6000,
-// 17 - 300 queries, 28/4 heads have 220: 87 us with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
+// 17 - 300 queries, 28/4 heads have 220: 85 us with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
 // 4 / 2 blocks by workgroups of the larger block, half of its rows in use or more:
 //   workgroups              24 - 95   96 - 134   135 - 191   192 - 270   271 - 383   384 - 542   543 and more
 //   under 512 tokens   16    1.17      1.12        0.82        0.86        0.84        0.79       0.73
@@ -211,18 +211,17 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
 
 // Classes of a call's order, 0: dealt pair by pair.  A workgroup finds its block in about 0.8 us (the lengths come from memory, then
 // a hundred dependent instructions), so a call whose workgroups all run at once, or of a single sequence, is dealt: six sequences of 800 tokens, 40 queries,
-// 8/2 heads, d = 64 8.2 : 9.1 us, dealt : longest first.  So are short contexts, whose time goes into reading queries and writing rows as much as into their
-// ranges, and which do better with long and short blocks side by side: nine of 274 - 453, 64/8 heads, whole prompts 73 : 80.  Otherwise:
-//   5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads 89 : 75; 10 of 1.1 k - 1.8 k, 9 - 36 queries, 28/4 38 : 25; 10 of 8 k, 168 - 506
-//   queries, 16/2 415 : 244; 12 fp8 of 2.5 k - 8 k, 700 - 2048 queries, 32/8 1276 : 1225; 8 prompts of 1.5 k - 4 k, d = 64 413 : 403;
-//   eight classes do as well as 32; with 32 fewer blocks of a sequence run side by side, which costs large calls a tenth.
+// 8/2 heads, d = 64 7.7 : 8.5 us, dealt : longest first.  So are contexts under 512 tokens, whose time goes into reading queries and writing rows as much as into their
+// ranges, and which do better with long and short blocks side by side: nine of 274 - 453, 64/8 heads, whole prompts 65 : 76.  Otherwise:
+//   10 of 8 k, 168 - 506 queries, 16/2 heads 401 : 221; 12 fp8 of 2.5 k - 8 k, 700 - 2048 queries, 32/8 1255 : 1204; 8 prompts of 1.5 k - 4 k, d = 64 402 : 399.
+// Four or eight classes differ by 0.1 % over 2400 calls; with 32 fewer blocks of a sequence run side by side, which costs large calls a tenth.
 // What finding the block costs grows with the rounds of workgroups, what the order can gain with the walk of one of them.  3020 random calls (512 tokens to 16 k,
 // 2 to 64 sequences, heads as in perf/cases.py, bf16 and fp8), dealt over longest first, by context / 256 against the rounds, and how many lose and gain more than 8 %:
 //                     512 - 767          768 - 1023         1024 - 2047         2048 - 4095         4096 and more
 //   no more rounds    1.10 (14, 103)     1.09 (11, 71)      1.10 (23, 187)      1.11 (14, 233)      1.11 (23, 355)
 //   more               .97 (32, 3)        .99 (7, 7)        1.00 (1, 4)         1.01 (0, 2)
 // (without the calls of the next paragraph)
-// From 16 rounds on it is 1.00 at any length (16 of 8192 with 2048 each, 32/8 3283 : 3296 us), and at head_dim 64 under 1024 tokens from one round on.
+// From 16 rounds on it is 1.00 at any length (16 of 8192 with 2048 each, 32/8 3257 : 3264 us with four classes, 3287 with eight), and at head_dim 64 under 1024 tokens from one round on.
 // In turn over the dies, the blocks of a (sequence, KV head) pair meet on one die only if the heads are a multiple of 8; otherwise several fetch the pair's K/V.  Workgroups of 2
 // blocks, 32 rows, over bf16 pools are bound by that where many sequences are walked at once: 24 of 5.7 - 6.4 k, 22 - 58 queries, 8/2 heads fetch 583 MB
 // instead of 156 and take 108 instead of 72 us.  1260 such calls, 2 and 4 heads, by sequences: under 12 1.14 (d = 64: 1.07), 12 - 19 .97 (1.00), 20 and more .86
@@ -257,6 +256,7 @@ __host__ __device__ inline int shared_slots(int sh, int chunk) { return (sh + ch
 //   16 x 16 branches of 64 - 4096, 32/8 458 : 434 : 432                1000 bf16 of 100 - 4000, 16/2 364 : 356 : 350
 //   1024 fp8 of 64 - 1024, 64/8 221 : 219 : 228                        600 bf16 of 100 - 2000, 32/8 418 : 409 : 409
 // Batches whose workgroups all run at once, or under 1024 tokens (300 us of short workgroups gain nothing), keep their order.
+// 150 random decode and prefix calls that are ordered: 1.02 times as fast as in batch order, one loses more than 3 %, 49 gain that much.
 constexpr int kMaxOrderedItems = 256;   // sequences whose lengths a wave holds, four to a lane
 constexpr int kWorthOrdering = 1024;
 struct SplitOrder {
