@@ -33,27 +33,30 @@
 
 namespace sd {
 
-// Tokens of sequence b that its group shares: whole pages, never more than the
+// Tokens of a sequence of L that its group shares, of the `stated` ones: whole pages, never more than the
 // sequence has and never more than the host-side bound.
-SD_DEV int shared_tokens(const SplitArgs &a, int b)
-{
-    const int L = max(0, min(a.context_lens[b], a.max_context_len));
-    return max(0, min(min(a.shared_len[b], a.max_shared_len), L)) & ~(kPage - 1);
-}
+SD_DEV int shared_tokens(const SplitArgs &a, int L, int stated) { return max(0, min(min(stated, a.max_shared_len), L)) & ~(kPage - 1); }
+SD_DEV int shared_tokens(const SplitArgs &a, int b) { return shared_tokens(a, max(0, min(a.context_lens[b], a.max_context_len)), a.shared_len[b]); }
 
-// The k-th of n sequences with the longest first: by the class (eighths of the longest) of the tokens that key(i) says sequence i brings,
+// The k-th of n sequences with the longest first: by the class (eighths of the longest) of the tokens that key(load(i)) says sequence i brings,
 // descending, in order within a class.  Every wave works it out for itself, 64 sequences to a register, counted by ballots; about 1 us that the
 // other workgroup of the compute unit mostly hides, but not from workgroups of a few tiles: if none of the n is long, the order stays.
-template <class Key>
-SD_DEV int longest_first(int sequences, int k, int lane, Key key)
+// (All loads are on their way before the first is looked at: behind the tile loads of the workgroup beside it each trip takes about 2 us,
+// and four of them in a row made a workgroup's start 9 us long instead of 5.5.)
+template <class Load, class Key>
+SD_DEV int longest_first(int sequences, int k, int lane, Load load, Key key)
 {
     constexpr int kPer = kMaxOrderedItems / 64;
     const int per = (sequences + 63) / 64;
+    decltype(load(0)) raw[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) raw[i] = load(min(i * 64 + lane, sequences - 1));
+    __builtin_amdgcn_sched_barrier(0);
     int x[kPer], top = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        x[i] = -1;   // no sequence
-        if (i < per && i * 64 + lane < sequences) x[i] = key(i * 64 + lane);
+        const int tokens = key(raw[i]);
+        x[i] = i * 64 + lane < sequences ? tokens : -1;   // -1: no sequence
     }
 #pragma unroll
     for (int i = 0; i < kPer; ++i) top = max(top, x[i]);
@@ -228,10 +231,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     const int from_end = a.grid_chunks - 1 - (int)(item / (Hv * a.B));
     if (from_end == 0 && b >= a.order.from) {   // last (or only) chunks are of all lengths; groups are counted from the batch's end
         const int group_end = a.B - (a.B - 1 - b) / a.order.group * a.order.group, first = max(a.order.from, group_end - a.order.group);
-        b = first + longest_first(group_end - first, b - first, lane, [&](int s) {
-            const int own = max(0, min(a.context_lens[first + s], a.max_context_len)) - (GROUPS ? shared_tokens(a, first + s) : 0);
-            return own <= a.chunk_tokens ? own : (own - 1) % a.chunk_tokens + 1;
-        });
+        b = first + longest_first(group_end - first, b - first, lane,
+            [&](int s) { return int2{a.context_lens[first + s], GROUPS ? a.shared_len[first + s] : 0}; },
+            [&](int2 stated) {
+                const int L = max(0, min(stated.x, a.max_context_len)), own = L - (GROUPS ? shared_tokens(a, L, stated.y) : 0);
+                return own <= a.chunk_tokens ? own : (own - 1) % a.chunk_tokens + 1;
+            });
     }
 
     const int L = max(0, min(a.context_lens[b], a.max_context_len));
@@ -300,24 +305,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
 
     // merge the four waves; some wave saw a token, so the max is finite
     const int64_t row0 = (int64_t)b * a.Hq + hb.head0;
-    for (int idx = tid; idx < hb.rows * D; idx += kWaves * 64) {
-        const int hn = idx / D, dd = idx % D;
+    for (int idx = tid; idx < hb.rows * (D / 4); idx += kWaves * 64) {
+        const int hn = idx / (D / 4), dd = idx % (D / 4) * 4;
         float M = s_m[0][hn];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s_m[w][hn]);
-        float num = 0.f, den = 0.f;
+        f32x4 num = {0, 0, 0, 0};
+        float den = 0.f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             const float wt = __builtin_amdgcn_exp2f(s_m[w][hn] - M);
-            num += wt * s_acc[w][hn][dd];
+            num += wt * *reinterpret_cast<const f32x4 *>(&s_acc[w][hn][dd]);
             den += wt * s_l[w][hn];
         }
         if (a.out_direct) {  // the only chunk of its sequence: this is the result
-            a.out_direct[(row0 + hn) * D + dd] = num / den;
+            store_through(a.out_direct + row0 * D, hb.rows * D * 4, idx * 16, num / den);
             continue;
         }
         const int64_t slot = (row0 + hn) * a.S + c;
-        a.ws_acc[slot * D + dd] = num;
+        *reinterpret_cast<f32x4 *>(a.ws_acc + slot * D + dd) = num;
         if (dd == 0) {
             a.ws_m[slot] = M;
             a.ws_l[slot] = den;

@@ -72,6 +72,16 @@ SD_DEV T kv_load(const T *p)
     return *p;
 }
 
+// 16 bytes per lane to byte `offset` of the `bytes` at `dst` (wave-uniform), written through the L2 of the die.  Memory that is being read
+// at its full rate pays for every change of direction: 33 MB of finished rows that left the L2s one by one, as streaming reads displaced them, cost
+// a launch that reads 5 GB 84 us (773 : 690 us with the stores taken out); written through as they come 62 (752).  Partial results, which another
+// launch reads at once, are better kept in the caches (shared-prefix step 432 : 444 us).
+SD_DEV void store_through(float *dst, int bytes, int offset, f32x4 x)
+{
+    constexpr int kSc1 = 16;   // cache policy bit sc1
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), __builtin_amdgcn_make_buffer_rsrc(dst, 0, bytes, 0x00027000), offset, 0, kSc1);
+}
+
 // What a decode or prefill kernel only reads and nothing running beside it writes (the block table,
 // the fp8 scales) is read through the constant address space: that pins wave-uniform reads to scalar
 // loads whatever else the kernel stores.  As vector loads they would queue behind the tile loads,
