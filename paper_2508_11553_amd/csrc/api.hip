@@ -540,6 +540,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     if (group_items + plain_items > 0x7fffffffull) return SD_EUNSUPPORTED;
     sa.group_items = (uint32_t)group_items;
     sa.max_shared_len = max_shared_len;
+    sa.store_through = direct && sd::stores_through((int64_t)shape->batch * shape->num_q_heads * shape->head_dim * 4);
     sa.order = sd::split_order(shape->batch, sa.Hkv * sa.HB, std::min(shape->max_context_len, chunk));
     sa.out_direct = direct ? out : nullptr;
     const bool in_place = direct && k_new;

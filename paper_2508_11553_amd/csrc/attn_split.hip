@@ -319,7 +319,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
             den += wt * s_l[w][hn];
         }
         if (a.out_direct) {  // the only chunk of its sequence: this is the result
-            store_through(a.out_direct + row0 * D, hb.rows * D * 4, idx * 16, num / den);
+            if (a.store_through)
+                store_through(a.out_direct + row0 * D, hb.rows * D * 4, idx * 16, num / den);
+            else
+                *reinterpret_cast<f32x4 *>(a.out_direct + (row0 + hn) * D + dd) = num / den;
             continue;
         }
         const int64_t slot = (row0 + hn) * a.S + c;

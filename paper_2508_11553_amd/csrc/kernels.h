@@ -270,6 +270,12 @@ __host__ inline SplitOrder split_order(int batch, int heads, int longest)   // l
     if ((int64_t)batch * heads <= 512 || longest < kWorthOrdering) return SplitOrder{group, batch};
     return SplitOrder{group, deep || batch < group ? 0 : batch - group};
 }
+// Whether a launch writes its finished rows through the L2s.  Few rows are better left in them (4 MB each), from where they reach memory after the
+// reads: 16 - 200 sequences of 125 - 1000 tokens, 32/8 heads, up to 3.3 MB of rows lose 2 - 5 % written through, 500 (8.2 MB) +1 %, over fp8 0, 500 of
+// 62 - 500 -1 %.  Many are displaced by what is read, one line at a time: 800 of 600 - 4096, 28/4 (11.5 MB) 601 : 586 us, 1000 of 125 - 1000, 32/8
+// (16.8 MB) 392 : 382, 1024 fp8 of 512 - 4096, 64/8 (33.5 MB) 780 : 751.
+__host__ inline bool stores_through(int64_t bytes) { return bytes >= 10 << 20; }
+
 // Arguments of the split-K pass (by value, lives in kernel-argument memory).
 struct SplitArgs {
     const uint16_t *q;           // [B][Hq][D] bf16
@@ -302,6 +308,7 @@ struct SplitArgs {
     int32_t max_shared_len;      // host-known bound on shared_len[]; larger values are clamped to it
     int32_t grid_chunks;         // chunk slots the plain part of the grid spans (S, or S-1 without groups)
     SplitOrder order;            // of the sequences' last chunks
+    int32_t store_through;       // finished rows are written through the L2 (stores_through)
 };
 
 // Hand-over inside a workgroup.  The four waves of a workgroup walk neighbouring pieces (ranges 4i ..
