@@ -540,7 +540,9 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     if (group_items + plain_items > 0x7fffffffull) return SD_EUNSUPPORTED;
     sa.group_items = (uint32_t)group_items;
     sa.max_shared_len = max_shared_len;
-    sa.store_through = direct && sd::stores_through((int64_t)shape->batch * shape->num_q_heads * shape->head_dim * 4);
+    const int64_t out_bytes = (int64_t)shape->batch * shape->num_q_heads * shape->head_dim * 4;
+    sa.store_through = direct && sd::stores_through(out_bytes);
+    sa.store_windows = direct && sd::stores_in_windows(out_bytes, shape->max_context_len, 2 * shape->head_dim * (shape->kv_dtype == SD_BF16 ? 2 : 1));
     sa.order = sd::split_order(shape->batch, sa.Hkv * sa.HB, std::min(shape->max_context_len, chunk));
     sa.out_direct = direct ? out : nullptr;
     const bool in_place = direct && k_new;

@@ -303,6 +303,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     P::store_acc(st, &s_acc[wave][n][0], qd);
     __syncthreads();
 
+    // (the last round of workgroups would only end later)
+    if (a.store_windows && (t1 - t0) * (2 * P::kTileBytes / kPage) >= kWorthAWindow && gridDim.x - blockIdx.x > 512u) await_store_window();
+
     // merge the four waves; some wave saw a token, so the max is finite
     const int64_t row0 = (int64_t)b * a.Hq + hb.head0;
     for (int idx = tid; idx < hb.rows * (D / 4); idx += kWaves * 64) {

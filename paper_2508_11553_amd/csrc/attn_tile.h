@@ -82,6 +82,13 @@ SD_DEV void store_through(float *dst, int bytes, int offset, f32x4 x)
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), __builtin_amdgcn_make_buffer_rsrc(dst, 0, bytes, 0x00027000), offset, 0, kSc1);
 }
 
+// Waits for the next window of the clock in which rows are stored (stores_in_windows): 0.64 us of every 6.4 on the 100 MHz clock
+// that all dies share.
+SD_DEV void await_store_window()
+{
+    while ((unsigned)__builtin_amdgcn_s_memrealtime() % 640u >= 64u) __builtin_amdgcn_s_sleep(1);
+}
+
 // What a decode or prefill kernel only reads and nothing running beside it writes (the block table,
 // the fp8 scales) is read through the constant address space: that pins wave-uniform reads to scalar
 // loads whatever else the kernel stores.  As vector loads they would queue behind the tile loads,

@@ -275,6 +275,17 @@ __host__ inline SplitOrder split_order(int batch, int heads, int longest)   // l
 // 62 - 500 -1 %.  Many are displaced by what is read, one line at a time: 800 of 600 - 4096, 28/4 (11.5 MB) 601 : 586 us, 1000 of 125 - 1000, 32/8
 // (16.8 MB) 392 : 382, 1024 fp8 of 512 - 4096, 64/8 (33.5 MB) 780 : 751.
 __host__ inline bool stores_through(int64_t bytes) { return bytes >= 10 << 20; }
+// Whether its workgroups moreover store in the same windows of the clock.  Memory that reads at its full rate turns around for every few lines that are
+// written at any time; rows that all arrive in the same 0.64 of every 6.4 us are written together.  (A read-only walk of 4 GB with 32 MB of
+// stores: 604 us without them, 687 plain, 666 written through, 640 and 622 in windows every 20 and 50 us.)  A workgroup waits 3 us for the next window on average,
+// which costs nothing as long as the other one of its compute unit reads meanwhile and walks last much longer: us per step without : with windows
+//   1024 fp8 of 512 - 4096, 64/8 heads 748 : 726    1024 fp8 of 256 - 2048, 64/8 398 : 381    1024 bf16 of 125 - 1000, 64/8 396 : 378
+//   1000 bf16 of 125 - 1000, 32/8 372 : 367         800 bf16 of 512 - 4096, 28/4 578 : 577    1000 bf16 of 62 - 500, 32/8 197 : 199
+//   1000 fp8 of 50 - 400, 32/8 100 : 139 if every workgroup waits
+// So the longest sequence may have 384 KB of K/V per head (fp8 of up to 1280 gain 0 - 1 %, bf16 of up to 500 lose as much), and only workgroups that walked 128 KB wait.  Periods of 5 to 13 us and windows of
+// a tenth to a quarter of them differ by 1 %.
+constexpr int kWorthAWindow = 128 << 10;   // bytes of K/V
+__host__ inline bool stores_in_windows(int64_t bytes, int longest, int token_bytes) { return stores_through(bytes) && (int64_t)longest * token_bytes >= 384 << 10; }
 
 // Arguments of the split-K pass (by value, lives in kernel-argument memory).
 struct SplitArgs {
@@ -309,6 +320,7 @@ struct SplitArgs {
     int32_t grid_chunks;         // chunk slots the plain part of the grid spans (S, or S-1 without groups)
     SplitOrder order;            // of the sequences' last chunks
     int32_t store_through;       // finished rows are written through the L2 (stores_through)
+    int32_t store_windows;       // and in windows of the clock (stores_in_windows)
 };
 
 // Hand-over inside a workgroup.  The four waves of a workgroup walk neighbouring pieces (ranges 4i ..
