@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     __syncthreads();
 
     // (the last round of workgroups would only end later)
-    if (a.store_windows && (t1 - t0) * (2 * P::kTileBytes / kPage) >= kWorthAWindow && gridDim.x - blockIdx.x > 512u) await_store_window();
+    if (!GROUPS && a.store_windows && (t1 - t0) * (2 * P::kTileBytes / kPage) >= kWorthAWindow && gridDim.x - blockIdx.x > 512u) await_store_window();
 
     // merge the four waves; some wave saw a token, so the max is finite
     const int64_t row0 = (int64_t)b * a.Hq + hb.head0;
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
             num += wt * *reinterpret_cast<const f32x4 *>(&s_acc[w][hn][dd]);
             den += wt * s_l[w][hn];
         }
-        if (a.out_direct) {  // the only chunk of its sequence: this is the result
+        if (!GROUPS && a.out_direct) {  // the only chunk of its sequence: this is the result
             if (a.store_through)
                 store_through(a.out_direct + row0 * D, hb.rows * D * 4, idx * 16, num / den);
             else
