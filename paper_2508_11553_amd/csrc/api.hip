@@ -674,10 +674,13 @@ int paged_prefill_attention(const sd_shape *shape, const void *q, const int32_t 
     a.max_q_len = max_q_len < total_q ? max_q_len : total_q;
     const int units = sd::units_per_block(a.G);
     a.plan = sd::prefill_plan(shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
-    const int tokens_per_wg = a.plan.blocks * units;
+    a.plan.on_device = total_q < 1 << 23 && a.max_context_len < 1 << 23 &&
+                       sd::prefill_on_device(a.plan, shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
+    const int tokens_per_wg = (a.plan.on_device ? 8 : a.plan.blocks) * units;
     a.round_up = tokens_per_wg - 1;
     a.reciprocal = sd::reciprocal_of((unsigned)tokens_per_wg);
-    a.q_blocks = (int32_t)(((int64_t)a.max_q_len + tokens_per_wg - 1) / tokens_per_wg);
+    const int tokens_per_slot = a.plan.on_device ? tokens_per_wg / 2 : tokens_per_wg;   // (a grid for 4 blocks)
+    a.q_blocks = (int32_t)(((int64_t)a.max_q_len + tokens_per_slot - 1) / tokens_per_slot);
     // (the reciprocal is exact below 2^24)
     a.plan.order = total_q < 1 << 24 && a.max_context_len < 1 << 24 ? sd::prefill_order(a.plan, shape->kv_dtype, shape->head_dim, total_q, units, a.B, a.Hkv * a.HB, a.q_blocks, a.max_context_len) : 0;
     if ((uint64_t)a.q_blocks * (uint64_t)a.B * (uint64_t)(a.Hkv * a.HB) > 0x7ffffff0ull) return SD_EUNSUPPORTED;

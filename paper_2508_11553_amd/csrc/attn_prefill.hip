@@ -33,23 +33,31 @@
 
 namespace sd {
 
-// The sequences of a batch as prefill_pick asks for them, one to a lane.
+// The sequences of a batch as prefill_pick asks for them, one to a lane, cut into workgroups' tokens or (halves = 1) half of them.
 struct WaveSequences {
+    int nq, L;          // 0 queries: nothing to do
     int end, blocks;
-    SD_DEV WaveSequences(const PrefillArgs &a, int lane) : end(0), blocks(0)
+    int round_up;
+    uint32_t reciprocal;
+    SD_DEV WaveSequences(const PrefillArgs &a, int lane) : nq(0), L(0), round_up(a.round_up), reciprocal(a.reciprocal)
     {
-        int qs = 0, next = 0, L = 0;
-        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], L = a.context_lens[lane];
-        {
-            const int nq = min(next - qs, a.max_q_len);
-            L = max(0, min(L, a.max_context_len));
-            // rounded up; a.reciprocal = 2^32 / tokens of a workgroup, rounded up: exact below 2^24
-            if (lane < a.B && qs >= 0 && nq > 0 && (int64_t)qs + nq <= a.total_q) {
-                blocks = (int)__umulhi((unsigned)(nq + a.round_up), a.reciprocal);
-                end = (int)__umulhi((unsigned)(L + a.round_up), a.reciprocal);
-            }
-        }
+        int qs = 0, next = 0, stored = 0;
+        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], stored = a.context_lens[lane];
+        const int n = min(next - qs, a.max_q_len);
+        if (lane < a.B && qs >= 0 && n > 0 && (int64_t)qs + n <= a.total_q) nq = n, L = max(0, min(stored, a.max_context_len));
+        cut(0);
     }
+    // rounded up; reciprocal = 2^32 / tokens of a workgroup, rounded up: exact below 2^24
+    SD_DEV int count(int tokens, int halves) const { return (int)__umulhi((unsigned)((tokens << halves) + round_up), reciprocal); }
+    SD_DEV void cut(int halves)
+    {
+        blocks = nq > 0 ? count(nq, halves) : 0;
+        end = nq > 0 ? count(L, halves) : 0;
+    }
+    // for prefill_prefers_four
+    SD_DEV int longest() const { return wave_max(nq > 0 ? L : 0); }
+    template <class F>
+    SD_DEV int total(F f) const { return __builtin_amdgcn_readlane(wave_scan(nq > 0 ? f(nq, L) : 0), 63); }
     SD_DEV int top() const { return wave_max(end); }
     template <class F>
     SD_DEV int sum(F f) const { return __builtin_amdgcn_readlane(wave_scan(f(end, blocks)), 63); }
@@ -81,8 +89,6 @@ struct PrefillRows {
     SD_DEV bool find(const PrefillArgs &a, int groups, int group, int blocks)
     {
         const int Hv = a.Hkv * a.HB;
-        tpb = units_per_block(a.G);
-        const int tpw = blocks * tpb;   // query tokens per wave
         int seq, head, jb;
         if (a.plan.order) {   // head fastest
             const PrefillBlock at = prefill_pick(WaveSequences(a, threadIdx.x & 63), (int)(blockIdx.x / Hv), a.plan.order);
@@ -91,7 +97,13 @@ struct PrefillRows {
             const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
             seq = item.pair / Hv, head = item.pair % Hv, jb = a.q_blocks - 1 - item.block;
         }
-        if (jb < 0) return false;
+        return jb >= 0 && take(a, seq, head, jb, groups, group, blocks);
+    }
+    // The same, in block jb of a sequence and (virtual) head.
+    SD_DEV bool take(const PrefillArgs &a, int seq, int head, int jb, int groups, int group, int blocks)
+    {
+        tpb = units_per_block(a.G);
+        const int tpw = blocks * tpb;   // query tokens per wave
         b = seq;
         hb = head_block(head, a.G, a.HB);
         qs = a.q_start[b];
@@ -506,7 +518,7 @@ SD_DEV void leave_parts(const PrefillArgs &a, const PrefillRows &rows, typename 
                              [&](int at, int word) { return *PartImage<P, NB>::word(image_of(at / (NB * 16)), at % (NB * 16), word); });
 }
 
-// Calls over bf16 pools that do not fill the chip with blocks of 16 (head_dim 128): 8 waves of two column blocks each, kSplit neighbouring waves own the
+// Calls over bf16 pools that do not fill the chip with blocks of 16 (head_dim 128): 8 waves of two column blocks each, kSplit waves own the
 // same rows and every kSplit-th tile; a round is kSplit tiles, a tile step per wave.
 //
 // What bounds it is how a round's parts line up: with one step per wave between barriers nothing covers the time a wave spends on its own loads.
@@ -517,23 +529,36 @@ SD_DEV void leave_parts(const PrefillArgs &a, const PrefillRows &rows, typename 
 // (Cycles by time stamps, from builds that wrote them out.)
 // One sequence of 8192, 512 queries, 32/8 heads (kSplit 4): 98 -> 78 us; five sequences of 300 - 6000, 17 - 300 queries, 28/4
 // heads, cut to 4 blocks: 75 -> 60 us; 1740 random calls with kSplit 2: 0.91 of the time.
+// kSplit 0: the size of the workgroups is chosen here, from the lengths (prefill_prefers_four).  (A kernel of 4 blocks alone is 0.3 us faster in calls of 15 us.)
 template <int kSplit>
 __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs a)
 {
     constexpr int D = 128, NB = 2, kW = 8, S = D / 32;
     typedef Bf16Path<D> P;
     typedef RowSlot<D> Slot;
-    constexpr int kGroups = kW / kSplit;
-    constexpr int kBuf = kSplit * Slot::kBytes;
-    constexpr int kMore = kSplit == 2 ? kBuf : 16;
+    // Two tiles to an array; where workgroups only ever have 4 blocks, the tiles of both sides (below) share one, which halves the code (small
+    // calls, which fetch it as they start, 0.3 us).
+    constexpr int kBuf = (kSplit == 4 ? 4 : 2) * Slot::kBytes, kMore = kSplit == 4 ? 16 : kBuf;
     __shared__ __attribute__((aligned(16))) char buf0[kBuf], buf1[kBuf], buf2[kMore], buf3[kMore];
     __shared__ float ms[kW * NB * 16], ls[kW * NB * 16];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int group = wave / kSplit, part = wave % kSplit;
+    // 8 blocks: four groups of two waves; 4 blocks: waves 0, 1, 4, 5 and 2, 3, 6, 7
+    const int group_of_eight = wave >> 1, group_of_four = wave >> 1 & 1;
+    bool four = kSplit == 4;
     PrefillRows rows;
-    if (!rows.find(a, kGroups, group, NB)) return;
+    if constexpr (kSplit == 0) {
+        const int Hv = a.Hkv * a.HB;
+        WaveSequences sequences(a, lane);
+        four = prefill_prefers_four(sequences, Hv, a.round_up + 1);
+        if (four) sequences.cut(1);
+        const PrefillBlock at = prefill_pick(sequences, (int)(blockIdx.x / Hv), 8);
+        if (at.block < 0) return;
+        if (!rows.take(a, at.b, blockIdx.x % Hv, at.block, four ? 2 : 4, four ? group_of_four : group_of_eight, NB)) return;
+    } else {
+        if (!rows.find(a, kW / kSplit, four ? group_of_four : group_of_eight, NB)) return;
+    }
     int row_end[NB];
     u32x4 qop[NB][S];
     typename P::ParkedState st[NB];
@@ -541,77 +566,67 @@ __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs
 
     const PageRows<D> pages(a, rows, lane);
     constexpr int kLoads = PageRows<D>::kLoads;
-    auto attend = [&](const u32x4 (&ka)[S], const u32x4 (&kb)[S], auto v_of, int tile, auto masked) {
-        P::template attend_fetched<NB, decltype(masked)::value, false>(ka, kb, v_of, qop, st, a.scale_log2e, tile * kTileTokens, lane, row_end, true,
-                                                                      nullptr, rows.first_end, rows.tpb);
-    };
-    const int rounds = (pages.ntiles + kSplit - 1) / kSplit;
-    constexpr int kKinds = kSplit == 4 ? 2 : 1;   // K and V of a page, or one of them
-    const int my_tile = kSplit == 4 ? wave >> 1 : wave >> 2, my_page = kSplit == 4 ? wave & 1 : wave >> 1 & 1, my_kind = kSplit == 4 ? 0 : wave & 1;
-    const int my_at = my_tile * Slot::kBytes + my_page * Slot::kPageBytes;
-    auto page_of = [&](int rd) { return pages.id(kSplit * min(rd, rounds - 1) + my_tile, my_page); };
-    // K and V of the page (kSplit 4), or the first and second half of one of them
-    auto bring_half = [&](int half, char *buf, int page) {
-        if constexpr (kKinds == 2)
-            pages.bring(half, page, buf, my_at + half * 2 * Slot::kPageBytes);
-        else
-            pages.bring(my_kind, page, buf, my_at + my_kind * 2 * Slot::kPageBytes, half * kLoads / 2, kLoads / 2);
-    };
-    auto bring_round = [&](char *buf, int page) { bring_half(0, buf, page); bring_half(1, buf, page); };
-    auto clean = [&](char *buf, int rd) {
-        if (kKinds == 2 || my_kind) pages.clean(buf, my_at + 2 * Slot::kPageBytes, (kSplit * rd + my_tile) * kTileTokens + my_page * kPage);
-    };
-    constexpr int kPer = kKinds * kLoads;
-    constexpr int kAhead = kSplit == 4 ? 1 : 3;
-    auto turn = [&](int rd, char *cur, char *next, char *fill, int page) {
-        const int t0 = kSplit * rd * kTileTokens;
-        const int j_end = rows.active ? min(kSplit, (rows.max_end - t0 + kTileTokens - 1) / kTileTokens) : 0;
-        const int j_plain = max(0, min(j_end, (rows.min_end - t0) / kTileTokens));
-        u32x4 ka[S], kb[S];
-        Slot::fetch_k(cur, part * Slot::kBytes, lane, ka, kb);
-        __builtin_amdgcn_sched_barrier(0);
-        bring_half(0, fill, page);
-        auto step = [&](int j, auto masked) {
-            attend(ka, kb, [&](int k) {
-                const u32x4 v = Slot::v_operand(cur, part * Slot::kBytes, k, lane);
-                if (k == D / 16 - 1) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    bring_half(1, fill, page);
-                }
-                return v;
-            }, kSplit * rd + j, masked);
+    const int part = wave & 1;   // the tile of a pair that this wave attends
+    // The step over tile first + part, whose rows lie at buf + at; the V^T operands are followed by behind().
+    auto step = [&](const char *buf, int at, const u32x4 (&ka)[S], const u32x4 (&kb)[S], int first, auto behind) {
+        auto attend = [&](int tile, auto masked) {
+            P::template attend_fetched<NB, decltype(masked)::value, false>(
+                ka, kb, [&](int k) {
+                    const u32x4 v = Slot::v_operand(buf, at, k, lane);
+                    if (k == D / 16 - 1) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        behind();
+                    }
+                    return v;
+                }, qop, st, a.scale_log2e, tile * kTileTokens, lane, row_end, true, nullptr, rows.first_end, rows.tpb);
         };
+        // (Loops of one turn or none: of two branches the compiler joins what they have in common ahead of them, the operands' reads above all, and spills.)
+        const int t0 = first * kTileTokens;
+        const int j_end = rows.active ? min(2, (rows.max_end - t0 + kTileTokens - 1) / kTileTokens) : 0;
+        const int j_plain = max(0, min(j_end, (rows.min_end - t0) / kTileTokens));
         int j = part;
 #pragma unroll 1
-        for (; j < j_plain; j += kSplit) step(j, std::false_type{});
+        for (; j < j_plain; j += 2) attend(first + j, std::false_type{});
 #pragma unroll 1
-        for (; j < j_end; j += kSplit) step(j, std::true_type{});
-        if (part >= j_end) bring_half(1, fill, page);
-        wait_loads<(kAhead - 1) * kPer>();   // round rd + 1 has arrived
-        clean(next, rd + 1);
-        wait_lds();
-        phase_barrier();
+        for (; j < j_end; j += 2) attend(first + j, std::true_type{});
+        if (part >= j_end) behind();
     };
-    if (rounds > 0) {
-        if constexpr (kSplit == 4) {
-            bring_round(buf0, page_of(0));
-            int page = page_of(1);
-            wait_loads<0>();
-            clean(buf0, 0);
+    auto image_of = [&](int w) {
+        constexpr int kPer = kBuf / PartImage<P, NB>::kBytes;
+        const int b = w / kPer;
+        return (b == 0 ? buf0 : b == 1 ? buf1 : b == 2 ? buf2 : buf3) + w % kPer * PartImage<P, NB>::kBytes;
+    };
+
+    // A round is two tiles in one of the four arrays, asked for three rounds ahead; a wave brings half of a tile's K or V.
+    auto eight = [&] {
+        const int rounds = (pages.ntiles + 1) / 2;
+        const int my_tile = wave >> 2, my_page = wave >> 1 & 1, my_kind = wave & 1;
+        const int my_at = my_tile * Slot::kBytes + my_page * Slot::kPageBytes;
+        auto page_of = [&](int rd) { return pages.id(2 * min(rd, rounds - 1) + my_tile, my_page); };
+        auto bring_half = [&](int half, char *buf, int page) {
+            pages.bring(my_kind, page, buf, my_at + my_kind * 2 * Slot::kPageBytes, half * kLoads / 2, kLoads / 2);
+        };
+        auto bring_round = [&](char *buf, int page) { bring_half(0, buf, page); bring_half(1, buf, page); };
+        auto clean = [&](char *buf, int rd) {
+            if (my_kind) pages.clean(buf, my_at + 2 * Slot::kPageBytes, (2 * rd + my_tile) * kTileTokens + my_page * kPage);
+        };
+        auto turn = [&](int rd, char *cur, char *next, char *fill, int page) {
+            u32x4 ka[S], kb[S];
+            Slot::fetch_k(cur, part * Slot::kBytes, lane, ka, kb);
+            __builtin_amdgcn_sched_barrier(0);
+            bring_half(0, fill, page);
+            step(cur, part * Slot::kBytes, ka, kb, 2 * rd, [&] { bring_half(1, fill, page); });
+            wait_loads<2 * kLoads>();   // round rd + 1 has arrived
+            clean(next, rd + 1);
             wait_lds();
             phase_barrier();
-            for (int rd = 0;;) {
-                { const int after = page_of(rd + 2); turn(rd, buf0, buf1, buf1, page); page = after; }
-                if (++rd == rounds) break;
-                { const int after = page_of(rd + 2); turn(rd, buf1, buf0, buf0, page); page = after; }
-                if (++rd == rounds) break;
-            }
-        } else {
+        };
+        if (rounds > 0) {
             bring_round(buf0, page_of(0));
             bring_round(buf1, page_of(1));
             bring_round(buf2, page_of(2));
             int page = page_of(3);
-            wait_loads<2 * kPer>();
+            wait_loads<2 * kLoads>();
             clean(buf0, 0);
             wait_lds();
             phase_barrier();
@@ -625,15 +640,63 @@ __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs
                 { const int after = page_of(rd + 4); turn(rd, buf3, buf0, buf2, page); page = after; }
                 if (++rd == rounds) break;
             }
+            wait_loads<0>();   // no load may land in what follows
         }
-        wait_loads<0>();   // no load may land in what follows
-    }
-    constexpr int kPerBuf = kBuf / PartImage<P, NB>::kBytes;
-    leave_parts<P, NB, kSplit>(a, rows, st, wave, lane, ms, ls, [&](int w) {
-        const int b = w / kPerBuf;
-        char *buf = kSplit == 2 ? (b == 0 ? buf0 : b == 1 ? buf1 : b == 2 ? buf2 : buf3) : (b == 0 ? buf0 : buf1);
-        return buf + w % kPerBuf * PartImage<P, NB>::kBytes;
-    });
+        leave_parts<P, NB, 2>(a, rows, st, wave, lane, ms, ls, image_of);
+    };
+    // Waves 0 - 3 take tiles 0, 1, 4, 5, ... through two of the arrays, waves 4 - 7 tiles 2, 3, 6, 7, ... through the others; a wave brings K and V of one
+    // page per round, a round ahead.
+    auto by_four = [&] {
+        const int rounds = (pages.ntiles + 3) / 4;
+        const int side = wave >> 2, my_tile = wave >> 1 & 1, my_page = wave & 1;
+        const int side_at = kSplit == 4 ? side * 2 * Slot::kBytes : 0, my_at = side_at + my_tile * Slot::kBytes + my_page * Slot::kPageBytes;
+        auto page_of = [&](int rd) { return pages.id(4 * min(rd, rounds - 1) + 2 * side + my_tile, my_page); };
+        auto bring_half = [&](int half, char *buf, int page) { pages.bring(half, page, buf, my_at + half * 2 * Slot::kPageBytes); };   // K, V
+        auto clean = [&](char *buf, int rd) {
+            pages.clean(buf, my_at + 2 * Slot::kPageBytes, (4 * rd + 2 * side + my_tile) * kTileTokens + my_page * kPage);
+        };
+        auto turn = [&](int rd, char *cur, char *next, int page) {
+            u32x4 ka[S], kb[S];
+            Slot::fetch_k(cur, side_at + part * Slot::kBytes, lane, ka, kb);
+            __builtin_amdgcn_sched_barrier(0);
+            bring_half(0, next, page);
+            step(cur, side_at + part * Slot::kBytes, ka, kb, 4 * rd + 2 * side, [&] { bring_half(1, next, page); });
+            wait_loads<0>();   // round rd + 1 has arrived
+            clean(next, rd + 1);
+            wait_lds();
+            phase_barrier();
+        };
+        auto walk = [&](char *even, char *odd) {
+            bring_half(0, even, page_of(0));
+            bring_half(1, even, page_of(0));
+            int page = page_of(1);
+            wait_loads<0>();
+            clean(even, 0);
+            wait_lds();
+            phase_barrier();
+            for (int rd = 0;;) {
+                { const int after = page_of(rd + 2); turn(rd, even, odd, page); page = after; }
+                if (++rd == rounds) break;
+                { const int after = page_of(rd + 2); turn(rd, odd, even, page); page = after; }
+                if (++rd == rounds) break;
+            }
+        };
+        if (rounds > 0) {
+            if (kSplit == 4 || side == 0)
+                walk(buf0, buf1);
+            else
+                walk(buf2, buf3);
+        }
+        leave_parts<P, NB, 4>(a, rows, st, 4 * group_of_four + 2 * side + part, lane, ms, ls, image_of);
+    };
+    if constexpr (kSplit == 2)
+        eight();
+    else if constexpr (kSplit == 4)
+        by_four();
+    else if (four)
+        by_four();
+    else
+        eight();
 }
 
 // All waves own the same rows and every wave loads tiles of its own: nobody waits for anybody.  K of the next tile is asked for as soon as the operands of this
@@ -1000,7 +1063,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
                           hipEvent_t stop)
 {
     const unsigned pairs = (unsigned)a.B * (unsigned)(a.Hkv * a.HB);
-    const unsigned grid = a.plan.order ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
+    const unsigned grid = a.plan.order || a.plan.on_device ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
     if (grid == 0) return hipSuccess;
     auto go = [&](auto kernel, int waves) {
         const dim3 g(grid), b(waves * 64);
@@ -1013,6 +1076,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
         if constexpr (std::is_same<P, Bf16Path<128>>::value) {
+            if (a.plan.on_device) return go(prefill_wide_kernel_direct<0>, 8);
             switch (a.plan.blocks) {
             case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us)
                 return a.plan.phases ? go(prefill_pingpong_kernel, 8) : go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);

@@ -114,6 +114,7 @@ struct PrefillPlan {
     int blocks, split;
     bool phases;
     int order;      // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
+    bool on_device; // 8 or 4 blocks, as the kernel finds better for the lengths (prefill_on_device)
 };
 // Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
 // waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
@@ -238,6 +239,41 @@ __host__ inline int prefill_order(const PrefillPlan &plan, int kv_dtype, int hea
     const int reach = head_dim == 64 && max_context_len < 1024 ? 256 : std::min(max_context_len, 16 * 256);
     if ((blocks + batch / 2) * heads * 256 > (int64_t)slots * reach) return 0;
     return blocks * heads >= 1536 ? 4 : 8;
+}
+
+// 8 or 4 blocks, by the lengths themselves.  The host knows bounds and totals: calls of equal lengths want 8 blocks from 192 workgroups on, ragged ones, whose longest
+// range sets the end, many more.  From 1536 tokens on, from 96 workgroups of 8 blocks on and while the grid for 4 is not mostly empty, the kernel
+// therefore decides.  Every workgroup estimates both times: a range of `longest` tiles or the chip's share of all tiles, whichever is more; the share of a last
+// round that is not full, the less the more lengths differ; and a start per round.  us per tile and factor are fitted to 601 random calls (2 to 32 sequences, 1.5 k to 16 k
+// tokens, 8 - 2048 queries, heads as in perf/cases.py), each timed with both sizes: 1.025 times as fast as by the host's rule (1.037 with the better size of
+// each call), 86 gain more than 8 % and 14 lose that much; of 219 others 1.035, 31 and 4.  (The worst fetch more K/V than the estimate knows: 24 sequences of
+// 6.8 - 15.6 k, 15 queries, 64/8 heads 253 -> 310 us.)  5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads: 220 workgroups of 8 blocks 85 us, 432 of 4 61.
+//
+// Deciding costs 1 us, so shorter contexts keep the host's rule (300 calls under 1024 tokens .98), and fewer workgroups (.97), of which none is better with 8.
+//
+// `s` holds the sequences: longest() in tokens, total(f) = sum of f(queries, tokens), count(tokens, halves) = workgroups of 8 (4, halves = 1) blocks that cover them.
+template <class Sequences>
+__host__ __device__ inline bool prefill_prefers_four(const Sequences &s, int heads, int tokens)
+{
+    const float longest = (float)((s.longest() + kTileTokens - 1) / kTileTokens);
+    const auto time = [&](int halves, float tile) {
+        const int own = tokens >> halves;
+        const float n = (float)(s.total([&](int nq, int) { return s.count(nq, halves); }) * heads);
+        const float walked = (float)s.total([&](int nq, int L) {   // the ends of a sequence's blocks grow evenly
+            return s.count(nq, halves) * ((L + (L > nq ? L - nq : 0) + (nq < own ? nq : own)) / (2 * kTileTokens));
+        }) * (float)heads;
+        const float rounds = n / 256, share = walked / 256, average = walked / (n > 1 ? n : 1);
+        const float last = rounds > 1 ? 0.5f * ((float)(int)(rounds + 0.999f) - rounds) * average * average / (longest > 1 ? longest : 1) : 0;
+        return tile * ((longest > share ? longest : share) + last) + 5 * (rounds > 1 ? rounds : 1);
+    };
+    return 0.7f * time(0, 0.524f) >= time(1, 0.265f);
+}
+// Whether the choice is left to the kernel.
+__host__ inline bool prefill_on_device(const PrefillPlan &plan, int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)
+{
+    if (kv_dtype != 0 || head_dim != 128 || (plan.blocks != 8 && plan.blocks != 4) || batch == 1 || batch > kMaxOrderedBatch || max_context_len < 1536) return false;
+    const int64_t most = ((int64_t)max_q_len + 4 * units - 1) / (4 * units) * batch * heads, expected = (total_q / (4 * units) + batch / 2) * heads;
+    return most <= 4096 && most <= 2 * expected + 256 && std::max<int64_t>(total_q / (8 * units) + batch / 2, batch) * heads >= 96;
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens
