@@ -33,31 +33,24 @@
 
 namespace sd {
 
-// The sequences of a batch as prefill_pick asks for them, one to a lane, cut into workgroups' tokens or (halves = 1) half of them.
+// The sequences of a batch as prefill_pick asks for them, one to a lane.
 struct WaveSequences {
-    int nq, L;          // 0 queries: nothing to do
     int end, blocks;
-    int round_up;
-    uint32_t reciprocal;
-    SD_DEV WaveSequences(const PrefillArgs &a, int lane) : nq(0), L(0), round_up(a.round_up), reciprocal(a.reciprocal)
+    SD_DEV WaveSequences(int end_, int blocks_) : end(end_), blocks(blocks_) {}
+    SD_DEV WaveSequences(const PrefillArgs &a, int lane) : end(0), blocks(0)
     {
-        int qs = 0, next = 0, stored = 0;
-        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], stored = a.context_lens[lane];
-        const int n = min(next - qs, a.max_q_len);
-        if (lane < a.B && qs >= 0 && n > 0 && (int64_t)qs + n <= a.total_q) nq = n, L = max(0, min(stored, a.max_context_len));
-        cut(0);
+        int qs = 0, next = 0, L = 0;
+        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], L = a.context_lens[lane];
+        {
+            const int nq = min(next - qs, a.max_q_len);
+            L = max(0, min(L, a.max_context_len));
+            // rounded up; a.reciprocal = 2^32 / tokens of a workgroup, rounded up: exact below 2^24
+            if (lane < a.B && qs >= 0 && nq > 0 && (int64_t)qs + nq <= a.total_q) {
+                blocks = (int)__umulhi((unsigned)(nq + a.round_up), a.reciprocal);
+                end = (int)__umulhi((unsigned)(L + a.round_up), a.reciprocal);
+            }
+        }
     }
-    // rounded up; reciprocal = 2^32 / tokens of a workgroup, rounded up: exact below 2^24
-    SD_DEV int count(int tokens, int halves) const { return (int)__umulhi((unsigned)((tokens << halves) + round_up), reciprocal); }
-    SD_DEV void cut(int halves)
-    {
-        blocks = nq > 0 ? count(nq, halves) : 0;
-        end = nq > 0 ? count(L, halves) : 0;
-    }
-    // for prefill_prefers_four
-    SD_DEV int longest() const { return wave_max(nq > 0 ? L : 0); }
-    template <class F>
-    SD_DEV int total(F f) const { return __builtin_amdgcn_readlane(wave_scan(nq > 0 ? f(nq, L) : 0), 63); }
     SD_DEV int top() const { return wave_max(end); }
     template <class F>
     SD_DEV int sum(F f) const { return __builtin_amdgcn_readlane(wave_scan(f(end, blocks)), 63); }
@@ -71,6 +64,25 @@ struct WaveSequences {
         const int b = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > m) | 1ull << 63);   // m is less than the sum
         return Found{b, __builtin_amdgcn_readlane(incl - own, b), __builtin_amdgcn_readlane(end, b), __builtin_amdgcn_readlane(blocks, b)};
     }
+};
+
+// Their queries and tokens, as prefill_prefers_four asks for them, and the sequences cut into the tokens of a workgroup or (halves = 1) half of them.
+struct WaveLengths {
+    int nq, L;   // 0 queries: nothing to do
+    int round_up;
+    uint32_t reciprocal;
+    SD_DEV WaveLengths(const PrefillArgs &a, int lane) : nq(0), L(0), round_up(a.round_up), reciprocal(a.reciprocal)
+    {
+        int qs = 0, next = 0, stored = 0;
+        if (lane < a.B) qs = a.q_start[lane], next = a.q_start[lane + 1], stored = a.context_lens[lane];
+        const int n = min(next - qs, a.max_q_len);
+        if (lane < a.B && qs >= 0 && n > 0 && (int64_t)qs + n <= a.total_q) nq = n, L = max(0, min(stored, a.max_context_len));
+    }
+    SD_DEV int count(int tokens, int halves) const { return (int)__umulhi((unsigned)((tokens << halves) + round_up), reciprocal); }   // as above
+    SD_DEV int longest() const { return wave_max(nq > 0 ? L : 0); }
+    template <class F>
+    SD_DEV int total(F f) const { return __builtin_amdgcn_readlane(wave_scan(nq > 0 ? f(nq, L) : 0), 63); }
+    SD_DEV WaveSequences cut(int halves) const { return nq > 0 ? WaveSequences(count(L, halves), count(nq, halves)) : WaveSequences(0, 0); }
 };
 
 // Which query rows a wave owns (everything but `n`-dependent values is wave-uniform).
@@ -89,6 +101,7 @@ struct PrefillRows {
     SD_DEV bool find(const PrefillArgs &a, int groups, int group, int blocks)
     {
         const int Hv = a.Hkv * a.HB;
+        tpb = units_per_block(a.G);
         int seq, head, jb;
         if (a.plan.order) {   // head fastest
             const PrefillBlock at = prefill_pick(WaveSequences(a, threadIdx.x & 63), (int)(blockIdx.x / Hv), a.plan.order);
@@ -97,12 +110,12 @@ struct PrefillRows {
             const PrefillItem item = prefill_item(blockIdx.x, a.q_blocks, a.B * Hv);
             seq = item.pair / Hv, head = item.pair % Hv, jb = a.q_blocks - 1 - item.block;
         }
-        return jb >= 0 && take(a, seq, head, jb, groups, group, blocks);
+        if (jb < 0) return false;
+        return take(a, seq, head, jb, groups, group, blocks);
     }
-    // The same, in block jb of a sequence and (virtual) head.
+    // The same, in block jb of a sequence and (virtual) head; tpb is known.
     SD_DEV bool take(const PrefillArgs &a, int seq, int head, int jb, int groups, int group, int blocks)
     {
-        tpb = units_per_block(a.G);
         const int tpw = blocks * tpb;   // query tokens per wave
         b = seq;
         hb = head_block(head, a.G, a.HB);
@@ -550,11 +563,11 @@ __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs
     PrefillRows rows;
     if constexpr (kSplit == 0) {
         const int Hv = a.Hkv * a.HB;
-        WaveSequences sequences(a, lane);
-        four = prefill_prefers_four(sequences, Hv, a.round_up + 1);
-        if (four) sequences.cut(1);
-        const PrefillBlock at = prefill_pick(sequences, (int)(blockIdx.x / Hv), 8);
+        const WaveLengths lengths(a, lane);
+        four = prefill_prefers_four(lengths, Hv, a.round_up + 1);
+        const PrefillBlock at = prefill_pick(lengths.cut(four), (int)(blockIdx.x / Hv), 8);
         if (at.block < 0) return;
+        rows.tpb = units_per_block(a.G);
         if (!rows.take(a, at.b, blockIdx.x % Hv, at.block, four ? 2 : 4, four ? group_of_four : group_of_eight, NB)) return;
     } else {
         if (!rows.find(a, kW / kSplit, four ? group_of_four : group_of_eight, NB)) return;

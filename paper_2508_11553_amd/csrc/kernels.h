@@ -113,8 +113,8 @@ __host__ __device__ inline PrefillBlock prefill_pick(const Sequences &s, int k, 
 struct PrefillPlan {
     int blocks, split;
     bool phases;
-    int order;      // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
     bool on_device; // 8 or 4 blocks, as the kernel finds better for the lengths (prefill_on_device)
+    int order;      // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
 };
 // Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
 // waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
