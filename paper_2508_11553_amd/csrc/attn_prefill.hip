@@ -15,7 +15,7 @@
 // 2048 queries, 32/8 heads: 1.50 -> 1.28 ms against converting K in every consuming wave).
 //
 // bf16 pools, whose rows need no conversion, have kernels of their own further down for large calls and for split ranges; the general kernel
-// serves them in one phase (short contexts and few queries per sequence), and at head_dim 64 with blocks of 8.
+// serves them in one phase (head_dim 128, short contexts and few queries per sequence).
 //
 // The causal limit is a per-lane token bound in the score mask; a wave stops
 // once a tile starts at or past the last position any of its rows may see.
@@ -789,18 +789,22 @@ __global__ __launch_bounds__(kW * 64, 2) void prefill_wide_kernel_own(PrefillArg
     leave_parts<P, NB, kW>(a, rows, st, wave, lane, ms, ls, [&](int w) { return (w < kW / 2 ? kbuf : vbuf) + w % (kW / 2) * PartImage<P, NB>::kBytes; });
 }
 
-// head_dim 64: workgroups of 4 waves with four column blocks each, two to a compute unit; a round is two tiles in one of four
-// arrays, asked for three rounds ahead.  (8 prompts of 1.5 k to 4 k, 32/8 heads 429 -> 405 us, 16 x 8192 / 2048 1909 -> 1828 us,
-// against parking through registers.)
+// head_dim 64: workgroups of 4 waves; a round is two tiles in one of several arrays.  Softmax and matrix instructions of a wave's step take about as
+// long, one after the other, so what counts is other waves to fill the gaps: with two column blocks per wave (142 registers) and three arrays, asked for two
+// rounds ahead, a compute unit holds three workgroups.  Against the general kernel with as many blocks and waves: 160 random calls 1.05 times as fast, up to 1.15 (10
+// sequences of 87 - 595, 227 - 1365 queries, 16/2 heads 18.0 -> 16.9 us; 14 of 582 - 785, whole prompts, 32/4 62.5 -> 56.3).  Four workgroups' worth of
+// waves (16 to a compute unit, 128 registers) are no faster than the general kernel.
+// With four blocks per wave, four arrays and three rounds ahead it holds two, and a tile's operands are read once for twice the rows: for the
+// largest calls (16 x 8192 / 2048, 32/8 heads 1909 -> 1828 us against the general kernel).
 template <int NB>
-__global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
+__global__ __launch_bounds__(256, NB == 2 ? 3 : 2) void prefill_direct_kernel(PrefillArgs a)
 {
-    constexpr int D = 64, kW = 4, kTiles = 2;
+    constexpr int D = 64, kW = 4, kTiles = 2, kAhead = NB == 2 ? 2 : 3;
     typedef Bf16Path<D> P;
     typedef RowSlot<D> Slot;
     constexpr int kLoads = Slot::kPageBytes / 1024;   // of a K or V page
     static_assert(2 * kTiles == kW, "a wave brings K and V of one page per round");
-    __shared__ __attribute__((aligned(16))) char buf0[kTiles * Slot::kBytes], buf1[kTiles * Slot::kBytes], buf2[kTiles * Slot::kBytes], buf3[kTiles * Slot::kBytes];
+    __shared__ __attribute__((aligned(16))) char buf0[kTiles * Slot::kBytes], buf1[kTiles * Slot::kBytes], buf2[kTiles * Slot::kBytes], buf3[kAhead == 3 ? kTiles * Slot::kBytes : 16];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -844,7 +848,7 @@ __global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
     };
     constexpr int kPer = 2 * kLoads;   // loads a wave issues per round
     auto turn = [&](int rd, char *cur, char *next, char *fill, int page) {
-        bring(fill, page);   // round rd + 3
+        bring(fill, page);   // round rd + kAhead
         if (rows.active) {
             const int t0 = kTiles * rd * kTileTokens;
             const int j_end = min(kTiles, (rows.max_end - t0 + kTileTokens - 1) / kTileTokens);
@@ -855,7 +859,7 @@ __global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
 #pragma unroll 1
             for (; j < j_end; ++j) step(cur, j, kTiles * rd + j, std::true_type{});
         }
-        wait_loads<2 * kPer>();   // round rd + 1 has arrived
+        wait_loads<(kAhead - 1) * kPer>();   // round rd + 1 has arrived
         clean(next, rd + 1);
         wait_lds();
         phase_barrier();
@@ -863,21 +867,23 @@ __global__ __launch_bounds__(256, 2) void prefill_direct_kernel(PrefillArgs a)
     if (rounds > 0) {
         bring(buf0, page_of(0));
         bring(buf1, page_of(1));
-        bring(buf2, page_of(2));
-        int page = page_of(3);
-        wait_loads<2 * kPer>();
+        if constexpr (kAhead == 3) bring(buf2, page_of(2));
+        int page = page_of(kAhead);
+        wait_loads<(kAhead - 1) * kPer>();
         clean(buf0, 0);
         wait_lds();
         phase_barrier();
         for (int rd = 0;;) {
-            { const int after = page_of(rd + 4); turn(rd, buf0, buf1, buf3, page); page = after; }
+            { const int after = page_of(rd + kAhead + 1); turn(rd, buf0, buf1, kAhead == 3 ? buf3 : buf2, page); page = after; }
             if (++rd == rounds) break;
-            { const int after = page_of(rd + 4); turn(rd, buf1, buf2, buf0, page); page = after; }
+            { const int after = page_of(rd + kAhead + 1); turn(rd, buf1, buf2, buf0, page); page = after; }
             if (++rd == rounds) break;
-            { const int after = page_of(rd + 4); turn(rd, buf2, buf3, buf1, page); page = after; }
+            { const int after = page_of(rd + kAhead + 1); turn(rd, buf2, kAhead == 3 ? buf3 : buf0, buf1, page); page = after; }
             if (++rd == rounds) break;
-            { const int after = page_of(rd + 4); turn(rd, buf3, buf0, buf2, page); page = after; }
-            if (++rd == rounds) break;
+            if constexpr (kAhead == 3) {
+                { const int after = page_of(rd + kAhead + 1); turn(rd, buf3, buf0, buf2, page); page = after; }
+                if (++rd == rounds) break;
+            }
         }
         wait_loads<0>();   // no load may outlive the workgroup
     }
@@ -1111,7 +1117,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
         if constexpr (std::is_same<P, Bf16Path<64>>::value) {
             switch (a.plan.blocks) {
             case 16: return go(prefill_direct_kernel<4>, 4);
-            case 8: return go(prefill_wide_kernel<P, 4, 2, 1, 2, 3>, 4);
+            case 8: return go(prefill_direct_kernel<2>, 4);
             case 4: return go(prefill_wide_kernel_own<64, 4, 4>, 4);
             default: return go(prefill_wide_kernel_own<64, 8, 2>, 8);
             }

@@ -210,6 +210,16 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
     return enough(4) || max_context_len < 1024 || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
 }
 
+// Calls of head_dim 64 over bf16 pools that fill the chip with blocks of 16 take 8 all the same where no sequence may reach 1536 tokens: three workgroups of a compute
+// unit fill each other's gaps better than two, and it is for long ranges that a tile's operands are better read once for twice the rows.  16 over 8 blocks, 60
+// random calls of 2048 workgroups of 16 blocks and more, run until the chip's clock had settled: under 1024 tokens 1.05, under 1536 1.03, under 2048 1.01, from there on .98, none above
+// 1.00.  (In bursts of 10 ms, before it has, 1.13, 1.09, 1.07 and 1.05.)
+__host__ inline PrefillPlan prefill_halved(PrefillPlan plan, int kv_dtype, int head_dim, int max_context_len)
+{
+    if (kv_dtype == 0 && head_dim == 64 && plan.blocks == 16 && max_context_len < 1536) plan.blocks = 8;
+    return plan;
+}
+
 // Classes of a call's order, 0: dealt pair by pair.  A workgroup finds its block in about 0.8 us (the lengths come from memory, then
 // a hundred dependent instructions), so a call whose workgroups all run at once, or of a single sequence, is dealt: six sequences of 800 tokens, 40 queries,
 // 8/2 heads, d = 64 7.7 : 8.5 us, dealt : longest first.  So are contexts under 512 tokens, whose time goes into reading queries and writing rows as much as into their
