@@ -15,7 +15,7 @@
 // 2048 queries, 32/8 heads: 1.50 -> 1.28 ms against converting K in every consuming wave).
 //
 // bf16 pools, whose rows need no conversion, have kernels of their own further down for large calls and for split ranges; the general kernel
-// serves them in one phase (head_dim 128, short contexts and few queries per sequence).
+// serves them where sequences bring few queries (head_dim 128).
 //
 // The causal limit is a per-lane token bound in the score mask; a wave stops
 // once a tile starts at or past the last position any of its rows may see.
@@ -796,14 +796,20 @@ __global__ __launch_bounds__(kW * 64, 2) void prefill_wide_kernel_own(PrefillArg
 // waves (16 to a compute unit, 128 registers) are no faster than the general kernel.
 // With four blocks per wave, four arrays and three rounds ahead it holds two, and a tile's operands are read once for twice the rows: for the
 // largest calls (16 x 8192 / 2048, 32/8 heads 1909 -> 1828 us against the general kernel).
-template <int NB>
-__global__ __launch_bounds__(256, NB == 2 ? 3 : 2) void prefill_direct_kernel(PrefillArgs a)
+//
+// head_dim 128: 8 waves of two column blocks, one workgroup to a compute unit; a wave brings K or V of one page per round.  For contexts of a few tiles, which do not pay
+// for the start-up of the two phases below.  Against the general kernel, 179 random calls under 512 tokens whose average sequence fills three quarters of a
+// workgroup's blocks or more 1.08 times as fast, under 128 tokens 1.15 (14 sequences of 95 - 115, whole prompts, 32/4 heads 19.5 -> 15.1 us); 31 emptier ones .98,
+// as all waves wait for rounds that few of them attend.
+template <int D, int kW, int NB>
+__global__ __launch_bounds__(kW * 64, D == 64 && NB == 2 ? 3 : 2) void prefill_direct_kernel(PrefillArgs a)
 {
-    constexpr int D = 64, kW = 4, kTiles = 2, kAhead = NB == 2 ? 2 : 3;
+    constexpr int kTiles = 2, kAhead = D == 64 && NB == 2 ? 2 : 3;
     typedef Bf16Path<D> P;
     typedef RowSlot<D> Slot;
     constexpr int kLoads = Slot::kPageBytes / 1024;   // of a K or V page
-    static_assert(2 * kTiles == kW, "a wave brings K and V of one page per round");
+    constexpr int kKinds = 4 * kTiles / kW;   // a wave brings K and V of one page per round, or one of them
+    static_assert(kKinds == 1 || kKinds == 2, "whole pages per wave");
     __shared__ __attribute__((aligned(16))) char buf0[kTiles * Slot::kBytes], buf1[kTiles * Slot::kBytes], buf2[kTiles * Slot::kBytes], buf3[kAhead == 3 ? kTiles * Slot::kBytes : 16];
 
     const int lane = threadIdx.x & 63;
@@ -823,18 +829,21 @@ __global__ __launch_bounds__(256, NB == 2 ? 3 : 2) void prefill_direct_kernel(Pr
     const int last_page = (rows.kv_end + kPage - 1) / kPage - 1;
     const int rounds = (ntiles + kTiles - 1) / kTiles;
     // past the end the last page once more; nobody attends it
-    auto page_of = [&](int rd) { return bt[min(2 * kTiles * min(rd, rounds - 1) + wave, last_page)]; };
-    const int my_k = (wave >> 1) * Slot::kBytes + (wave & 1) * Slot::kPageBytes, my_v = my_k + 2 * Slot::kPageBytes;
+    const int my_page = kKinds == 2 ? wave : wave % (2 * kTiles), my_kind = wave / (2 * kTiles);
+    auto page_of = [&](int rd) { return bt[min(2 * kTiles * min(rd, rounds - 1) + my_page, last_page)]; };
+    const int my_k = (my_page >> 1) * Slot::kBytes + (my_page & 1) * Slot::kPageBytes, my_v = my_k + 2 * Slot::kPageBytes;
     auto bring = [&](char *buf, int page) {
+        if (kKinds == 2 || my_kind == 0)
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) load_to_lds(kbase + page * page_bytes, Slot::kPageBytes, Slot::source(0, j * 1024 + lane * 16), buf + (my_k + j * 1024));
+            for (int j = 0; j < kLoads; ++j) load_to_lds(kbase + page * page_bytes, Slot::kPageBytes, Slot::source(0, j * 1024 + lane * 16), buf + (my_k + j * 1024));
+        if (kKinds == 2 || my_kind == 1)
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) load_to_lds(vbase + page * page_bytes, Slot::kPageBytes, Slot::source(1, j * 1024 + lane * 16), buf + (my_v + j * 1024));
+            for (int j = 0; j < kLoads; ++j) load_to_lds(vbase + page * page_bytes, Slot::kPageBytes, Slot::source(1, j * 1024 + lane * 16), buf + (my_v + j * 1024));
     };
     // V rows of tokens that do not exist may hold anything: zeros
     auto clean = [&](char *buf, int rd) {
-        const int tok0 = (2 * kTiles * rd + wave) * kPage;
-        if (tok0 + kPage <= rows.L) return;
+        const int tok0 = (2 * kTiles * rd + my_page) * kPage;
+        if ((kKinds == 1 && my_kind == 0) || tok0 + kPage <= rows.L) return;
 #pragma unroll
         for (int j = 0; j < kLoads; ++j)
             if (tok0 + (j * 1024 + lane * 16) / Slot::kRowBytes >= rows.L) *reinterpret_cast<u32x4 *>(buf + (my_v + j * 1024 + lane * 16)) = u32x4{0, 0, 0, 0};
@@ -846,7 +855,7 @@ __global__ __launch_bounds__(256, NB == 2 ? 3 : 2) void prefill_direct_kernel(Pr
             ka, kb, [&](int k) { return Slot::v_operand(buf, j * Slot::kBytes, k, lane); }, qop, st, a.scale_log2e, tile * kTileTokens,
             lane, row_end, true, nullptr, rows.first_end, rows.tpb);
     };
-    constexpr int kPer = 2 * kLoads;   // loads a wave issues per round
+    constexpr int kPer = kKinds * kLoads;   // loads a wave issues per round
     auto turn = [&](int rd, char *cur, char *next, char *fill, int page) {
         bring(fill, page);   // round rd + kAhead
         if (rows.active) {
@@ -1095,10 +1104,12 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
         if constexpr (std::is_same<P, Bf16Path<128>>::value) {
+            // (rows enough for the two phases, but not the tiles)
+            const bool full = (int64_t)a.total_q * 4 >= (int64_t)16 * 3 * units_per_block(a.G) * a.B;
             if (a.plan.on_device) return go(prefill_wide_kernel_direct<0>, 8);
             switch (a.plan.blocks) {
             case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us)
-                return a.plan.phases ? go(prefill_pingpong_kernel, 8) : go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
+                return a.plan.phases ? go(prefill_pingpong_kernel, 8) : full ? go(prefill_direct_kernel<128, 8, 2>, 8) : go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
             case 8: return go(prefill_wide_kernel_direct<2>, 8);
             case 4: return go(prefill_wide_kernel_direct<4>, 8);
             default: return go(prefill_wide_kernel_own<128, 8, 2>, 8);
@@ -1116,8 +1127,8 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
         typedef decltype(path) P;
         if constexpr (std::is_same<P, Bf16Path<64>>::value) {
             switch (a.plan.blocks) {
-            case 16: return go(prefill_direct_kernel<4>, 4);
-            case 8: return go(prefill_direct_kernel<2>, 4);
+            case 16: return go(prefill_direct_kernel<64, 4, 4>, 4);
+            case 8: return go(prefill_direct_kernel<64, 4, 2>, 4);
             case 4: return go(prefill_wide_kernel_own<64, 4, 4>, 4);
             default: return go(prefill_wide_kernel_own<64, 8, 2>, 8);
             }
