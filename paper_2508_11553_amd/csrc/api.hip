@@ -674,7 +674,7 @@ int paged_prefill_attention(const sd_shape *shape, const void *q, const int32_t 
     a.max_q_len = max_q_len < total_q ? max_q_len : total_q;
     const int units = sd::units_per_block(a.G);
     a.plan = sd::prefill_plan(shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
-    a.plan = sd::prefill_halved(a.plan, shape->kv_dtype, shape->head_dim, a.max_context_len);
+    a.plan = sd::prefill_halved(a.plan, shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
     a.plan.on_device = total_q < 1 << 23 && a.max_context_len < 1 << 23 &&
                        sd::prefill_on_device(a.plan, shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
     const int tokens_per_wg = (a.plan.on_device ? 8 : a.plan.blocks) * units;

@@ -213,10 +213,11 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
 // Calls of head_dim 64 over bf16 pools that fill the chip with blocks of 16 take 8 all the same where no sequence may reach 1536 tokens: three workgroups of a compute
 // unit fill each other's gaps better than two, and it is for long ranges that a tile's operands are better read once for twice the rows.  16 over 8 blocks, 60
 // random calls of 2048 workgroups of 16 blocks and more, run until the chip's clock had settled: under 1024 tokens 1.05, under 1536 1.03, under 2048 1.01, from there on .98, none above
-// 1.00.  (In bursts of 10 ms, before it has, 1.13, 1.09, 1.07 and 1.05.)
-__host__ inline PrefillPlan prefill_halved(PrefillPlan plan, int kv_dtype, int head_dim, int max_context_len)
+// 1.00.  (In bursts of 10 ms, before it has, 1.13, 1.09, 1.07 and 1.05.)  A grid that a loose bound on the queries leaves mostly empty is not doubled.
+__host__ inline PrefillPlan prefill_halved(PrefillPlan plan, int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)
 {
-    if (kv_dtype == 0 && head_dim == 64 && plan.blocks == 16 && max_context_len < 1536) plan.blocks = 8;
+    const int64_t most = ((int64_t)max_q_len + 8 * units - 1) / (8 * units) * batch * heads, expected = (total_q / (8 * units) + batch / 2) * heads;
+    if (kv_dtype == 0 && head_dim == 64 && plan.blocks == 16 && max_context_len < 1536 && most <= 2 * expected) plan.blocks = 8;
     return plan;
 }
 

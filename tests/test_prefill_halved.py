@@ -17,7 +17,8 @@ int main()
     for (int kv : {0, 1})
         for (int d : {64, 128})
             for (int blocks : {16, 8, 4, 2})
-                for (int longest : {100, 1535, 1536, 100000}) printf("%d %d %d %d %d\n", kv, d, blocks, longest, sd::prefill_halved(sd::PrefillPlan{blocks, 1, false}, kv, d, longest).blocks);
+                for (int longest : {100, 1535, 1536, 100000}) printf("%d %d %d %d %d\n", kv, d, blocks, longest, sd::prefill_halved(sd::PrefillPlan{blocks, 1, false}, kv, d, 8000, 1000, 16, 8, 4, longest).blocks);
+    for (int bound : {500, 1000, 1100, 5000}) printf("%d\n", sd::prefill_halved(sd::PrefillPlan{16, 1, false}, 0, 64, 8000, bound, 16, 8, 4, 1000).blocks);
 }
 """
 
@@ -29,8 +30,9 @@ def test_only_plans_of_16_at_head_dim_64_over_bf16_pools_are_halved(tmp_path):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     lines = subprocess.run([str(tmp_path / "halved")], capture_output=True, text=True, check=True).stdout.splitlines()
-    assert len(lines) == 64
-    for line in lines:
+    assert len(lines) == 68
+    assert lines[64:] == ["8", "8", "16", "16"]   # queries of a sequence, bound; the average is 500: no grid that is mostly empty
+    for line in lines[:64]:
         kv, d, blocks, longest, got = map(int, line.split())
         assert got == (8 if (kv, d, blocks) == (0, 64, 16) and longest < 1536 else blocks)
 
