@@ -542,7 +542,7 @@ int attend_impl(const sd_shape *shape, const void *q, const void *k_pages, const
     sa.max_shared_len = max_shared_len;
     const int64_t out_bytes = (int64_t)shape->batch * shape->num_q_heads * shape->head_dim * 4;
     sa.store_through = direct && sd::stores_through(out_bytes);
-    sa.store_windows = direct && sd::stores_in_windows(out_bytes, shape->max_context_len, 2 * shape->head_dim * (shape->kv_dtype == SD_BF16 ? 2 : 1));
+    sa.window_tokens = direct ? sd::window_tokens(out_bytes, shape->max_context_len, 2 * shape->head_dim * (shape->kv_dtype == SD_BF16 ? 2 : 1)) : 0;
     sa.order = sd::split_order(shape->batch, sa.Hkv * sa.HB, std::min(shape->max_context_len, chunk));
     sa.out_direct = direct ? out : nullptr;
     const bool in_place = direct && k_new;

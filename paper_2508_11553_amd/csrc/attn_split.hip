@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void split_kernel(SplitArgs a)
     __syncthreads();
 
     // (the last round of workgroups would only end later)
-    if (!GROUPS && a.store_windows && (t1 - t0) * (2 * P::kTileBytes / kPage) >= kWorthAWindow && gridDim.x - blockIdx.x > 512u) await_store_window();
+    if (!GROUPS && a.window_tokens && t1 - t0 >= a.window_tokens && gridDim.x - blockIdx.x > (unsigned)split_round(D)) await_store_window();
 
     // merge the four waves; some wave saw a token, so the max is finite
     const int64_t row0 = (int64_t)b * a.Hq + hb.head0;

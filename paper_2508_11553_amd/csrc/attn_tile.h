@@ -82,7 +82,7 @@ SD_DEV void store_through(float *dst, int bytes, int offset, f32x4 x)
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), __builtin_amdgcn_make_buffer_rsrc(dst, 0, bytes, 0x00027000), offset, 0, kSc1);
 }
 
-// Waits for the next window of the clock in which rows are stored (stores_in_windows): 0.64 us of every 6.4 on the 100 MHz clock
+// Waits for the next window of the clock in which rows are stored (window_tokens): 0.64 us of every 6.4 on the 100 MHz clock
 // that all dies share.
 SD_DEV void await_store_window()
 {

@@ -329,10 +329,17 @@ __host__ inline bool stores_through(int64_t bytes) { return bytes >= 10 << 20; }
 //   1024 fp8 of 512 - 4096, 64/8 heads 748 : 726    1024 fp8 of 256 - 2048, 64/8 398 : 381    1024 bf16 of 125 - 1000, 64/8 396 : 378
 //   1000 bf16 of 125 - 1000, 32/8 372 : 367         800 bf16 of 512 - 4096, 28/4 578 : 577    1000 bf16 of 62 - 500, 32/8 197 : 199
 //   1000 fp8 of 50 - 400, 32/8 100 : 139 if every workgroup waits
+//   at head_dim 64, whose compute units hold four workgroups: 1024 fp8 of 512 - 4096, 64/8 398 : 383    800 bf16 of 3000 - 6000, 64/4 566 : 561
+//   1024 bf16 of 100 - 1600, 48/16 539 : 543   (15 such calls 1.009 times as fast)
 // So the longest sequence may have 384 KB of K/V per head (fp8 of up to 1280 gain 0 - 1 %, bf16 of up to 500 lose as much), and only workgroups that walked 128 KB wait.  Periods of 5 to 13 us and windows of
 // a tenth to a quarter of them differ by 1 %.
-constexpr int kWorthAWindow = 128 << 10;   // bytes of K/V
-__host__ inline bool stores_in_windows(int64_t bytes, int longest, int token_bytes) { return stores_through(bytes) && (int64_t)longest * token_bytes >= 384 << 10; }
+// The tokens from which on a workgroup waits, 0: no windows.
+__host__ inline int window_tokens(int64_t bytes, int longest, int token_bytes)
+{
+    return stores_through(bytes) && (int64_t)longest * token_bytes >= 384 << 10 ? (128 << 10) / token_bytes : 0;
+}
+// Workgroups of the split pass that the chip holds at once: a compute unit two at head_dim 128 and four at head_dim 64 (registers, LDS).
+__host__ __device__ constexpr int split_round(int head_dim) { return 256 * (head_dim == 64 ? 4 : 2); }
 
 // Arguments of the split-K pass (by value, lives in kernel-argument memory).
 struct SplitArgs {
@@ -367,7 +374,7 @@ struct SplitArgs {
     int32_t grid_chunks;         // chunk slots the plain part of the grid spans (S, or S-1 without groups)
     SplitOrder order;            // of the sequences' last chunks
     int32_t store_through;       // finished rows are written through the L2 (stores_through)
-    int32_t store_windows;       // and in windows of the clock (stores_in_windows)
+    int32_t window_tokens;       // and in windows of the clock by workgroups that walked so many tokens, 0: by none
 };
 
 // Hand-over inside a workgroup.  The four waves of a workgroup walk neighbouring pieces (ranges 4i ..

@@ -29,6 +29,9 @@ int main(int argc, char **argv)
         const int G = s.num_q_heads / s.num_kv_heads;
         const sd::PrefillPlan p = sd::prefill_plan(s.kv_dtype, s.head_dim, v[6], v[7], s.batch, s.num_kv_heads * sd::head_blocks(G), sd::units_per_block(G), s.max_context_len);
         printf("%d %d\n", p.blocks, p.split);
+    } else if (!strcmp(argv[1], "stores")) {   // MB of rows, bytes beyond them, bytes of K/V per token and head
+        const int64_t bytes = ((int64_t)v[6] << 20) + v[7];
+        printf("%d %d %d\n", sd::stores_through(bytes), sd::window_tokens(bytes, s.max_context_len, v[8]), sd::split_round(s.head_dim) / 256);
     } else if (!strcmp(argv[1], "merge_width")) {   // items, rows, groups
         printf("%d\n", sd::merge_width(v[0], v[1], v[2]));
     }
@@ -102,3 +105,16 @@ def test_prefill_plan_at_the_ends_of_its_arguments(rule, batch, total_q, max_q, 
     assert (blocks, split) in {(16, 1), (8, 1), (8, 2), (4, 4), (2, 8)}
     if batch > 1:
         assert split <= 2   # a grid of more than 4096 workgroups takes the largest blocks there are
+
+
+@pytest.mark.parametrize("d,kv,longest,mb,more,want", [
+    (128, 0, 4096, 10, -16, [0, 0, 2]), (128, 0, 4096, 10, 0, [1, 256, 2]),      # 10 MB of rows
+    (128, 0, 767, 32, 0, [1, 0, 2]), (128, 0, 768, 32, 0, [1, 256, 2]),          # 384 KB of K/V per head
+    (128, 1, 1535, 32, 0, [1, 0, 2]), (128, 1, 1536, 32, 0, [1, 512, 2]),
+    (64, 0, 1535, 32, 0, [1, 0, 4]), (64, 0, 1536, 32, 0, [1, 512, 4]),
+    (64, 1, 3071, 32, 0, [1, 0, 4]), (64, 1, 3072, 32, 0, [1, 1024, 4]),
+    (128, 0, 2**31 - 16, 2000, 0, [1, 256, 2]),                                  # bytes beyond 32 bits
+])
+def test_rows_that_are_written_through_and_in_windows(rule, d, kv, longest, mb, more, want):
+    """Written through, tokens from which on a workgroup waits for a window, workgroups that a compute unit holds."""
+    assert rule("stores", 1000, 64, 8, d, kv, longest, mb, more, 2 * d * (1 if kv else 2)) == want

@@ -17,6 +17,7 @@ PAGE = 16
     ("bf16", 128, 40, 2, 520, 800, False),     # 20 query heads per KV head: two blocks of rows, 16 and 4
     ("fp8", 128, 64, 8, 340, 2000, False),
     ("fp8", 64, 48, 16, 860, 700, False),
+    ("fp8", 64, 64, 2, 660, 3300, False),      # windows at head_dim 64; 32 query heads per KV head
 ])
 def test_many_rows_equal_the_same_rows_of_smaller_calls(kv, d, Hq, Hkv, B, longest, append):
     import torch

@@ -47,3 +47,16 @@ def test_decode_kernels_keep_their_tiles_in_registers(source, kernels, least, tm
         assert res["ScratchSize"] == 0, (name, res)
         assert res["VGPRs Spill"] == 0, (name, res)
         assert res["Occupancy"] >= 2, (name, res)
+
+
+@pytest.mark.skipif(shutil.which(sd_build.HIPCC) is None and not os.path.exists(sd_build.HIPCC), reason="needs hipcc")
+def test_a_compute_unit_holds_as_many_workgroups_of_the_split_pass_as_its_last_round_counts(tmp_path):
+    """Workgroups of four waves, so waves per SIMD are workgroups per compute unit."""
+    (tmp_path / "round.hip").write_text('#include <cstdio>\n#include "kernels.h"\nint main() { printf("%d %d", sd::split_round(64) / 256, sd::split_round(128) / 256); }\n')
+    r = subprocess.run([sd_build.HIPCC, "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(tmp_path / "round.hip"), "-o", str(tmp_path / "round")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    narrow, wide = map(int, subprocess.run([str(tmp_path / "round")], capture_output=True, text=True, check=True).stdout.split())
+    remarks = {k: v for k, v in resource_remarks("attn_split.hip", tmp_path).items() if "split_kernel" in k}
+    assert len(remarks) >= 10
+    for name, res in remarks.items():
+        assert res["Occupancy"] == (narrow if "Li64" in name or "Fp8Path64" in name else wide), (name, res)
