@@ -673,17 +673,11 @@ int paged_prefill_attention(const sd_shape *shape, const void *q, const int32_t 
     a.total_q = total_q;
     a.max_q_len = max_q_len < total_q ? max_q_len : total_q;
     const int units = sd::units_per_block(a.G);
-    a.plan = sd::prefill_plan(shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
-    a.plan = sd::prefill_halved(a.plan, shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
-    a.plan.on_device = total_q < 1 << 23 && a.max_context_len < 1 << 23 &&
-                       sd::prefill_on_device(a.plan, shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
-    const int tokens_per_wg = (a.plan.on_device ? 8 : a.plan.blocks) * units;
-    a.round_up = tokens_per_wg - 1;
-    a.reciprocal = sd::reciprocal_of((unsigned)tokens_per_wg);
-    const int tokens_per_slot = a.plan.on_device ? tokens_per_wg / 2 : tokens_per_wg;   // (a grid for 4 blocks)
-    a.q_blocks = (int32_t)(((int64_t)a.max_q_len + tokens_per_slot - 1) / tokens_per_slot);
-    // (the reciprocal is exact below 2^24)
-    a.plan.order = total_q < 1 << 24 && a.max_context_len < 1 << 24 ? sd::prefill_order(a.plan, shape->kv_dtype, shape->head_dim, total_q, units, a.B, a.Hkv * a.HB, a.q_blocks, a.max_context_len) : 0;
+    const sd::PrefillRoute route = sd::prefill_route(shape->kv_dtype, shape->head_dim, total_q, a.max_q_len, a.B, a.Hkv * a.HB, units, a.max_context_len);
+    a.plan = route.plan;
+    a.round_up = route.tokens - 1;
+    a.reciprocal = sd::reciprocal_of((unsigned)route.tokens);
+    a.q_blocks = route.q_blocks;
     if ((uint64_t)a.q_blocks * (uint64_t)a.B * (uint64_t)(a.Hkv * a.HB) > 0x7ffffff0ull) return SD_EUNSUPPORTED;
     hipEvent_t none[2] = {nullptr, nullptr};
     hipEvent_t *ev = timer ? &timer->ev[(size_t)timer->calls * 4] : none;

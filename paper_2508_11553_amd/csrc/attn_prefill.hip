@@ -565,7 +565,7 @@ __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs
         const int Hv = a.Hkv * a.HB;
         const WaveLengths lengths(a, lane);
         four = prefill_prefers_four(lengths, Hv, a.round_up + 1);
-        const PrefillBlock at = prefill_pick(lengths.cut(four), (int)(blockIdx.x / Hv), 8);
+        const PrefillBlock at = prefill_pick(lengths.cut(four), (int)(blockIdx.x / Hv), a.plan.order);
         if (at.block < 0) return;
         rows.tpb = units_per_block(a.G);
         if (!rows.take(a, at.b, blockIdx.x % Hv, at.block, four ? 2 : 4, four ? group_of_four : group_of_eight, NB)) return;
@@ -1091,7 +1091,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
                           hipEvent_t stop)
 {
     const unsigned pairs = (unsigned)a.B * (unsigned)(a.Hkv * a.HB);
-    const unsigned grid = a.plan.order || a.plan.on_device ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
+    const unsigned grid = a.plan.order ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
     if (grid == 0) return hipSuccess;
     auto go = [&](auto kernel, int waves) {
         const dim3 g(grid), b(waves * 64);
@@ -1104,12 +1104,10 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
     auto wide = [&](auto path) {   // head_dim 128: one workgroup of 8 waves per compute unit
         typedef decltype(path) P;
         if constexpr (std::is_same<P, Bf16Path<128>>::value) {
-            // (rows enough for the two phases, but not the tiles)
-            const bool full = (int64_t)a.total_q * 4 >= (int64_t)16 * 3 * units_per_block(a.G) * a.B;
             if (a.plan.on_device) return go(prefill_wide_kernel_direct<0>, 8);
             switch (a.plan.blocks) {
             case 16:   // (a context of a few tiles does not pay for the start-up of the two phases: 127 tokens, 32/8 heads 14.7 against 15.9 us)
-                return a.plan.phases ? go(prefill_pingpong_kernel, 8) : full ? go(prefill_direct_kernel<128, 8, 2>, 8) : go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
+                return a.plan.phases ? go(prefill_pingpong_kernel, 8) : a.plan.direct ? go(prefill_direct_kernel<128, 8, 2>, 8) : go(prefill_wide_kernel<P, 8, 4, 1, 2, 2>, 8);
             case 8: return go(prefill_wide_kernel_direct<2>, 8);
             case 4: return go(prefill_wide_kernel_direct<4>, 8);
             default: return go(prefill_wide_kernel_own<128, 8, 2>, 8);

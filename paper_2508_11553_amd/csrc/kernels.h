@@ -112,9 +112,9 @@ __host__ __device__ inline PrefillBlock prefill_pick(const Sequences &s, int k, 
 // range of a block, and whether the workgroups run in two phases (bf16 pools with head_dim 128).
 struct PrefillPlan {
     int blocks, split;
-    bool phases;
-    bool on_device; // 8 or 4 blocks, as the kernel finds better for the lengths (prefill_on_device)
-    int order;      // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
+    bool phases, direct;   // 16 blocks over bf16 pools with head_dim 128: in two phases, or straight into LDS in one
+    bool on_device;        // 8 or 4 blocks, as the kernel finds better for the lengths (prefill_on_device); blocks and split are those of 8
+    int order;             // longest first (prefill_pick), in so many classes; 0: dealt by prefill_item
 };
 // Large blocks share a tile among most rows; small ones give more workgroups, and below 16 (head_dim 128) or 8 (head_dim 64) several
 // waves share a block's range.  The line lies where the workgroups of the next larger block no longer fill the chip: about half a
@@ -165,7 +165,8 @@ struct PrefillPlan {
 // bound of 1302, 4/1 heads 14.6 / 20.8 / 27.5 / 37.8 us with 16 / 8 / 4 / 2 blocks (1155, 2255, 4510 and 8965 workgroups).  No smaller blocks than
 // a grid of 4096 allows.
 // The two phases leave the matrix pipe to the waves in turn, also to those without rows: by the share of the 16 blocks that the average
-// sequence's queries fill, time against one phase: up to 0.1 1.27, 0.2 1.22, 0.3 1.14, 0.5 1.04, 0.8 to 1 0.97, above 4 0.95.
+// sequence's queries fill, time against one phase: up to 0.1 1.27, 0.2 1.22, 0.3 1.14, 0.5 1.04, 0.8 to 1 0.97, above 4 0.95.  So they, and under
+// kPrefillShort tokens, which do not pay for their start-up, the direct loads, are for calls that fill three quarters.
 constexpr int kPrefillShort = 512;
 __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)
 {
@@ -197,7 +198,8 @@ __host__ inline PrefillPlan prefill_plan(int kv_dtype, int head_dim, int64_t tot
         // sequences that fill their blocks is up to 1.5 times their count (101 such calls that it alone puts past the 256 take 0.93 of the time uncut).
         const int64_t w = std::min(workgroups(16), ((int64_t)max_q_len + 16 * units - 1) / (16 * units) * batch * heads);
         const bool just_past = depth == 3 && filled(16, 2) && w > 256 && w < 320;
-        if ((enough(16) && !just_past) || !small_grid(8)) return PrefillPlan{16, 1, depth > 0 && total_q * 4 >= (int64_t)16 * 3 * units * batch};
+        const bool full = total_q * 4 >= (int64_t)16 * 3 * units * batch;
+        if ((enough(16) && !just_past) || !small_grid(8)) return PrefillPlan{16, 1, full && depth > 0, full && depth == 0};
         if (enough(8) || !small_grid(4)) return PrefillPlan{8, 2, false};
         return enough(4) || !small_grid(2) ? PrefillPlan{4, 4, false} : PrefillPlan{2, 8, false};
     }
@@ -285,6 +287,25 @@ __host__ inline bool prefill_on_device(const PrefillPlan &plan, int kv_dtype, in
     if (kv_dtype != 0 || head_dim != 128 || (plan.blocks != 8 && plan.blocks != 4) || batch == 1 || batch > kMaxOrderedBatch || max_context_len < 1536) return false;
     const int64_t most = ((int64_t)max_q_len + 4 * units - 1) / (4 * units) * batch * heads, expected = (total_q / (4 * units) + batch / 2) * heads;
     return most <= 4096 && most <= 2 * expected + 256 && std::max<int64_t>(total_q / (8 * units) + batch / 2, batch) * heads >= 96;
+}
+
+// What runs: the rules above, one after the other.
+struct PrefillRoute {
+    PrefillPlan plan;
+    int tokens;     // query tokens of a workgroup, of 8 blocks where the kernel chooses
+    int q_blocks;   // workgroups that cover max_q_len, of 4 blocks where it does
+};
+__host__ inline PrefillRoute prefill_route(int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)
+{
+    PrefillPlan plan = prefill_plan(kv_dtype, head_dim, total_q, max_q_len, batch, heads, units, max_context_len);
+    plan = prefill_halved(plan, kv_dtype, head_dim, total_q, max_q_len, batch, heads, units, max_context_len);
+    const int64_t most = std::max<int64_t>(total_q, max_context_len);   // the reciprocal is exact below 2^24
+    plan.on_device = most < 1 << 23 && prefill_on_device(plan, kv_dtype, head_dim, total_q, max_q_len, batch, heads, units, max_context_len);
+    if (plan.on_device) plan.blocks = 8, plan.split = 2, plan.order = 8;
+    const int tokens = plan.blocks * units, per_slot = plan.on_device ? tokens / 2 : tokens;
+    const int q_blocks = (int)(((int64_t)max_q_len + per_slot - 1) / per_slot);
+    if (!plan.on_device && most < 1 << 24) plan.order = prefill_order(plan, kv_dtype, head_dim, total_q, units, batch, heads, q_blocks, max_context_len);
+    return PrefillRoute{plan, tokens, q_blocks};
 }
 
 // Chunk slots of one output row.  Without a shared prefix, chunk c covers tokens
@@ -494,9 +515,9 @@ struct PrefillArgs {
     int32_t B, Hq, Hkv, G, HB, max_blocks, max_context_len;  // HB: head blocks per KV head, ceil(G / 16)
     int32_t total_q, max_q_len;  // rows of q; host-known bound on the rows of one sequence
     PrefillPlan plan;
-    uint32_t reciprocal;         // of the query tokens of a workgroup: 2^32 / tokens, rounded up (plan.order)
+    uint32_t reciprocal;         // of the query tokens of a workgroup (PrefillRoute): 2^32 / tokens, rounded up (plan.order)
     int32_t round_up;            // query tokens of a workgroup - 1
-    int32_t q_blocks;            // workgroups (plan.blocks x 16/G query tokens each) that cover max_q_len
+    int32_t q_blocks;            // workgroups that cover max_q_len (PrefillRoute)
 };
 
 struct AppendArgs {

@@ -9,8 +9,8 @@ import oracle
 import workloads
 from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 from tests.test_gpu_parity import check as check_decode, check_fp8, device_workload, sd  # noqa: F401  (sd is a fixture)
-from tests.test_prefill_geometry import (DIRECT, FOUR_CLASSES, LONGEST_FIRST, PLANS, block_case, direct_case, longest_first_case, plan, program,  # noqa: F401
-                                         stretch_case)  # (program is a fixture)
+from tests.test_prefill_geometry import (DIRECT, FOUR_CLASSES, LONGEST_FIRST, PLANS, block_case, context_bound, direct_case, longest_first_case, program,  # noqa: F401
+                                         route, stretch_case)  # (program is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +32,14 @@ def make(lens, nq, Hq, Hkv, d, kv_dtype="bf16", seed=0, **kw):
     q_start = np.concatenate([[0], np.cumsum(nq)]).astype(np.int32)
     q = f32_to_bf16_bits(rng.standard_normal((int(q_start[-1]), Hq, d)).astype(np.float32))
     return wl, q, q_start
+
+
+def make_bound(lens, nq, Hq, Hkv, d, kv_dtype, bound, **kw):
+    """The same under a bound on the context lengths that is not their own."""
+    made = make(lens, nq, Hq, Hkv, d, kv_dtype, **kw, **({"max_blocks_per_seq": -(-bound // 16)} if bound else {}))
+    if bound:
+        made[0].max_context_len = bound
+    return made
 
 
 def ref(wl, q, q_start):
@@ -71,7 +79,7 @@ def test_negative_and_zero_scale(sd, scale, kv_dtype):
 def stretch(kv_dtype, d, plan, seed, **kw):
     """A call that takes the plan, and which of its sequences to hold against the oracle (all but those of the large batches that repeat)."""
     lens, nq, Hq, Hkv = stretch_case(plan, d)
-    return (*make(lens, nq, Hq, Hkv, d, kv_dtype, seed=seed, **kw), lens, min(len(lens), 4) if len(lens) > 9 else len(lens))
+    return (*make_bound(lens, nq, Hq, Hkv, d, kv_dtype, context_bound(plan[0], d), seed=seed, **kw), lens, min(len(lens), 4) if len(lens) > 9 else len(lens))
 
 
 def check_first(wl, q, q_start, seqs, kv_dtype, got=None):
@@ -231,7 +239,7 @@ def test_every_block_size_of_a_workgroup(sd, blocks, kv_dtype, d):
     """Each size of a workgroup's row block (the small ones split the range over the waves) at its edges; one sequence's fp8
     scales include a V scale of 0 and a negative one, which are turned into codes when a page is parked."""
     lens, nq, Hq, Hkv = block_case(blocks, d)
-    wl, q, q_start = make(lens, nq, Hq, Hkv, d, kv_dtype, seed=300 + blocks + d)
+    wl, q, q_start = make_bound(lens, nq, Hq, Hkv, d, kv_dtype, context_bound(blocks, d), seed=300 + blocks + d)
     if kv_dtype == "fp8":
         pages = wl.block_table[len(lens) - 1]
         wl.v_scales[pages[0]] = 0.0
@@ -259,26 +267,28 @@ def test_fp8_value_scales_far_apart(sd, blocks, d):
     check(got, want, "fp8")
 
 
-@pytest.mark.parametrize("blocks,d,L,want", [
-    (16, 128, 300, (16, 1, 0)), (16, 128, 600, (16, 1, 1)), (2, 128, 1100, (2, 8, 0)),   # short contexts, two phases, split ranges
-    (16, 64, 300, (16, 1, 0)), (2, 64, 1100, (2, 8, 0)),
+@pytest.mark.parametrize("blocks,d,L,n,bound,want", [   # n queries of each sequence; the route and whether 16 blocks load straight into LDS
+    (16, 128, 300, 150, None, (16, 1, 0, 1)), (16, 128, 300, 90, None, (16, 1, 0, 0)), (16, 128, 600, 150, None, (16, 1, 1, 0)),   # short contexts, few queries, two phases
+    (2, 128, 1100, 150, None, (2, 8, 0, 0)),   # split ranges
+    (16, 64, 300, 150, None, (8, 1, 0, 0)), (16, 64, 300, 150, 1536, (16, 1, 0, 0)), (2, 64, 1100, 150, None, (2, 8, 0, 0)),
 ])
-def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, program, blocks, d, L, want):
+def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(sd, program, blocks, d, L, n, bound, want):
     """K and V rows of the last 20 tokens are NaN and infinite: rows that end 64 tokens (a tile and a wave's rows) before them
     do not change.  Many sequences of one length, so that waves past their own rows still ride along with their workgroup."""
     B, Hq, Hkv = (40, 16, 8) if blocks == 16 else (1, 8, 4)
     if d == 64 and blocks == 16:
         B, Hq, Hkv = 64, 32, 32
-    lens, nq = [L] * B, [150] * B
-    assert plan(program, lens, nq, Hq, Hkv, d) == want
-    wl, q, q_start = make(lens, nq, Hq, Hkv, d, seed=77)
+    lens, nq = [L] * B, [n] * B
+    got = route(program, lens, nq, Hq, Hkv, d, bound=bound)
+    assert got[:3] + got[4:5] == want
+    wl, q, q_start = make_bound(lens, nq, Hq, Hkv, d, "bf16", bound, seed=77)
     want = gpu(wl, q, q_start)
     for b in range(B):
         for t in range(L - 20, L):
             wl.v_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 2 else 0x7f80
             wl.k_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 3 else 0xff80
-    got = gpu(wl, q, q_start).reshape(B, 150, Hq, d)
-    assert np.array_equal(got[:, :150 - 84], want.reshape(B, 150, Hq, d)[:, :150 - 84])
+    got = gpu(wl, q, q_start).reshape(B, n, Hq, d)
+    assert np.array_equal(got[:, :n - 84], want.reshape(B, n, Hq, d)[:, :n - 84])
 
 
 @pytest.mark.parametrize("B", [2, 64, 65])

@@ -23,10 +23,10 @@ int main(int argc, char **argv)
         return 0;
     }
     if (argc > 3) {
-        const sd::PrefillPlan p = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[8]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
-        const int max_q = std::min(atoll(argv[8]), atoll(argv[2])), tokens = p.blocks * atoi(argv[5]);
-        const int order = sd::prefill_order(p, atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), atoi(argv[5]), atoi(argv[3]), atoi(argv[4]), (max_q + tokens - 1) / tokens, atoi(argv[6]));
-        printf("%d %d %d %d\n", p.blocks, p.split, p.phases, order);
+        const int max_q = std::min(atoll(argv[8]), atoll(argv[2]));
+        const sd::PrefillPlan p = sd::prefill_route(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), max_q, atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])).plan;
+        const sd::PrefillPlan by_rule = sd::prefill_plan(atoi(argv[7]), atoi(argv[1]), atoll(argv[2]), max_q, atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
+        printf("%d %d %d %d %d %d\n", p.on_device ? 0 : p.blocks, p.on_device ? 0 : p.split, p.phases, p.order, p.direct, by_rule.blocks);
         return 0;
     }
     const int q_blocks = atoi(argv[1]), pairs = atoi(argv[2]);
@@ -85,6 +85,11 @@ def block_case(blocks, d):
     return lens, [min(n, L) for n, L in zip(q, lens)], Hq, Hkv
 
 
+def context_bound(blocks, d):
+    """The bound on the context lengths with which such a case of bf16 pools takes 16 blocks at head_dim 64; with their own lengths it takes 8."""
+    return 1536 if (blocks, d) == (16, 64) else None
+
+
 def stretch_case(plan, d):
     """(lens, queries, Hq, Hkv): sequences of 1500, 777 and 96 tokens, or many of 600, that take the plan (blocks, split, phases)."""
     long, many = [1500, 777, 96], [600] * 22 + [33, 511]
@@ -107,12 +112,17 @@ PLANS = [("bf16", 128, (16, 1, 1))] + [(kv, 128, p) for kv in ("bf16", "fp8") fo
 
 
 def plan(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
-    """(column blocks of a workgroup, waves that share a block's range, two phases) of a call."""
-    return plan_and_order(program, lens, q, Hq, Hkv, d, kv_dtype, bound, max_q)[:3]
+    """(column blocks of a workgroup, waves that share a block's range, two phases) of a call as it runs; (0, 0, 0) where the kernel chooses 8 or 4."""
+    return route(program, lens, q, Hq, Hkv, d, kv_dtype, bound, max_q)[:3]
 
 
 def plan_and_order(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
     """The same and the classes of the order in which the workgroups start, 0: dealt pair by pair."""
+    return route(program, lens, q, Hq, Hkv, d, kv_dtype, bound, max_q)[:4]
+
+
+def route(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, max_q=None):
+    """The same, whether 16 blocks load straight into LDS in one phase, and the blocks that the host's rule gives where the kernel does not choose."""
     G = Hq // Hkv
     args = (d, sum(q), len(lens), Hkv * ((G + 15) // 16), 16 // G if G <= 8 else 1, bound or max(lens), int(kv_dtype == "fp8"), max_q or max(q))
     got = subprocess.run([program] + [str(x) for x in args], capture_output=True, text=True, check=True)
@@ -122,12 +132,17 @@ def plan_and_order(program, lens, q, Hq, Hkv, d, kv_dtype="bf16", bound=None, ma
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("blocks", [16, 8, 4, 2])
 def test_the_block_cases_are_what_they_say(program, blocks, d):
-    assert plan(program, *block_case(blocks, d), d)[0] == blocks
+    assert plan(program, *block_case(blocks, d), d, bound=context_bound(blocks, d))[0] == blocks
 
 
 @pytest.mark.parametrize("kv_dtype,d,want", PLANS)
 def test_the_stretch_cases_are_what_they_say(program, kv_dtype, d, want):
-    assert plan(program, *stretch_case(want, d), d, kv_dtype) == want
+    assert plan(program, *stretch_case(want, d), d, kv_dtype, context_bound(want[0], d)) == want
+
+
+@pytest.mark.parametrize("call", [block_case(16, 64), stretch_case((16, 1, 0), 64)])
+def test_the_cases_of_16_blocks_at_head_dim_64_take_8_with_their_own_lengths(program, call):
+    assert plan(program, *call, 64) == (8, 1, 0)
 
 
 def test_two_phases_only_where_most_waves_have_rows(program):
@@ -151,8 +166,10 @@ def test_a_loose_bound_on_the_queries_keeps_the_grid_small(program):
     lens, q = [76] * 55, [23] * 54 + [45]
     assert plan(program, lens, q, 4, 1, 128, bound=548) == (4, 4, 0)
     assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=sum(q)) == (8, 2, 0)
-    assert plan(program, lens, q, 4, 1, 128, bound=548, max_q=20 * sum(q))[0] == 16
-    assert plan(program, [2000] * 8, [100] * 8, 16, 4, 64, max_q=20000)[0] == 8
+    assert plan(program, [76] * 110, [12] * 110, 4, 1, 128, bound=548) == (4, 4, 0)
+    assert plan(program, [76] * 110, [12] * 110, 4, 1, 128, bound=548, max_q=12 * 110)[0] == 16
+    assert plan(program, [2000] * 64, [40] * 64, 8, 2, 64)[0] == 4
+    assert plan(program, [2000] * 64, [40] * 64, 8, 2, 64, max_q=40 * 64)[0] == 8
 
 
 EDGES = [1, 16, 31, 32, 33, 63, 65, 127, 128, 129, 255, 257, 290]   # contexts that end at pages, tiles and rounds of 2, 4 and 8 tiles
@@ -176,19 +193,20 @@ def test_short_and_longer_contexts_take_every_split(program, d, blocks, short):
 @pytest.mark.parametrize("batch,blocks", [(11, 8), (12, 16), (15, 16), (16, 16), (17, 8), (19, 8), (20, 16)])
 def test_one_round_of_large_workgroups_stays_and_a_few_more_are_cut(program, batch, blocks):
     """Long contexts over bf16 pools: 16 workgroups per sequence, 256 of which run at once."""
-    assert plan(program, [4000] * batch, [96] * batch, 32, 8, 128)[0] == blocks
+    assert route(program, [4000] * batch, [96] * batch, 32, 8, 128)[5] == blocks
 
 
 @pytest.mark.parametrize("batch,blocks", [(22, 16), (32, 16), (33, 8), (34, 8), (39, 8), (40, 16)])
 def test_one_round_is_counted_by_full_blocks_where_all_are_full(program, batch, blocks):
     """8 workgroups per sequence without an empty row."""
-    assert plan(program, [4000] * batch, [64] * batch, 32, 8, 128)[0] == blocks
+    assert route(program, [4000] * batch, [64] * batch, 32, 8, 128)[5] == blocks
 
 
 @pytest.mark.parametrize("q,blocks", [(176, 4), (184, 8), (216, 8), (232, 8)])
 def test_long_contexts_over_bf16_pools_are_cut_below_8_blocks_where_192_workgroups_are_not_reached(program, q, blocks):
-    """Two sequences of long contexts: 184, 192, 224 and 240 workgroups of 8 blocks."""
-    assert plan(program, [8000] * 2, [q] * 2, 64, 8, 128)[0] == blocks
+    """Two sequences of long contexts: 184, 192, 224 and 240 workgroups of 8 blocks.  (The host's rule; with bounds as tight as these the kernel chooses.)"""
+    assert route(program, [8000] * 2, [q] * 2, 64, 8, 128)[5] == blocks
+    assert plan(program, [8000] * 2, [q] * 2, 64, 8, 128) == (0, 0, 0)
 
 
 LONGEST_FIRST = [(6, 2, 128, "bf16"), (4, 4, 64, "bf16"), (8, 2, 128, "fp8")]
@@ -198,7 +216,7 @@ def longest_first_case(B, Hq, Hkv, d):
     """(lens, queries, Hq, Hkv) of batches with two long sequences; larger ones also have sequences without queries, with more queries than tokens, and
     empty ones."""
     if B == 2:
-        return [2300, 1100], [1400, 1100], *((16, 16) if d == 64 else (Hq, Hkv))
+        return [2300 if d == 64 else 1500, 1100], [1400, 1100], *((16, 16) if d == 64 else (Hq, Hkv))
     rng = np.random.default_rng(B)
     lens = [1100, 530] + [int(x) for x in rng.integers(0, 300, B - 2)]
     nq = [700, 530] + [int(x) for x in rng.integers(0, 60, B - 2)]
@@ -209,7 +227,8 @@ def longest_first_case(B, Hq, Hkv, d):
 @pytest.mark.parametrize("B,classes", [(2, 8), (64, 8), (65, 0)])
 @pytest.mark.parametrize("Hq,Hkv,d,kv_dtype", LONGEST_FIRST)
 def test_the_longest_first_cases_are_what_they_say(program, Hq, Hkv, d, kv_dtype, B, classes):
-    assert plan_and_order(program, *longest_first_case(B, Hq, Hkv, d), d, kv_dtype)[3] == classes
+    blocks, _, _, order = plan_and_order(program, *longest_first_case(B, Hq, Hkv, d), d, kv_dtype)
+    assert order == classes and blocks   # not left to the kernel
 
 
 FOUR_CLASSES = ([1300, 1200, 1250, 700, 330, 1300, 1100, 40], [1300, 900, 1250, 700, 200, 1100, 1100, 40], 32, 32, 64)   # ragged
@@ -221,7 +240,7 @@ def test_large_calls_are_ordered_in_four_classes(program, call, want):
     assert plan_and_order(program, *call) == want
 
 
-@pytest.mark.parametrize("lens,q,classes", [([8000], [4096], 0), ([8000, 7000], [512, 512], 0), ([8000, 7000], [528, 512], 8)])
+@pytest.mark.parametrize("lens,q,classes", [([8000], [4096], 0), ([1500, 1400], [512, 512], 0), ([1500, 1400], [528, 512], 8)])
 def test_single_sequences_and_calls_that_run_at_once_are_dealt(program, lens, q, classes):
     """Workgroups of 32 queries, 256 of which run at once."""
     assert plan_and_order(program, lens, q, 32, 8, 128) == ((16, 1, 1) if len(lens) == 1 else (8, 2, 0)) + (classes,)
