@@ -565,10 +565,10 @@ __global__ __launch_bounds__(512, 2) void prefill_wide_kernel_direct(PrefillArgs
         const int Hv = a.Hkv * a.HB;
         const WaveLengths lengths(a, lane);
         four = prefill_prefers_four(lengths, Hv, a.round_up + 1);
-        const PrefillBlock at = prefill_pick(lengths.cut(four), (int)(blockIdx.x / Hv), a.plan.order);
+        const PrefillSlot at = prefill_slot(lengths.cut(four), blockIdx.x, Hv);
         if (at.block < 0) return;
         rows.tpb = units_per_block(a.G);
-        if (!rows.take(a, at.b, blockIdx.x % Hv, at.block, four ? 2 : 4, four ? group_of_four : group_of_eight, NB)) return;
+        if (!rows.take(a, at.b, at.head, at.block, four ? 2 : 4, four ? group_of_four : group_of_eight, NB)) return;
     } else {
         if (!rows.find(a, kW / kSplit, four ? group_of_four : group_of_eight, NB)) return;
     }
@@ -1091,7 +1091,7 @@ hipError_t launch_prefill(const PrefillArgs &a, int head_dim, int kv_dtype, hipS
                           hipEvent_t stop)
 {
     const unsigned pairs = (unsigned)a.B * (unsigned)(a.Hkv * a.HB);
-    const unsigned grid = a.plan.order ? pairs * (unsigned)a.q_blocks : prefill_grid(a.q_blocks, pairs);
+    const unsigned slots = pairs * (unsigned)a.q_blocks, grid = a.plan.on_device ? (slots + kXcds - 1) / kXcds * kXcds : a.plan.order ? slots : prefill_grid(a.q_blocks, pairs);
     if (grid == 0) return hipSuccess;
     auto go = [&](auto kernel, int waves) {
         const dim3 g(grid), b(waves * 64);

@@ -108,6 +108,28 @@ __host__ __device__ inline PrefillBlock prefill_pick(const Sequences &s, int k, 
     const auto at = s.find([above, lo, hi](int end, int blocks) { return above(lo, end, blocks) - above(hi, end, blocks); }, k - higher);
     return PrefillBlock{at.b, at.blocks - 1 - above(hi, at.end, at.blocks) - (k - higher - at.before)};
 }
+// The block that workgroup i of a call takes whose size the kernel has chosen: longest first (head fastest); but where all workgroups run at once, so that
+// their order is of no account, and a head would not keep its die (heads no multiple of 8), pair by pair, as many workgroups to every die: the blocks of all
+// but 7 pairs meet on one die, where the others find in its L2 what the first fetches.  (Random calls that this applies to, longest first over pair by pair: 2 heads
+// 1.04 with 8 blocks, 1.17 with 4, 4 heads 1.04 and 1.08; 27 sequences of 7.6 - 8.4 k, 51 queries, 8/2 heads, 4 blocks 124 : 78 us.)  The grid has a multiple
+// of 8 workgroups, at least as many as there are blocks.
+constexpr int kChosenClasses = 8;
+struct PrefillSlot {
+    int b, head, block;   // block < 0: nothing to do
+};
+template <class Sequences>
+__host__ __device__ inline PrefillSlot prefill_slot(const Sequences &s, unsigned i, int heads)
+{
+    const int n = s.sum([](int, int blocks) { return blocks; }) * heads;
+    if (heads % kXcds == 0 || n > 256) {
+        const PrefillBlock at = prefill_pick(s, (int)(i / heads), kChosenClasses);
+        return PrefillSlot{at.b, (int)(i % heads), at.block};
+    }
+    const int per_die = (n + kXcds - 1) / kXcds, k = (int)(i / kXcds), r = (int)(i % kXcds) * per_die + k;
+    if (k >= per_die || r >= n) return PrefillSlot{0, 0, -1};
+    const auto at = s.find([heads](int, int blocks) { return blocks * heads; }, r);
+    return PrefillSlot{at.b, (r - at.before) / at.blocks, at.blocks - 1 - (r - at.before) % at.blocks};
+}
 // How a call of the causal pass is cut: column blocks of 16 query rows that a workgroup owns (16, 8, 4 or 2), the waves that share the
 // range of a block, and whether the workgroups run in two phases (bf16 pools with head_dim 128).
 struct PrefillPlan {
@@ -301,7 +323,7 @@ __host__ inline PrefillRoute prefill_route(int kv_dtype, int head_dim, int64_t t
     plan = prefill_halved(plan, kv_dtype, head_dim, total_q, max_q_len, batch, heads, units, max_context_len);
     const int64_t most = std::max<int64_t>(total_q, max_context_len);   // the reciprocal is exact below 2^24
     plan.on_device = most < 1 << 23 && prefill_on_device(plan, kv_dtype, head_dim, total_q, max_q_len, batch, heads, units, max_context_len);
-    if (plan.on_device) plan.blocks = 8, plan.split = 2, plan.order = 8;
+    if (plan.on_device) plan.blocks = 8, plan.split = 2, plan.order = kChosenClasses;
     const int tokens = plan.blocks * units, per_slot = plan.on_device ? tokens / 2 : tokens;
     const int q_blocks = (int)(((int64_t)max_q_len + per_slot - 1) / per_slot);
     if (!plan.on_device && most < 1 << 24) plan.order = prefill_order(plan, kv_dtype, head_dim, total_q, units, batch, heads, q_blocks, max_context_len);

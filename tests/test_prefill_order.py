@@ -12,6 +12,7 @@ from tests.test_kernel_resources import CSRC
 PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 #include "kernels.h"
 struct Sequences {
@@ -39,6 +40,16 @@ int main(int argc, char **argv)
             for (unsigned q = 1; t > 1 && q < (1u << 24) / t; q += q < 64 ? 1 : q / 7) bad += (uint64_t)(q * t) * r >> 32 != q || (uint64_t)(q * t - 1) * r >> 32 != q - 1;
         }
         printf("%ld\n", bad);
+        return 0;
+    }
+    if (!strcmp(argv[1], "slots")) {   // heads, slots of a (sequence, head) pair; what every workgroup of the grid takes
+        Sequences s;
+        for (int i = 4; i + 1 < argc; i += 2) s.end.push_back(atoi(argv[i])), s.blocks.push_back(atoi(argv[i + 1]));
+        const int heads = atoi(argv[2]), slots = (int)s.end.size() * heads * atoi(argv[3]);
+        for (int i = 0; i < (slots + 7) / 8 * 8; ++i) {
+            const sd::PrefillSlot p = sd::prefill_slot(s, i, heads);
+            if (p.block >= 0) printf("%d %d %d %d\n", i, p.b, p.head, p.block);
+        }
         return 0;
     }
     const int classes = atoi(argv[1]);
@@ -92,3 +103,22 @@ def test_every_block_once_and_longest_first(program, kind, classes):
 
 def test_the_reciprocal_divides_exactly(program):
     assert subprocess.run([program, "-"], capture_output=True, text=True, check=True).stdout == "0\n"
+
+
+@pytest.mark.parametrize("heads", [1, 2, 4, 8, 12, 16])
+@pytest.mark.parametrize("kind", ["one", "edges", "few", "64", "equal"])
+def test_workgroups_of_calls_whose_size_the_kernel_chooses(program, kind, heads):
+    """Every block of every head once; where all run at once and a head would not keep its die, as many on every die and a pair on one die, but for 7."""
+    seqs = {"few": [(90, 3), (12, 1), (70, 5), (33, 2), (8, 2)]}.get(kind) or sequences(kind, random.Random(7))
+    args = [str(x) for e in seqs for x in e]
+    lines = subprocess.run([program, "slots", str(heads), str(max(n for _, n in seqs))] + args, capture_output=True, text=True, check=True).stdout.splitlines()
+    got = [tuple(map(int, l.split())) for l in lines]
+    n = sum(b for _, b in seqs) * heads
+    assert sorted(g[1:] for g in got) == sorted((b, h, j) for b, (_, blocks) in enumerate(seqs) for h in range(heads) for j in range(blocks))
+    if heads % 8 == 0 or n > 256:
+        order = [tuple(map(int, l.split())) for l in subprocess.run([program, "8"] + args, capture_output=True, text=True, check=True).stdout.splitlines()]
+        assert [g[1:] for g in got] == [(b, h, j) for b, j in order for h in range(heads)]
+        return
+    dies = [[g[1:3] for g in got if g[0] % 8 == die] for die in range(8)]
+    assert max(map(len, dies)) <= -(-n // 8)
+    assert sum(len(set(d)) for d in dies) <= len({g[1:3] for g in got}) + 7
