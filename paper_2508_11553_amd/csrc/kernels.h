@@ -278,11 +278,14 @@ __host__ inline int prefill_order(const PrefillPlan &plan, int kv_dtype, int hea
 
 // 8 or 4 blocks, by the lengths themselves.  The host knows bounds and totals: calls of equal lengths want 8 blocks from 192 workgroups on, ragged ones, whose longest
 // range sets the end, many more.  From 1536 tokens on, from 96 workgroups of 8 blocks on and while the grid for 4 is not mostly empty, the kernel
-// therefore decides.  Every workgroup estimates both times: a range of `longest` tiles or the chip's share of all tiles, whichever is more; the share of a last
-// round that is not full, the less the more lengths differ; and a start per round.  us per tile and factor are fitted to 601 random calls (2 to 32 sequences, 1.5 k to 16 k
-// tokens, 8 - 2048 queries, heads as in perf/cases.py), each timed with both sizes: 1.025 times as fast as by the host's rule (1.037 with the better size of
-// each call), 86 gain more than 8 % and 14 lose that much; of 219 others 1.035, 31 and 4.  (The worst fetch more K/V than the estimate knows: 24 sequences of
-// 6.8 - 15.6 k, 15 queries, 64/8 heads 253 -> 310 us.)  5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads: 220 workgroups of 8 blocks 85 us, 432 of 4 61.
+// therefore decides.  Every workgroup estimates both times: a range of `longest` tiles or the chip's share of all tiles, whichever is more, and the share of a last
+// round that is not full, the less the more lengths differ; or, if that is more, what the memory takes for the tiles, which are 16 KB each: workgroups
+// of a pair find half of what the others of their die fetch in its L2; and a start per round.  (Without the memory, sequences whose queries
+// fit one workgroup of 8 blocks and need two of 4 were read twice: 24 of 6.8 - 15.6 k, 15 queries, 64/8 heads 290 us, with it 244.)  us per tile and factors are fitted to 2250
+// random calls (2 to 64 sequences, 1.5 k to 16 k tokens, heads as in perf/cases.py), each timed with both sizes.  Against the host's rule, times as fast and calls that gain and lose
+// more than 8 %, of 1300 with one to three workgroups of 8 blocks a sequence 1.047, 262 and 5 (without the memory 1.033, 245 and 58), of 1500 with 8 - 2048
+// queries 1.023, 214 and 14 (1.022, 219 and 28).  (The better size of each call would give 1.057 and 1.034.)
+// 5 sequences of 300 - 6000, 17 - 300 queries, 28/4 heads: 220 workgroups of 8 blocks 81 us, 432 of 4 61.
 //
 // Deciding costs 1 us, so shorter contexts keep the host's rule (300 calls under 1024 tokens .98), and fewer workgroups (.97), of which none is better with 8.
 //
@@ -293,15 +296,17 @@ __host__ __device__ inline bool prefill_prefers_four(const Sequences &s, int hea
     const float longest = (float)((s.longest() + kTileTokens - 1) / kTileTokens);
     const auto time = [&](int halves, float tile) {
         const int own = tokens >> halves;
-        const float n = (float)(s.total([&](int nq, int) { return s.count(nq, halves); }) * heads);
-        const float walked = (float)s.total([&](int nq, int L) {   // the ends of a sequence's blocks grow evenly
-            return s.count(nq, halves) * ((L + (L > nq ? L - nq : 0) + (nq < own ? nq : own)) / (2 * kTileTokens));
-        }) * (float)heads;
-        const float rounds = n / 256, share = walked / 256, average = walked / (n > 1 ? n : 1);
-        const float last = rounds > 1 ? 0.5f * ((float)(int)(rounds + 0.999f) - rounds) * average * average / (longest > 1 ? longest : 1) : 0;
-        return tile * ((longest > share ? longest : share) + last) + 5 * (rounds > 1 ? rounds : 1);
+        const auto tiles = [&](int nq, int L) { return (L + (L > nq ? L - nq : 0) + (nq < own ? nq : own)) / (2 * kTileTokens); };   // a block's, on average: their ends grow evenly
+        const int count = s.total([&](int nq, int) { return s.count(nq, halves); }) * heads;
+        const int dies = heads % kXcds == 0 || count <= 256 ? 1 : heads % 4 == 0 ? 2 : heads % 2 == 0 ? 4 : 8;   // over which a pair's blocks spread (prefill_slot)
+        const float n = (float)count, walked = (float)s.total([&](int nq, int L) { return s.count(nq, halves) * tiles(nq, L); }) * (float)heads;
+        const float fetched = (float)s.total([&](int nq, int L) { const int c = s.count(nq, halves); return (c < dies ? c : dies) * tiles(nq, L); }) * (float)heads;
+        const float rounds = n / 256, share = walked / 256, average = walked / (n > 1 ? n : 1), level = average / (longest > 1 ? longest : 1);
+        const float last = rounds > 1 ? 0.5f * ((float)(int)(rounds + 0.999f) - rounds) * average * level * level : 0;
+        const float compute = tile * ((longest > share ? longest : share) + last), memory = 0.0012f * walked + 0.0008f * fetched;
+        return (compute > memory ? compute : memory) + 5 * (rounds > 1 ? rounds : 1);
     };
-    return 0.7f * time(0, 0.524f) >= time(1, 0.265f);
+    return 0.75f * time(0, 0.524f) >= time(1, 0.3f);
 }
 // Whether the choice is left to the kernel.
 __host__ inline bool prefill_on_device(const PrefillPlan &plan, int kv_dtype, int head_dim, int64_t total_q, int max_q_len, int batch, int heads, int units, int max_context_len)

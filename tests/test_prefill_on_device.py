@@ -78,6 +78,14 @@ def test_ragged_calls_take_four_blocks_and_even_ones_eight(choose):
     assert choose([2000] * 4, [30] * 4, 64, 8)[2] == 1                                              # half a round of 8
 
 
+def test_memory_bound_calls_are_not_read_twice(choose):
+    """15 queries fit one workgroup of 8 blocks and need two of 4, both of which read the sequence's K/V."""
+    assert choose([6800 + 383 * b for b in range(24)], [15] * 24, 64, 8)[1:] == (1, 0)
+    assert choose([6800 + 383 * b for b in range(24)], [8] * 24, 64, 8)[1:] == (1, 1)     # one of 4
+    assert choose([7601 + 32 * b for b in range(27)], [34] * 27, 16, 2)[1:] == (1, 0)     # 3 of 8, all at once
+    assert choose([1963 + 60 * b for b in range(13)], [33] * 13, 32, 4)[1:] == (1, 0)
+
+
 def test_calls_that_stay_with_the_host(choose):
     assert not choose([8000], [600], 28, 4)[1]                                  # one sequence: the bound is its length
     assert not choose([1500] * 5, [200] * 5, 28, 4)[1]                          # short contexts
