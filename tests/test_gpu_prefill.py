@@ -47,11 +47,22 @@ def ref(wl, q, q_start):
                                           wl.scale, wl.k_scales, wl.v_scales, wl.kv_dtype)
 
 
-def gpu(wl, q, q_start):
+def gpu(wl, q, q_start, max_q=None):
+    """The rows, NaN where nothing was written."""
     import torch
-    out = device_workload(wl).attend_prefill(q, q_start)
+    out = torch.full((len(q), wl.num_q_heads, wl.head_dim), float("nan"), device="cuda:0")
+    device_workload(wl).attend_prefill(q, q_start, out=out, max_q=max_q)
     torch.cuda.synchronize()
     return out.cpu().numpy()
+
+
+def poison(wl, lens):
+    """Slots of the pool past a sequence's end hold NaN and infinity (fp8: NaN)."""
+    for b, L in enumerate(lens):
+        if L % 16:
+            page = wl.block_table[b, L // 16]
+            wl.k_pages[page, :, L % 16:] = 0x7f if wl.kv_dtype == "fp8" else 0x7fc0
+            wl.v_pages[page, :, L % 16:] = 0x7f if wl.kv_dtype == "fp8" else 0x7f80
 
 
 @pytest.mark.parametrize("kv_dtype,d", [("bf16", 64), ("bf16", 128), ("fp8", 128), ("fp8", 64)])
@@ -311,9 +322,21 @@ def test_split_ranges_that_end_at_pages_tiles_and_rounds(sd, d, blocks, short):
     """Slots of the pool past a sequence's end hold NaN and infinity: what is loaded for tokens that do not exist must not reach any row."""
     lens, nq, Hq, Hkv = direct_case(blocks, short, d)
     wl, q, q_start = make(lens, nq, Hq, Hkv, d, seed=120 + blocks)
-    for b, L in enumerate(lens):
-        if L % 16:
-            page = wl.block_table[b, L // 16]
-            wl.k_pages[page, :, L % 16:] = 0x7fc0
-            wl.v_pages[page, :, L % 16:] = 0x7f80
+    poison(wl, lens)
+    check(gpu(wl, q, q_start), ref(wl, q, q_start))
+
+
+@pytest.mark.parametrize("kv_dtype,d,plan", PLANS)
+def test_slots_past_the_end_hold_anything_in_every_kernel(sd, kv_dtype, d, plan):
+    wl, q, q_start, lens, seqs = stretch(kv_dtype, d, plan, 140 + d)
+    poison(wl, lens)
+    check_first(wl, q, q_start, seqs, kv_dtype)
+
+
+@pytest.mark.parametrize("blocks", [16, 8])
+def test_large_blocks_of_head_dim_64_that_end_at_pages_tiles_and_rounds(sd, blocks):
+    """Like the split ranges above, for the two sizes that load straight into LDS."""
+    lens, nq, Hq, Hkv = block_case(blocks, 64)
+    wl, q, q_start = make_bound(lens, nq, Hq, Hkv, 64, "bf16", context_bound(blocks, 64), seed=160 + blocks)
+    poison(wl, lens)
     check(gpu(wl, q, q_start), ref(wl, q, q_start))

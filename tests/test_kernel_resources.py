@@ -39,14 +39,16 @@ def resource_remarks(source, tmp_path):
 @pytest.mark.skipif(shutil.which(sd_build.HIPCC) is None and not os.path.exists(sd_build.HIPCC), reason="needs hipcc")
 @pytest.mark.parametrize("source,kernels,least", [("attn_range.hip", "range_kernel", 8), ("attn_range.hip", "range_merge_kernel", 6),
                                                    ("attn_split.hip", "split_kernel", 10), ("attn_prefill.hip", "prefill_wide_kernel", 15),
-                                                   ("attn_prefill.hip", "prefill_pingpong_kernel", 1), ("attn_prefill.hip", "prefill_direct_kernel", 1)])
+                                                   ("attn_prefill.hip", "prefill_pingpong_kernel", 1), ("attn_prefill.hip", "prefill_direct_kernel", 3),
+                                                   ("attn_prefill.hip", "prefill_wide_kernel_direct", 3), ("attn_prefill.hip", "prefill_wide_kernel_own", 3)])
 def test_decode_kernels_keep_their_tiles_in_registers(source, kernels, least, tmp_path):
     remarks = {k: v for k, v in resource_remarks(source, tmp_path).items() if kernels in k}
     assert len(remarks) >= least, list(remarks)
     for name, res in remarks.items():
         assert res["ScratchSize"] == 0, (name, res)
         assert res["VGPRs Spill"] == 0, (name, res)
-        assert res["Occupancy"] >= 2, (name, res)
+        # (three workgroups to a compute unit are what the small blocks of head_dim 64 gain by)
+        assert res["Occupancy"] >= (3 if "prefill_direct_kernelILi64ELi4ELi2E" in name else 2), (name, res)
 
 
 @pytest.mark.skipif(shutil.which(sd_build.HIPCC) is None and not os.path.exists(sd_build.HIPCC), reason="needs hipcc")

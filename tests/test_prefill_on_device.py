@@ -8,6 +8,7 @@ import pytest
 
 from paper_2508_11553_amd import build as sd_build
 from tests.test_kernel_resources import CSRC
+from tests.test_prefill_geometry import plan, program  # noqa: F401  (program is a fixture)
 
 PROGRAM = r"""
 #include <algorithm>
@@ -93,15 +94,112 @@ def test_calls_that_stay_with_the_host(choose):
     assert not choose([4092, 5323, 3358, 2488, 1434], [112, 20, 190, 274, 254], 28, 4, bound=1000)[1]   # a grid mostly empty
 
 
+# 120 workgroups of 8 blocks and 200 of 4; 240 and 400
+LEVEL = {5: True, 10: False}
+
+
+@pytest.mark.parametrize("B", LEVEL)
+def test_what_the_kernel_takes_for_level_calls(choose, B):
+    assert choose([1600] * B, [150] * B, 16, 8)[1:] == (1, LEVEL[B])
+
+
+# (lens, queries), whether the kernel takes 4 blocks.  The first sequence alone is the host's: 8 blocks under its own bound on the length, 4 under 2048
+ALONE = {"ragged": ([1990, 200], [590, 200], True), "alike": ([1990, 1980], [640, 640], False)}
+
+
+@pytest.mark.parametrize("name", ALONE)
+def test_the_first_sequence_alone_takes_either_size(choose, program, name):  # noqa: F811
+    lens, nq, four = ALONE[name]
+    assert choose(lens, nq, 28, 4)[2] == four
+    assert plan(program, lens, nq, 28, 4, 128, bound=4096) == (0, 0, 0)
+    assert plan(program, lens[:1], nq[:1], 28, 4, 128) == (8, 2, 0) and plan(program, lens[:1], nq[:1], 28, 4, 128, bound=2048) == (4, 4, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ALONE)
+def test_the_size_that_runs_is_the_one_the_lengths_ask_for(name):
+    """Bit for bit the rows of the first sequence by the host's kernel of that size, and not those of the other."""
+    from tests.test_gpu_prefill import gpu, make_bound
+
+    lens, nq, four = ALONE[name]
+    wl, q, q_start = make_bound(lens, nq, 28, 4, 128, "bf16", 4096, seed=82)
+    rows = q_start[1]
+    got = gpu(wl, q, q_start)[:rows]
+    wl.batch, wl.block_table, wl.context_lens = 1, wl.block_table[:1], wl.context_lens[:1]
+    by_size = {}
+    for size, bound in ((8, lens[0]), (4, 2048)):
+        wl.max_context_len = bound
+        by_size[size] = gpu(wl, q[:rows], q_start[:2])
+    assert np.array_equal(got, by_size[4 if four else 8])
+    assert not np.array_equal(by_size[4], by_size[8])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", CASES)
-def test_both_choices_against_the_oracle(name):
+@pytest.mark.parametrize("what", ["plain", "negative scale", "zero scale", "constant V", "ramp", "jumps", "decay", "not finite past the end"])
+def test_both_choices_against_the_oracle(name, what):
     import paper_2508_11553_amd as sd
-    from tests.test_gpu_prefill import check, gpu, make, ref
+    from tests.test_gpu_prefill import check, gpu, grow, make, poison, ref
 
     sd.load()
     (lens, nq, Hq, Hkv), _ = CASES[name]
-    wl, q, q_start = make(lens, nq, Hq, Hkv, 128, seed=81)
+    wl, q, q_start = make(lens, nq, Hq, Hkv, 128, seed=81, **{"negative scale": dict(scale=-0.11), "zero scale": dict(scale=0.0)}.get(what, {}))
+    if what == "constant V":
+        wl.v_pages[...] = 0x3ec0   # 0.375
+        got, seen = gpu(wl, q, q_start), np.concatenate([np.arange(n) >= n - L for L, n in zip(lens, nq)])   # rows that see a token
+        assert np.abs(got[seen] - 0.375).max() <= 2e-6 and not got[~seen].any()
+        return
+    if what in ("ramp", "jumps", "decay"):
+        grow(wl, lens, what, "bf16")
+    if what == "not finite past the end":
+        poison(wl, lens)
     got = gpu(wl, q, q_start)
-    assert not np.isnan(got).any()
+    assert not np.isnan(got).any()   # every row was written
     check(got, ref(wl, q, q_start))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CASES)
+def test_looser_bounds_change_nothing(name, choose):
+    from tests.test_gpu_prefill import gpu, make_bound
+
+    (lens, nq, Hq, Hkv), _ = CASES[name]
+    wide = max(nq) + 4   # more slots of a sequence in all but one
+    assert choose(lens, nq, Hq, Hkv, bound=wide)[1:] == choose(lens, nq, Hq, Hkv)[1:]
+    wl, q, q_start = make_bound(lens, nq, Hq, Hkv, 128, "bf16", 6000, seed=83)
+    loose = gpu(wl, q, q_start, max_q=wide)
+    wl.max_context_len = max(lens)
+    assert np.array_equal(loose, gpu(wl, q, q_start))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CASES)
+def test_ranges_outside_of_the_rows_are_skipped(name):
+    from tests.test_gpu_prefill import check, gpu, make, ref
+
+    (lens, nq, Hq, Hkv), _ = CASES[name]
+    wl, q, q_start = make(lens, nq, Hq, Hkv, 128, seed=84)
+    last = max(b for b, n in enumerate(nq) if n)   # its range is to end behind the rows, that of the first sequence to begin before them
+    bad = q_start.copy()
+    bad[0], bad[last + 1:] = -3, len(q) + 8
+    got = gpu(wl, q, bad, max_q=max(nq) + 8)
+    inner = slice(q_start[1], q_start[last])
+    assert np.isnan(got[:q_start[1]]).all() and np.isnan(got[q_start[last]:]).all()
+    check(got[inner], ref(wl, q, q_start)[inner])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", LEVEL)
+def test_later_tokens_that_are_not_finite_do_not_reach_earlier_rows(B):
+    """K and V rows of the last 20 tokens: rows that end a tile and a wave's rows before them do not change."""
+    from tests.test_gpu_prefill import gpu, make
+
+    L, n = 1600, 150
+    wl, q, q_start = make([L] * B, [n] * B, 16, 8, 128, seed=85)
+    want = gpu(wl, q, q_start)
+    for b in range(B):
+        for t in range(L - 20, L):
+            wl.v_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 2 else 0x7f80
+            wl.k_pages[wl.block_table[b, t // 16], :, t % 16] = 0x7fc0 if t % 3 else 0xff80
+    got = gpu(wl, q, q_start)
+    assert np.array_equal(got.reshape(B, n, -1)[:, :n - 84], want.reshape(B, n, -1)[:, :n - 84])
