@@ -42,7 +42,7 @@ SD_DEV int shared_tokens(const SplitArgs &a, int b) { return shared_tokens(a, ma
 // descending, in order within a class.  Every wave works it out for itself, 64 sequences to a register, counted by ballots; about 1 us that the
 // other workgroup of the compute unit mostly hides, but not from workgroups of a few tiles: if none of the n is long, the order stays.
 // (All loads are on their way before the first is looked at: behind the tile loads of the workgroup beside it each trip takes about 2 us,
-// and four of them in a row made a workgroup's start 9 us long instead of 5.5.)
+// and four of them in a row made a workgroup's start 9 us long instead of 5.5.  26 calls that are ordered gain 0.1 % by it, fp8 batches of up to 2 k tokens 1 %.)
 template <class Load, class Key>
 SD_DEV int longest_first(int sequences, int k, int lane, Load load, Key key)
 {

@@ -74,7 +74,7 @@ SD_DEV T kv_load(const T *p)
 
 // 16 bytes per lane to byte `offset` of the `bytes` at `dst` (wave-uniform), written through the L2 of the die.  Memory that is being read
 // at its full rate pays for every change of direction: 33 MB of finished rows that left the L2s one by one, as streaming reads displaced them, cost
-// a launch that reads 5 GB 84 us (773 : 690 us with the stores taken out); written through as they come 62 (752).  Partial results, which another
+// a launch that reads 5 GB 90 us (780 : 690 us with the stores taken out); written through as they come 61 (751).  Partial results, which another
 // launch reads at once, are better kept in the caches (shared-prefix step 432 : 444 us).
 SD_DEV void store_through(float *dst, int bytes, int offset, f32x4 x)
 {

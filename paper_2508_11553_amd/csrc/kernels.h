@@ -143,10 +143,10 @@ struct PrefillPlan {
 // workgroup per compute unit at head_dim 128, which runs one at a time, and one at head_dim 64, which runs two or three.  Workgroups whose
 // rows are mostly empty end early, and long ranges gain more by being shared, so both move the line up.
 // The lines over bf16 pools at head_dim 128 are fitted to 1740 random calls (1 to 24 sequences of 200 to 16 k tokens, 8 to 2048 queries, heads as in
-// perf/cases.py), each timed with every block size; the rule costs 1.8 % over the best size of each call on average, 136 calls take more than 1.1 and 64 more than 1.2 of it.
-// (8 or 4 blocks from 2048 tokens on, 800 more calls drawn for it: 0.99 of the time with 8 from 176 workgroups on, 0.94 from 192 to 255.  Which calls do better with 4 is a matter
-// of the context lengths, which are on the device: 1.08 where their mean is under three quarters of the longest, 0.91 otherwise.  5 sequences of 300 - 6000,
-// 17 - 300 queries, 28/4 heads have 220: 85 us with 8 blocks, 60 with 4.)  Geometric mean of the time with 16 / 8, 8 / 4 and
+// perf/cases.py), each timed with every block size; by these lines alone a call takes 1.8 % more than with the best size on average, 136 take more than 1.1 and 64 more than 1.2 of it.
+// From 1536 tokens on whether 8 or 4 blocks suit a call is a matter of how its lengths are spread: there the kernel chooses (prefill_on_device; with the better of the two for every
+// call that it may choose for 1.5 %, 110 and 56), and the lines of 8 and 4 hold for the rest: under 96 workgroups of 8 blocks, single sequences, more than 64, loose bounds on the
+// queries.  (192 for 8 over 4 blocks from 2048 tokens on: 800 calls drawn for it, .99 of the time with 8 from 176 workgroups on, .94 from 192 to 255.)  Geometric mean of the time with 16 / 8, 8 / 4 and
 // 4 / 2 blocks by workgroups of the larger block, half of its rows in use or more:
 //   workgroups              24 - 95   96 - 134   135 - 191   192 - 270   271 - 383   384 - 542   543 and more
 //   under 512 tokens   16    1.17      1.12        0.82        0.86        0.84        0.79       0.73
@@ -262,6 +262,7 @@ __host__ inline PrefillPlan prefill_halved(PrefillPlan plan, int kv_dtype, int h
 // blocks, 32 rows, over bf16 pools are bound by that where many sequences are walked at once: 24 of 5.7 - 6.4 k, 22 - 58 queries, 8/2 heads fetch 583 MB
 // instead of 156 and take 108 instead of 72 us.  1260 such calls, 2 and 4 heads, by sequences: under 12 1.14 (d = 64: 1.07), 12 - 19 .97 (1.00), 20 and more .86
 // (.84, down to .53).  Over fp8 pools, half the bytes, they gain: 1.24 and 1.23 with 2 and 4 heads (d = 64 1.19, 1.08).
+// (Calls left to the kernel are not asked about here: prefill_slot orders them.)
 __host__ inline int prefill_order(const PrefillPlan &plan, int kv_dtype, int head_dim, int64_t total_q, int units, int batch, int heads, int q_blocks, int max_context_len)
 {
     if (batch == 1 || batch > kMaxOrderedBatch || max_context_len < kPrefillShort) return 0;
